@@ -66,8 +66,11 @@ enum vns_option {
                              up to 4 entries (default 0x421 = flip zM, flip zR, shift)                   */
     VNS_OPT_TRACE = 4,    /* 1 = vns_run keeps one record per chain and iteration (default 1)           */
     VNS_OPT_RUN_WAVES = 5, /* wavefronts per workgroup of the search kernel, 1..8 (default 8)           */
-    VNS_OPT_EVAL_GROUP = 6, /* chains of one instance priced together by one pricing workgroup, 1..16
-                              (default 4); a tuning knob, results do not depend on it                   */
+    VNS_OPT_EVAL_GROUP = 6, /* chains of one instance priced together by one pricing workgroup of the full
+                              decode, 1..16 (default 4); a tuning knob, results do not depend on it.
+                              Interval pricing (every context whose products have demand and return sums
+                              below 2^23 and worst-case costs below 2^31, without the disposal reading)
+                              has its own launch shape                                                 */
     VNS_OPT_RUN_LDS = 7,   /* bytes of LDS the search kernel may use to keep an instance's rows resident,
                               0..131072 (default 65536); a tuning knob, results do not depend on it     */
     VNS_OPT_GRAPH = 8,     /* 1 = vns_run captures its launch (search kernel + iteration-counter advance)
@@ -128,7 +131,10 @@ enum vns_option {
                               pattern's state there, until its state equals the current pattern's again
                               (the rest of the cost then differs by known amounts) or it turns
                               infeasible.  Same prices, argmins and counted evaluations;
-                              vns_stats.last_eval_decoded_steps reports the period-steps decoded      */
+                              vns_stats.last_eval_decoded_steps reports the period-steps decoded.
+                              Interval pricing (see VNS_OPT_EVAL_GROUP) always works this way, by setup
+                              intervals: with this option it reports the pattern's own T periods per
+                              (chain, product), one step per move and one per later interval priced anew */
     VNS_OPT_DECODE = 19,   /* decode reading, a bit set (default 0); the paper leaves both points open
                               (Section 2 names returns and recoverable stock without the rules):
                               bit 1 (strict): a period whose latest setup is remanufacturing only must be
@@ -151,7 +157,7 @@ enum vns_option {
                               (one for W = 16), each pricing every move of its range (a range spans a
                               few products when their rows fit its LDS); 0 (default) = one workgroup
                               per product and group of VNS_OPT_EVAL_GROUP chains.  Same prices and
-                              argmins.  Not used with incremental pricing                             */
+                              argmins.  Not used with incremental or interval pricing                 */
 };
 
 /* One GVNS iteration of one chain. */

@@ -1,0 +1,443 @@
+// Interval pricing: the exact cost of every move of a pattern from one parallel decode of the pattern itself.
+//
+// The forward decode needs no period-by-period walk.  Between two setups the limit, the last remanufacturing
+// and the last manufacturing setup are fixed, so a setup interval with demand d remanufactures
+// min(XR + d, lim) - XR units as a whole; and an interval's only effect on what follows is XR (and, until the
+// next manufacturing setup, which period makes the shortfalls).  So a move at period t changes the pattern's
+// cost in three places:
+//   * its own one or two intervals, recomputed from the state before t;
+//   * later remanufacturing intervals, while the total remanufactured differs from the unchanged pattern's by
+//     d != 0: an interval that had shortage c (units of its demand not remanufactured) and headroom E (returns
+//     left over), at most one of them positive, turns d into min(d + c, E), and the difference is made at its
+//     own periods instead, weight w per unit.  |d| never grows and most moves are done after one or two;
+//   * the shortfalls up to the next manufacturing setup M1, when the move changes which period makes them.
+// One lane holds one period (two for T > 63): the pattern's own states come from five wavefront scans, and every
+// move of the lane's period is then priced from registers, one 8-byte record of the next setup and of M1, and
+// the remanufacturing intervals' records {c, E, w, period} in LDS.
+//
+// What bounds it: VALU issue (97% of the issue slots in the 256 x 16 sweep).  A full decode costs every move 14 T
+// operations (728 at T = 52); here the scans and records are about 130 instructions per pattern, a move takes
+// 20 to 35, and two records of a walk 11 to 15, of which the slowest of 64 lanes needs 3 to 5 pairs (1.3 records on
+// average; local optima, T = 52): 500 instructions for a pattern's 156 slots in place of 2000.  Best move of every
+// pattern of 256 instances (K 100..1000, T 52 or 104) x 16 chains: 15.9 -> 3.05 ms; of 1024 instances (K 10..200, T
+// 12, 24 or 52) x 8: 1.18 -> 0.43 ms.  Short horizons share a wavefront (16 or 32 lanes per pattern), which halves the
+// instructions per pattern at T = 24 and quarters them at T = 12.
+//
+// Integers: for a "compact" product (compact_product below: sums of demand and returns, weights and unit terms
+// below 2^23, worst-case cost below 2^31) every product here has two signed 24-bit factors and every sum is
+// taken modulo 2^32 with a result below 2^31, so 32-bit arithmetic is exact; contexts with other products and
+// the disposal reading keep the period-by-period decode.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "vns_device.hpp"
+
+namespace vns {
+
+constexpr int32_t kBad32 = INT32_MAX;   // price of an infeasible move or of a slot that is no move
+
+namespace iv {
+
+// Inclusive scans over groups of G lanes with identity 0 (the group's lanes are in order): row shifts, then the
+// last lane of each row of 16 into the next rows.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp0(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, ROWS == 0xf);
+}
+template <int G, class Op>
+__device__ __forceinline__ uint32_t scan(uint32_t x, Op op) {
+    x = op(x, dpp0<0x111, 0xf>(x));
+    x = op(x, dpp0<0x112, 0xf>(x));
+    x = op(x, dpp0<0x114, 0xf>(x));
+    x = op(x, dpp0<0x118, 0xf>(x));
+    if constexpr (G >= 32) x = op(x, dpp0<0x142, 0xa>(x));   // lane 15 of rows 0, 2 into rows 1, 3
+    if constexpr (G >= 64) x = op(x, dpp0<0x143, 0xc>(x));   // lane 31 into rows 2, 3
+    return x;
+}
+template <int G>
+__device__ __forceinline__ uint32_t scan_add(uint32_t x) {
+    return scan<G>(x, [](uint32_t a, uint32_t b) { return a + b; });
+}
+template <int G>
+__device__ __forceinline__ uint32_t scan_max(uint32_t x) {
+    return scan<G>(x, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+}
+// The previous lane's value (0 before the wavefront's first lane) and the next lane's (last after the last).
+__device__ __forceinline__ uint32_t prev_lane(uint32_t x, uint32_t first = 0) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)x, 0x138, 0xf, 0xf, false);
+}
+__device__ __forceinline__ int32_t next_lane(int32_t x, int32_t last = 0) {
+    return __builtin_amdgcn_update_dpp(last, x, 0x130, 0xf, 0xf, false);
+}
+__device__ __forceinline__ int32_t last_lane(uint32_t x) { return __builtin_amdgcn_readlane((int)x, 63); }
+
+// acc + a * b, a and b signed 24-bit
+__device__ __forceinline__ int32_t mad24(int32_t a, int32_t b, int32_t acc) { return __mul24(a, b) + acc; }
+
+// A product's parameters in 32 bits (exact for a compact product).
+struct Cost {
+    int32_t kM, kR, hM, wd;   // wd = hR - hM: a remanufactured unit's weight per period of its lot
+    int32_t cXR;
+};
+__device__ __forceinline__ Cost cost_of(const ProdParams &pp) {
+    return Cost{pp.kM, pp.kR, pp.hM, pp.hR - pp.hM, (int32_t)pp.cXR};
+}
+
+// A group of G lanes prices one pattern: one period per lane for T <= G, G = 16, 32 or 64, or two periods per lane
+// for T <= 128 (G = 64, NV = 2).
+template <int G>
+using Word = typename std::conditional<(G < 64), uint32_t, uint64_t>::type;
+
+// Setup bits, word v: periods 64 v ...  G = 64: the same words in every lane (scalar registers); fewer: per lane.
+template <int G, int NV>
+struct Masks {
+    Word<G> m[NV], r[NV];
+};
+
+template <int G, int NV>
+__device__ __forceinline__ Masks<G, NV> masks_of(const Bits &b) {
+    Masks<G, NV> k;
+    if constexpr (G < 64) {
+        k.m[0] = b.m[0];
+        k.r[0] = b.r[0];
+    } else {
+        auto word = [](uint32_t lo, uint32_t hi) {
+            return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)lo) |
+                   (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)hi) << 32;
+        };
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            k.m[v] = word(b.m[2 * v], b.m[2 * v + 1]);
+            k.r[v] = word(b.r[2 * v], b.r[2 * v + 1]);
+        }
+    }
+    return k;
+}
+
+// This lane's bit of a word.
+template <int G>
+__device__ __forceinline__ bool lane_bit(Word<G> w) {
+    if constexpr (G < 64) return (w >> (threadIdx.x & (G - 1))) & 1u;
+    else return __builtin_amdgcn_inverse_ballot_w64(w);
+}
+// The word of the next periods' bits: bit t = bit t + 1 of z.
+template <int G, int NV>
+__device__ __forceinline__ Word<G> next_bits(const Word<G> (&z)[NV], int v) {
+    if constexpr (NV == 1) return z[0] >> 1;
+    else return v == 0 ? (z[0] >> 1) | (z[1] << 63) : z[1] >> 1;
+}
+// Periods t with t + 1 < T whose bits t and t + 1 of z differ: the swaps that are moves.
+template <int G, int NV>
+__device__ __forceinline__ Word<G> swap_bits(const Word<G> (&z)[NV], int v, int T) {
+    const int lim = T - 1 - 64 * v;   // periods of this word
+    const Word<G> all = (Word<G>)~(Word<G>)0;
+    const Word<G> keep = lim <= 0 ? (Word<G>)0 : lim >= 8 * (int)sizeof(Word<G>) ? all : (Word<G>)~(all << lim);
+    return (z[v] ^ next_bits<G, NV>(z, v)) & keep;
+}
+
+// LDS of one wavefront: per group, pos[k] = (XR, H) before period k, H the units manufactured (the demand before k
+// less XR), and the remanufacturing setups' records with two that end every walk.
+template <int G, int NV>
+struct Lds {
+    static constexpr int kPos = G * NV + 1;
+    static constexpr int kRec = G * NV + 2;
+    int4 rec[(64 / G) * kRec];
+    int2 pos[(64 / G) * kPos];
+};
+
+// One period of the unchanged pattern.
+struct Period {
+    int32_t t, D, PR;
+    int32_t xb, xa, Hb;           // XR before and after t, H before t
+    int32_t lmz, lsz, cap0;       // last M and R setup before t (0 if none), returns at the latter
+    int32_t lm;                   // last M setup up to t
+    int32_t ls;                   // last R setup up to t
+    int32_t XRn, Hn, Hm;          // XR and H before the next setup after t, H before the next M setup after t
+    int32_t M1;                   // the latter's period, or T
+    int32_t j;                    // R setups up to t: the ordinal of the first one after t
+    int32_t w;                    // cost of a unit remanufactured for a period of t's interval
+    bool m, r;
+    bool reg0, hm0, hm;           // remanufacturing open before t; an M setup before t, up to t
+    bool blk0;                    // strict reading: no manufacturing allowed before t
+};
+
+__device__ __forceinline__ void lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A row past the horizon: no demand, and returns that never bind.
+__device__ __forceinline__ int2 no_row() { return make_int2(0, 1 << 23); }
+
+// A pattern's periods in this lane, and the cost change of its moves.
+template <int G, int NV, bool STRICT>
+struct Pattern {
+    Period p[NV];
+    const int4 *rec;   // this group's records
+
+    // row: this lane's periods' rows (no_row() past T).
+    __device__ __forceinline__ void build(const Masks<G, NV> &k, const int2 (&row)[NV], int T, const Cost &c,
+                                          Lds<G, NV> &sh) {
+        const int lane = threadIdx.x & 63, t0 = lane & (G - 1), grp = lane / G;
+        int4 *grec = sh.rec + grp * Lds<G, NV>::kRec;
+        int2 *pos = sh.pos + grp * Lds<G, NV>::kPos;
+        rec = grec;
+        uint32_t lm1[NV], key[NV], pda[NV];   // last setups as period + 1; key = returns at the last R setup << 8 | it
+        // 1. last setups, open capacity, demand and remanufactured units up to each period
+        int32_t cm = 0, ckey = 0, cpd = 0, cA = 0, cS = 0;   // carries into the second word
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            Period &q = p[v];
+            q.t = t0 + 64 * v;
+            q.D = row[v].x;
+            q.PR = row[v].y;
+            q.m = lane_bit<G>(k.m[v]);
+            q.r = lane_bit<G>(k.r[v]);
+            lm1[v] = scan_max<G>(q.m ? (uint32_t)(q.t + 1) : 0u);
+            key[v] = scan_max<G>(q.r ? ((uint32_t)q.PR << 8) + (uint32_t)(q.t + 1) : 0u);   // returns never drop
+            pda[v] = scan_add<G>((uint32_t)q.D);
+            if (v > 0) {
+                lm1[v] = max(lm1[v], (uint32_t)cm);
+                key[v] = max(key[v], (uint32_t)ckey);
+                pda[v] += (uint32_t)cpd;
+            }
+            const uint32_t ls1 = key[v] & 255u;
+            const bool open = ls1 >= max(lm1[v], 1u);
+            // while open, XR follows the demand A of the open periods and lags by the largest excess of A over the
+            // open capacity so far (XR <- min(XR + d, cap) composed over the periods)
+            const uint32_t A = scan_add<G>(open ? (uint32_t)q.D : 0u) + (v > 0 ? (uint32_t)cA : 0u);
+            uint32_t S = scan_max<G>((uint32_t)(open ? max((int32_t)A - (int32_t)(key[v] >> 8), 0) : 0));
+            if (v > 0) S = max(S, (uint32_t)cS);
+            q.xa = (int32_t)(A - S);
+            pos[q.t + 1] = make_int2(q.xa, (int)pda[v] - q.xa);
+            if (NV > 1 && v == 0) {
+                cm = last_lane(lm1[0]);
+                ckey = last_lane(key[0]);
+                cpd = last_lane(pda[0]);
+                cA = last_lane(A);
+                cS = last_lane(S);
+            }
+        }
+        lds_fence();
+        // 2. the state before each period, the next setup and the next M setup
+        int nR = 0;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            Period &q = p[v];
+            uint32_t l0, k0, x0;
+            if (v > 0) {
+                l0 = prev_lane(lm1[v], last_lane(lm1[v - 1]));
+                k0 = prev_lane(key[v], last_lane(key[v - 1]));
+                x0 = prev_lane((uint32_t)q.xa, last_lane((uint32_t)p[v - 1].xa));
+            } else {
+                l0 = prev_lane(lm1[v]);
+                k0 = prev_lane(key[v]);
+                x0 = prev_lane((uint32_t)q.xa);
+                if (G < 64 && t0 == 0) l0 = k0 = x0 = 0u;
+            }
+            const uint32_t s0 = k0 & 255u, s1 = key[v] & 255u;
+            q.xb = (int32_t)x0;
+            q.Hb = (int32_t)pda[v] - q.D - q.xb;
+            q.hm0 = l0 != 0u;
+            q.hm = lm1[v] != 0u;
+            q.lmz = (int32_t)max(l0, 1u) - 1;
+            q.lm = (int32_t)max(lm1[v], 1u) - 1;
+            q.lsz = (int32_t)max(s0, 1u) - 1;
+            q.ls = (int32_t)max(s1, 1u) - 1;
+            q.cap0 = (int32_t)(k0 >> 8);
+            q.reg0 = s0 >= max(l0, 1u);
+            q.blk0 = s0 > l0 || l0 == 0u;
+            const int n = next_setup(k.m, k.r, v, t0, T);
+            q.M1 = next_setup(k.m, k.m, v, t0, T);
+            if constexpr (G < 64) {
+                q.j = __popc(k.r[0] & ~(~0u << 1 << t0));
+                nR = __popc(k.r[0]);
+            } else {
+                q.j = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(k.r[v] >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)k.r[v], (uint32_t)nR)) +
+                      (q.r ? 1 : 0);
+                nR += __popcll(k.r[v]);
+            }
+            const int2 an = pos[n];
+            q.XRn = an.x;
+            q.Hn = an.y;
+            q.Hm = pos[q.M1].y;
+            q.w = mad24(c.hM, q.lm, __mul24(c.wd, q.ls));
+            // 3. the record of a remanufacturing setup (its ls is t itself)
+            if (q.r) grec[q.j - 1] = make_int4(q.Hn - q.Hb, q.PR - q.XRn, q.w, STRICT && !q.m ? q.t + 256 : q.t);
+        }
+        // the horizon's end takes every difference: its units are worth -cXR each
+        if (t0 == 0) {
+            grec[nR] = make_int4(1 << 28, 0, -c.cXR, 255);
+            grec[nR + 1] = make_int4(0, 0, 0, 255);
+        }
+        lds_fence();
+    }
+
+    // The first setup after period t0 + 64 v of the words a | b (lane-varying), or T; T in the lanes past the horizon.
+    static __device__ __forceinline__ int next_setup(const Word<G> (&a)[NV], const Word<G> (&b)[NV], int v, int t0, int T) {
+        if constexpr (G < 64) {
+            return min(__builtin_ctzg((a[0] | b[0]) & (~0u << 1 << t0), 32), T);
+        } else if constexpr (NV == 1) {
+            return min(__builtin_ctzg((a[0] | b[0]) & (~0ull << 1 << t0), 64), T);
+        } else {
+            const uint64_t hi = a[1] | b[1], x = (v ? hi : a[0] | b[0]) & (~0ull << 1 << t0);
+            const int past = v == 0 && hi ? 64 + __builtin_ctzll(hi) : T;
+            return x ? 64 * v + __builtin_ctzll(x) : past;
+        }
+    }
+
+    // The pattern's own cost without the setups' and the constant: sum of u w - hM D lm over the periods, plus cXR XR
+    // (modulo 2^32), in every lane of a wavefront (G = 64).
+    __device__ __forceinline__ int32_t own_cost(const Cost &c) const {
+        static_assert(G == 64, "one pattern per wavefront");
+        uint32_t s = 0;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const Period &q = p[v];
+            s += (uint32_t)(__mul24(q.xa - q.xb, q.w) - __mul24(q.D, __mul24(c.hM, q.lm)));
+        }
+        s = scan_add<64>(s);
+        const int32_t xr = last_lane((uint32_t)p[NV - 1].xa);
+        return last_lane(s) + __mul24(c.cXR, xr);
+    }
+
+    // The difference d of the remanufactured units passed on to R setup j and those after it; returns its cost.
+    // dM: what is left of it at M1.  Two records per round: the one after the horizon's changes nothing.
+    template <bool TRACK>
+    __device__ __forceinline__ int32_t walk(int j, int32_t d, int32_t M1, int32_t &dM, bool &bad, int &steps) const {
+        int32_t acc = 0;
+        const int4 *at = rec + j;
+        dM = d;
+        while (d != 0) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int4 q = at[h];
+                const int32_t dn = min(d + q.x, q.y), du = dn - d;
+                acc = mad24(du, q.z, acc);
+                if constexpr (TRACK) dM = (STRICT ? q.w & 255 : q.w) < M1 ? dn : dM;
+                if constexpr (STRICT) bad |= q.w > 255 && du < 0;   // a remanufacture-only interval runs short
+                d = dn;
+            }
+            at += 2;
+            steps += 2;
+        }
+        return acc;
+    }
+
+    // Cost change of flipping zM(t).  The interval of t: nothing changes if t remanufactures; else a new M setup closes
+    // what was open before t (v0 units), and a removed one leaves it open.
+    __device__ __forceinline__ int32_t flip_m(const Period &q, const Cost &c, int &steps) const {
+        const int32_t dseg = (q.XRn + q.Hn) - (q.xb + q.Hb);
+        const int32_t v0 = q.reg0 ? min(dseg, q.cap0 - q.xb) : 0;
+        const int32_t d = q.r ? 0 : q.m ? v0 : -v0;
+        const int32_t wL = mad24(c.hM, q.lm, __mul24(c.wd, q.lsz));
+        bool bad = false;
+        int32_t dM;
+        const int32_t x = mad24(d, wL, walk<true>(q.j, d, q.M1, dM, bad, steps));
+        const int32_t S = q.Hm - q.Hb - dM;   // shortfalls up to M1, made at t or at the M setup before it
+        const int32_t y = c.kM - __mul24(__mul24(c.hM, q.t - q.lmz), S);
+        bad |= q.m && !q.hm0 && S > 0;
+        if constexpr (STRICT) bad |= q.m && (q.r || q.blk0) && dseg - (q.XRn - q.xb + d) > 0;
+        return bad ? kBad32 : x + (q.m ? -y : y);
+    }
+
+    // Cost change of flipping zR(t): the interval remanufactures a units with it, b without.
+    __device__ __forceinline__ int32_t flip_r(const Period &q, const Cost &c, int &steps) const {
+        const int32_t dseg = (q.XRn + q.Hn) - (q.xb + q.Hb), hl = __mul24(c.hM, q.lm);
+        const int32_t a = min(dseg, q.PR - q.xb), b = q.reg0 && !q.m ? min(dseg, q.cap0 - q.xb) : 0;
+        const int32_t y = __mul24(a, mad24(c.wd, q.t, hl)) - __mul24(b, mad24(c.wd, q.lsz, hl)) + c.kR;
+        const int32_t d = q.r ? b - a : a - b;
+        bool bad = false;
+        int32_t dM, x;
+        if (__any(!q.hm)) {   // before the first M setup a shortfall cannot be made
+            x = walk<true>(q.j, d, q.M1, dM, bad, steps);
+            bad |= !q.hm && q.Hm - q.Hb - dM > 0;
+        } else {
+            x = walk<false>(q.j, d, q.M1, dM, bad, steps);
+        }
+        if constexpr (STRICT) bad |= !q.m && dseg - (q.r ? b : a) > 0 && (!q.r || q.blk0);
+        return bad ? kBad32 : x + (q.r ? -y : y);
+    }
+
+    // What a swap of periods t, t + 1 needs of period t + 1.
+    struct Next {
+        int32_t PR, M1, XRn, Hn, Hm, j, w;
+        bool m, r;
+    };
+    __device__ __forceinline__ void next_of(const Masks<G, NV> &k, Next (&x)[NV]) const {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const Period &q = p[v], &o = p[NV - 1];   // the second word's lane 0 follows lane 63
+            auto nx = [&](int32_t a, int32_t b) {
+                return next_lane(a, NV > 1 && v == 0 ? __builtin_amdgcn_readlane(b, 0) : 0);
+            };
+            x[v].PR = nx(q.PR, o.PR);
+            x[v].M1 = nx(q.M1, o.M1);
+            x[v].XRn = nx(q.XRn, o.XRn);
+            x[v].Hn = nx(q.Hn, o.Hn);
+            x[v].Hm = nx(q.Hm, o.Hm);
+            x[v].w = nx(q.w, o.w);
+            x[v].m = lane_bit<G>(next_bits<G, NV>(k.m, v));
+            x[v].r = lane_bit<G>(next_bits<G, NV>(k.r, v));
+            x[v].j = q.j + (x[v].r ? 1 : 0);
+        }
+    }
+
+    // Cost change of swapping zM(t), zM(t + 1), which differ.  e0, e1: more units remanufactured for period t and for
+    // t + 1 up to the next setup; their lots are the pattern's own.  What is manufactured for t and, up to the next
+    // M setup, after it moves by one period or back to the M setup before t.
+    __device__ __forceinline__ int32_t swap_m(const Period &q, const Next &x, const Cost &c, bool valid, int &steps) const {
+        const int32_t Ha = q.Hb + q.D - (q.xa - q.xb), d1 = (x.XRn + x.Hn) - (q.xa + Ha);
+        const int32_t c0 = q.reg0 ? min(q.D, q.cap0 - q.xb) : 0;
+        const int32_t e0 = q.r ? 0 : q.m ? c0 : -c0;
+        const int32_t x1 = q.xa + e0;
+        const int32_t u1 = x.r ? min(d1, x.PR - x1) : q.r && !q.m ? min(d1, q.PR - q.xa) : 0;
+        const int32_t e1 = u1 - (x.XRn - q.xa);
+        const int32_t d = valid ? e0 + e1 : 0;
+        bool bad = false;
+        int32_t dM;
+        const int32_t y = mad24(e1, x.w, mad24(e0, q.w, walk<true>(x.j, d, x.M1, dM, bad, steps)));
+        const int32_t S = x.Hm - dM - (Ha - e0), made0 = q.D - (x1 - q.xb);
+        const int32_t z = __mul24(c.hM, S) - __mul24(__mul24(c.hM, q.t - q.lmz), made0);
+        bad |= q.m && !q.hm0 && made0 > 0;
+        if constexpr (STRICT) {
+            const bool blk = q.m && (q.r || q.blk0);   // m: the M setup leaves t
+            bad |= blk && made0 > 0;
+            bad |= !q.m && x.r && d1 - u1 > 0;         // !m: it leaves t + 1
+        }
+        return bad ? kBad32 : y + (q.m ? -z : z);
+    }
+
+    // Cost change of swapping zR(t), zR(t + 1), which differ.
+    __device__ __forceinline__ int32_t swap_r(const Period &q, const Next &x, const Cost &c, bool valid, int &steps) const {
+        const int32_t hl = __mul24(c.hM, q.lm), Ha = q.Hb + q.D - (q.xa - q.xb), d1 = (x.XRn + x.Hn) - (q.xa + Ha);
+        const int32_t a0 = min(q.D, q.PR - q.xb), b0 = q.reg0 && !q.m ? min(q.D, q.cap0 - q.xb) : 0;
+        const int32_t y0 = __mul24(a0, mad24(c.wd, q.t, hl)) - __mul24(b0, mad24(c.wd, q.lsz, hl));
+        const int32_t u0 = q.r ? b0 : a0, x1 = q.xb + u0;
+        const int32_t u1 = q.r ? min(d1, x.PR - x1) : x.m ? 0 : min(d1, q.PR - x1);
+        const int32_t w1 = mad24(c.wd, q.t + (q.r ? 1 : 0), x.m ? __mul24(c.hM, q.t + 1) : hl);
+        const int32_t d = valid ? x1 + u1 - x.XRn : 0;
+        int32_t y = mad24(u1, w1, q.r ? -y0 : y0) - __mul24(x.XRn - q.xa, x.w);
+        bool bad = false;
+        int32_t dM;
+        if (__any(valid && !q.hm)) {
+            y += walk<true>(x.j, d, x.M1, dM, bad, steps);
+            bad |= !q.hm && q.D - u0 > 0;
+            bad |= !(q.hm || x.m) && x.Hm - dM - (q.Hb + q.D - u0) > 0;
+        } else {
+            y += walk<false>(x.j, d, x.M1, dM, bad, steps);
+        }
+        if constexpr (STRICT) {
+            const bool blk = !q.m && (!q.r || q.blk0);   // after t: an R-only setup came to it, or it lost one
+            bad |= blk && q.D - u0 > 0;
+            bad |= !x.m && (q.r || blk) && d1 - u1 > 0;
+        }
+        return bad ? kBad32 : y;
+    }
+};
+
+}  // namespace iv
+}  // namespace vns

@@ -16,6 +16,7 @@
 #include <algorithm>
 
 #include "vns_device.hpp"
+#include "vns_interval.hpp"
 #include "vns_launch.hpp"
 #include "vns_search.hpp"
 
@@ -432,6 +433,168 @@ __global__ __launch_bounds__(256) void k_eval_inc(EvalArgs a, const EvalWg *__re
     __shared__ EvalShared sh;
     extern __shared__ __attribute__((aligned(16))) int4 s_snap[];
     eval_body<true>(a, wg, sh, s_snap);
+}
+
+// ---------------------------------------------------------------------------------------------------
+// k_eval_iv: the sweep by interval pricing.  A wavefront takes per_wave consecutive (chain, product) pairs, one at
+// a time for T > 32, two at a time (32 lanes each) for T > 16, four at a time up to 16, and prices the four slot
+// blocks of each with one period per lane.  No workgroup synchronisation and no move list: a slot is (block,
+// lane).
+// ---------------------------------------------------------------------------------------------------
+namespace {
+
+// A value every lane of the wavefront reads alike, through the scalar cache (written before the launch only).
+template <class T>
+__device__ __forceinline__ T load_uniform(const T *p) {
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    typedef const __attribute__((address_space(4))) uint32_t *Words;
+    const Words w = (Words)(uintptr_t)p;
+    uint32_t r[sizeof(T) / 4];
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 4; ++i) r[i] = w[i];
+    T out;
+    __builtin_memcpy(&out, r, sizeof(T));
+    return out;
+}
+
+template <int G, int NV, bool STRICT, bool STEPS>
+__device__ __forceinline__ void eval_unit(const EvalArgs &a, const ChainInfo &ci, int g, int64_t F, int64_t cp, int cnt,
+                                          iv::Lds<G, NV> &sh, uint32_t &moves, uint32_t &decoded) {
+    const int lane = threadIdx.x & 63, t0 = lane & (G - 1), grp = lane / G;
+    const int T = ci.T, p0 = (int)(cp - ci.cp0);
+    const int my = G == 64 ? 0 : min(grp, cnt - 1);   // a group without a pair repeats the last one's
+    const bool live = G == 64 || grp < cnt;
+    int2 row[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int t = t0 + 64 * v;
+        row[v] = t < T ? a.rows[ci.row0 + (p0 + my) * T + t] : iv::no_row();
+    }
+    const ProdParams pp = G == 64 ? load_uniform(a.prod + ci.prod0 + p0) : a.prod[ci.prod0 + p0 + my];
+    const Bits b = G == 64 ? load_uniform(a.cur + cp) : a.cur[cp + my];
+    const int64_t base = G == 64 ? load_uniform(a.cur_cost + cp) : a.cur_cost[cp + my];
+    const iv::Cost c = iv::cost_of(pp);
+    const iv::Masks<G, NV> k = iv::masks_of<G, NV>(b);
+    iv::Pattern<G, NV, STRICT> pat;
+    pat.build(k, row, T, c, sh);
+
+    const bool fm = a.nb_mask & 1u, fr = a.nb_mask & 2u, shift = a.nb_mask & 4u;
+    int32_t x[4][NV];   // cost changes by slot block
+    iv::Word<G> vm[NV], vr[NV];
+    int steps = 0;
+    uint32_t n = (fm ? T : 0) + (fr ? T : 0);
+    typename iv::Pattern<G, NV, STRICT>::Next nx[NV];
+    if (shift) pat.next_of(k, nx);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const iv::Period &q = pat.p[v];
+        const bool in = q.t < T;
+        x[0][v] = x[1][v] = x[2][v] = x[3][v] = kBad32;
+        if (fm) {
+            const int32_t y = pat.flip_m(q, c, steps);
+            x[0][v] = in ? y : kBad32;
+        }
+        if (fr) {
+            const int32_t y = pat.flip_r(q, c, steps);
+            x[1][v] = in ? y : kBad32;
+        }
+        if (shift) {
+            vm[v] = iv::swap_bits<G, NV>(k.m, v, T);
+            vr[v] = iv::swap_bits<G, NV>(k.r, v, T);
+            const bool sm = iv::lane_bit<G>(vm[v]), sr = iv::lane_bit<G>(vr[v]);
+            const int32_t y = pat.swap_m(q, nx[v], c, sm, steps), z = pat.swap_r(q, nx[v], c, sr, steps);
+            x[2][v] = sm ? y : kBad32;
+            x[3][v] = sr ? z : kBad32;
+            n += G < 64 ? __popc((uint32_t)vm[v]) + __popc((uint32_t)vr[v]) : __popcll(vm[v]) + __popcll(vr[v]);
+        }
+    }
+    if (a.slot_price) {
+        int64_t *out = a.slot_price + (a.price_off[g] + (int64_t)(p0 + my) * 4 * T);
+#pragma unroll
+        for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const int t = t0 + 64 * v;
+                if (live && t < T) out[blk * T + t] = x[blk][v] == kBad32 ? kInf : F + x[blk][v];
+            }
+    }
+    // the lowest (cost, slot): the cost first, then the lowest slot that has it.  (x as unsigned from the lowest int32:
+    // kBad32 is the largest.)
+    uint32_t low = 0;
+#pragma unroll
+    for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) low = max(low, ~((uint32_t)x[blk][v] ^ 0x80000000u));
+    low = iv::scan_max<G>(low);
+    const int last = lane | (G - 1);
+    int slot = 0;
+    if constexpr (G == 64) {
+        const int32_t best = (int32_t)(~(uint32_t)iv::last_lane(low) ^ 0x80000000u);
+#pragma unroll
+        for (int blk = 3; blk >= 0; --blk)
+#pragma unroll
+            for (int v = NV - 1; v >= 0; --v) {
+                const uint64_t at = __ballot(x[blk][v] == best);
+                slot = at ? blk * T + 64 * v + __builtin_ctzll(at) : slot;
+            }
+        if (lane == 0)
+            a.prod_key[cp] = best == kBad32 ? kInfKey : ((uint64_t)(base + best) << kSlotBits) | (uint64_t)slot;
+    } else {
+        const int32_t best = (int32_t)(~(uint32_t)__shfl((int)low, last, 64) ^ 0x80000000u);
+        uint32_t at = 0;
+#pragma unroll
+        for (int blk = 3; blk >= 0; --blk) at = x[blk][0] == best ? 0x10000u - (uint32_t)(blk * T + t0) : at;
+        at = iv::scan_max<G>(at);
+        if (lane == last && live)
+            a.prod_key[cp + my] =
+                best == kBad32 ? kInfKey : ((uint64_t)(base + best) << kSlotBits) | (uint64_t)(0x10000u - at);
+    }
+    if (t0 == 0 && live) moves += n;
+    if constexpr (STEPS) decoded += live ? (uint32_t)steps + (t0 == 0 ? n + (uint32_t)T : 0u) : 0u;
+}
+
+}  // namespace
+
+template <bool LONG, bool STRICT, bool STEPS>
+__global__ __launch_bounds__(256) void k_eval_iv(EvalArgs a, int64_t cp_begin, int64_t n_cp, int32_t per_wave) {
+    constexpr size_t kBytes = std::max({sizeof(iv::Lds<16, 1>), sizeof(iv::Lds<32, 1>), sizeof(iv::Lds<64, 1>),
+                                        LONG ? sizeof(iv::Lds<64, 2>) : (size_t)0});
+    __shared__ __attribute__((aligned(16))) unsigned char lds[4][kBytes];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t first = ((int64_t)blockIdx.x * 4 + wave) * per_wave;
+    const int64_t end = cp_begin + min(first + per_wave, n_cp);
+    uint32_t moves = 0, psteps = 0, decoded = 0;   // per lane (at most 16 pairs of 4 T <= 512 moves)
+    for (int64_t cp = cp_begin + first; cp < end;) {
+        const int g = load_uniform(a.cp_chain + cp);
+        const ChainInfo ci = load_uniform(a.chains + g);
+        const int64_t F = a.slot_price ? load_uniform(&a.cstate[g].F) : 0;
+        const int64_t left = min(end, ci.cp0 + ci.K) - cp;
+        const int T = ci.T;
+        uint32_t m = 0;
+        int cnt = 1;
+        if (T <= 16) {
+            cnt = (int)min(left, (int64_t)4);
+            eval_unit<16, 1, STRICT, STEPS>(a, ci, g, F, cp, cnt, *reinterpret_cast<iv::Lds<16, 1> *>(lds[wave]), m, decoded);
+        } else if (T <= 32) {
+            cnt = (int)min(left, (int64_t)2);
+            eval_unit<32, 1, STRICT, STEPS>(a, ci, g, F, cp, cnt, *reinterpret_cast<iv::Lds<32, 1> *>(lds[wave]), m, decoded);
+        } else if (!LONG || T <= 64) {
+            eval_unit<64, 1, STRICT, STEPS>(a, ci, g, F, cp, cnt, *reinterpret_cast<iv::Lds<64, 1> *>(lds[wave]), m, decoded);
+        } else if constexpr (LONG) {
+            eval_unit<64, 2, STRICT, STEPS>(a, ci, g, F, cp, cnt, *reinterpret_cast<iv::Lds<64, 2> *>(lds[wave]), m, decoded);
+        }
+        moves += m;
+        psteps += m * (uint32_t)T;
+        cp += cnt;
+    }
+    const int32_t n = iv::last_lane(iv::scan_add<64>(moves)), ps = iv::last_lane(iv::scan_add<64>(psteps));
+    const int32_t dec = STEPS ? iv::last_lane(iv::scan_add<64>(decoded)) : ps;
+    if (lane == 0 && first < n_cp) {
+        unsigned long long *ctr = a.evals + (size_t)((blockIdx.x * 4 + wave) & (kCounterSlots - 1)) * kCounterStride;
+        atomicAdd(ctr, (unsigned long long)n);
+        atomicAdd(ctr + 1, (unsigned long long)ps);
+        atomicAdd(ctr + 2, (unsigned long long)dec);
+    }
 }
 
 // The pricing table for chains g0 .. g0+ng-1 and zeroed counters, on the device (see EvalPrepArgs).
@@ -1557,6 +1720,32 @@ hipError_t launch_eval(const EvalArgs &a, const EvalWg *wg, int64_t n_wg, hipStr
     void *params[] = {&args, &w};
     const void *fn = waves == 4 ? by_model<PickEval>(model) : by_model<PickEvalWide>(model);
     return hipLaunchKernel(fn, dim3((unsigned)n_wg), dim3(64 * waves), params, 0, s);
+}
+
+hipError_t launch_eval_iv(const EvalArgs &a, int64_t cp_begin, int64_t n_cp, int n_cu, bool long_T, bool count_steps,
+                          hipStream_t s, int model) {
+    if (n_cp <= 0) return hipSuccess;
+    // about 16 wavefronts per SIMD's worth of ranges, at most 16 pairs each (a multiple of 4: short horizons are priced
+    // four pairs at a time)
+    int64_t per = n_cp / ((int64_t)n_cu * 64);
+    per = per < 1 ? 1 : per > 16 ? 16 : per > 3 ? per & ~(int64_t)3 : per;
+    const int32_t per_wave = (int32_t)per;
+    const int64_t waves = (n_cp + per - 1) / per;
+    const dim3 grid((unsigned)((waves + 3) / 4)), block(256);
+    const bool strict = (model & kModelStrict) != 0;
+#define VNS_IV(L, S, C) hipLaunchKernelGGL((k_eval_iv<L, S, C>), grid, block, 0, s, a, cp_begin, n_cp, per_wave)
+    if (count_steps) {
+        if (long_T) VNS_IV(true, false, true);
+        else VNS_IV(false, false, true);
+    } else if (strict) {
+        if (long_T) VNS_IV(true, true, false);
+        else VNS_IV(false, true, false);
+    } else {
+        if (long_T) VNS_IV(true, false, false);
+        else VNS_IV(false, false, false);
+    }
+#undef VNS_IV
+    return hipGetLastError();
 }
 
 hipError_t launch_eval_prep(const EvalPrepArgs &a, hipStream_t s) {

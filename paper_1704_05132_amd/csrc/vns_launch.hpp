@@ -82,6 +82,11 @@ hipError_t launch_init(const InitArgs &a, int n_chains, hipStream_t s, int model
 hipError_t launch_eval_learned(const EvalLearnedArgs &a, int64_t cp_begin, int64_t n_cp, hipStream_t s);
 // waves: 4 (k_eval) or 8, 12, 16 (k_eval_wide) wavefronts per workgroup.
 hipError_t launch_eval(const EvalArgs &a, const EvalWg *wg, int64_t n_wg, hipStream_t s, int model, int waves = 4);
+// The same sweep by interval pricing, for contexts of compact products under the carry-back readings (model 0 or
+// kModelStrict): the (chain, product) pairs cp_begin .. cp_begin + n_cp - 1, no table.  long_T: a horizon above
+// 64 is among them.  count_steps: counter [2] counts what was decoded rather than every move in full.
+hipError_t launch_eval_iv(const EvalArgs &a, int64_t cp_begin, int64_t n_cp, int n_cu, bool long_T, bool count_steps,
+                          hipStream_t s, int model);
 // The pricing table of a chain range and zeroed counters, built on the device (no host staging).
 hipError_t launch_eval_prep(const EvalPrepArgs &a, hipStream_t s);
 // Incremental pricing of the same sweep; lds_bytes of dynamic LDS hold each workgroup's base snapshots

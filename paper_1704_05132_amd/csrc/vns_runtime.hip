@@ -81,6 +81,9 @@ struct vns_ctx {
     std::vector<int32_t> prod_row;        // row offset of every product (as in the device product table)
     std::vector<ProdParams> prod_host;    // the device product table
     std::vector<int64_t> cost_bound;      // each product's worst-case cost without unit costs (< 2^47)
+    std::vector<int64_t> sum_returns;     // each product's returns over the horizon
+    bool compact = false;                 // every product is compact: interval pricing applies (vns_interval.hpp)
+    int32_t max_T = 1;
     int64_t n_prod = 0;
     uint64_t seed = 0;
     int device = 0;
@@ -307,6 +310,7 @@ static vns_status setup_chains(vns_ctx *c) {
             ci.T = c->T[(size_t)i];
             ci.prod0 = c->prod0[(size_t)i];
             ci.cp0 = cp;
+            ci.row0 = c->prod_row[(size_t)ci.prod0];
             c->price_off[(size_t)g] = slots;
             cp += ci.K;
             slots += 4LL * ci.K * ci.T;
@@ -382,6 +386,8 @@ extern "C" vns_status vns_create_batch(int32_t n_inst, const int32_t *K, const i
     std::vector<int2> rows((size_t)n_rows);
     std::vector<ProdParams> prod((size_t)n_prod);
     std::vector<int64_t> bounds((size_t)n_prod);   // worst-case cost of each product without unit costs
+    std::vector<int64_t> returns((size_t)n_prod);
+    bool compact = true;
     std::vector<int32_t> prod0((size_t)n_inst);
     int64_t p = 0, r = 0;
     for (int32_t i = 0; i < n_inst; ++i) {
@@ -424,6 +430,8 @@ extern "C" vns_status vns_create_batch(int32_t n_inst, const int32_t *K, const i
             pp.SD = sumD;
             set_cost_terms(pp);
             bounds[(size_t)p] = (int64_t)bound;
+            returns[(size_t)p] = sumR;
+            compact = compact && compact_product(pp, sumR, (int64_t)bound);
             r += Ti;
         }
         if (F_bound >= ((__int128)1 << 62)) return fail(nullptr, VNS_ERANGE, "an instance's objective could reach 2^62");
@@ -440,6 +448,9 @@ extern "C" vns_status vns_create_batch(int32_t n_inst, const int32_t *K, const i
     for (int64_t q = 0; q < n_prod; ++q) c->prod_row[(size_t)q] = prod[(size_t)q].row;
     c->prod_host = prod;
     c->cost_bound = bounds;
+    c->sum_returns = returns;
+    c->compact = compact;
+    for (int32_t i = 0; i < n_inst; ++i) c->max_T = std::max<int32_t>(c->max_T, T[i]);
     c->seed = seed;
     vns_status st = VNS_OK;
     auto bail = [&](vns_status s) {
@@ -814,7 +825,9 @@ extern "C" vns_status vns_eval_neighbourhood(vns_ctx *c, uint32_t nb_mask, int32
     const int32_t spread = c->eval_inc ? 0 : c->eval_spread;
     const int64_t key[4] = {g0, ng, group, c->eval_inc ? 1 : 2 + spread};
     EvalWg *d_tab = ws_tab ? reinterpret_cast<EvalWg *>(c->ws + wl.eval_off) : c->d_eval_wg;
-    if (!(key[0] == c->eval_wg_key[0] && key[1] == c->eval_wg_key[1] && key[2] == c->eval_wg_key[2] &&
+    const bool interval = c->compact && !(c->model & kModelDispose);
+    if (!interval &&
+        !(key[0] == c->eval_wg_key[0] && key[1] == c->eval_wg_key[1] && key[2] == c->eval_wg_key[2] &&
           key[3] == c->eval_wg_key[3])) {
         std::vector<EvalWg> tab;
         int32_t g = g0;
@@ -914,7 +927,9 @@ extern "C" vns_status vns_eval_neighbourhood(vns_ctx *c, uint32_t nb_mask, int32
     ea.nb_mask = nb_mask;
     VNS_HIP(c, hipMemsetAsync(c->d_evals, 0, sizeof(unsigned long long) * counter_words(), c->stream));
     VNS_HIP(c, hipEventRecord(c->ev0, c->stream));
-    if (c->eval_inc)
+    if (interval)
+        VNS_HIP(c, launch_eval_iv(ea, cp_begin, n_cp, c->n_cu, maxT > 64, c->eval_inc != 0, c->stream, c->model));
+    else if (c->eval_inc)
         VNS_HIP(c, launch_eval_inc(ea, d_tab, c->eval_wg_n, (size_t)group * (size_t)(maxT + 1) * kSnapBytes,
                                    c->stream));
     else
@@ -1009,7 +1024,13 @@ extern "C" vns_status vns_eval_neighbourhood_noalloc(vns_ctx *c, uint32_t nb_mas
     ea.evals = ctr;
     ea.nb_mask = nb_mask;
     VNS_HIP(c, hipEventRecord(c->ev0, c->stream));
-    VNS_HIP(c, launch_eval(ea, tab, n_cp, c->stream, c->model));
+    if (c->compact && !(c->model & kModelDispose)) {
+        int32_t maxT = 1;
+        for (int32_t g = g0; g < g0 + ng; ++g) maxT = std::max<int32_t>(maxT, c->chains[(size_t)g].T);
+        VNS_HIP(c, launch_eval_iv(ea, cp_begin, n_cp, c->n_cu, maxT > 64, false, c->stream, c->model));
+    } else {
+        VNS_HIP(c, launch_eval(ea, tab, n_cp, c->stream, c->model));
+    }
     VNS_HIP(c, hipEventRecord(c->ev1, c->stream));
     ChainBestArgs cb{c->d_chains, c->d_cs, c->d_cur_cost, keys - cp_begin, c->d_prod_price, c->d_prod_slot, c->d_best,
                      c->d_best_slot, g0};
@@ -1310,6 +1331,7 @@ extern "C" vns_status vns_set_unit_costs(vns_ctx *c, const int32_t *pM, const in
     if (!pM || !pR) return fail(c, VNS_EINVAL, "NULL input");
     std::vector<ProdParams> prod = c->prod_host;
     size_t p = 0;
+    bool compact = true;
     for (int32_t i = 0; i < c->n_inst; ++i) {
         __int128 F_bound = 0;
         for (int32_t k = 0; k < c->K[(size_t)i]; ++k, ++p) {
@@ -1321,6 +1343,7 @@ extern "C" vns_status vns_set_unit_costs(vns_ctx *c, const int32_t *pM, const in
             prod[p].pM = pM[p];
             prod[p].pR = pR[p];
             set_cost_terms(prod[p]);
+            compact = compact && compact_product(prod[p], c->sum_returns[p], (int64_t)bound);
         }
         if (F_bound >= ((__int128)1 << 62)) return fail(c, VNS_ERANGE, "an instance's objective could reach 2^62");
     }
@@ -1332,6 +1355,7 @@ extern "C" vns_status vns_set_unit_costs(vns_ctx *c, const int32_t *pM, const in
     VNS_HIP(c, launch_init(ia, (int)c->chains.size(), c->stream, c->model));
     VNS_HIP(c, hipStreamSynchronize(c->stream));
     c->prod_host = prod;
+    c->compact = compact;
     return VNS_OK;
 }
 

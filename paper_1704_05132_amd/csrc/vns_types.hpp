@@ -57,6 +57,14 @@ struct ProdParams {
     int64_t SD;     // sum_t D(t): the items made, sum x_M + sum x_R
     int32_t pM, pR; // unit costs of a manufactured and a remanufactured item (0 unless set)
 };
+// Whether 32-bit arithmetic prices every move of the product exactly (vns_interval.hpp): the sums of its demand and
+// returns, a unit's weight hR ls + hM (lm - ls) and its end term below 2^23, and the worst-case cost (unit costs
+// included) below 2^31.
+inline bool compact_product(const ProdParams &pp, int64_t sum_returns, int64_t cost_bound) {
+    const int64_t lim = 1 << 23, h = pp.hM > pp.hR ? pp.hM : pp.hR;
+    return pp.SD < lim && sum_returns < lim && (h + pp.hM) * kTMax < lim && pp.cXR < lim && -pp.cXR < lim &&
+           cost_bound < (1LL << 31) - 1;
+}
 // The two derived fields of a product.
 inline void set_cost_terms(ProdParams &pp) {
     pp.C = (int64_t)pp.hM * pp.S_tD + (int64_t)pp.hR * pp.S_PR + (int64_t)pp.pM * pp.SD;
@@ -69,6 +77,8 @@ struct ChainInfo {
     int32_t T;
     int32_t prod0;  // global index of product 0 of the chain's instance
     int64_t cp0;    // index of the chain's product 0 in the cur/work arrays
+    int32_t row0;   // offset of the instance's first period in rows
+    int32_t pad;
 };
 
 struct ChainState {

@@ -1,0 +1,97 @@
+"""GPU: interval pricing (vns_interval.hpp) against the oracle, at the sizes where its lane groups change (16, 31
+and 63 periods), at the ends of the horizon's range, with (chain, product) counts that leave lane groups without a
+pair, under both carry-back readings, with the first manufacturing setup late, and on both sides of the bounds that
+make a product compact.  All results are whole numbers and must be equal.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1704_05132_amd.instances import draw_instance, edge_instance
+
+pytestmark = pytest.mark.gpu
+
+HORIZONS = (1, 2, 3, 12, 15, 16, 17, 24, 31, 32, 33, 52, 63, 64, 65, 104, 127, 128)
+
+
+@pytest.fixture(scope="module")
+def vns():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_1704_05132_amd import vns as v
+    return v
+
+
+def solution(inst, rng, p_m, p_r):
+    """A feasible random solution: setups of products that it leaves infeasible become every period manufacturing."""
+    zM = (rng.random((inst.K, inst.T)) < p_m).astype(np.uint8)
+    zR = (rng.random((inst.K, inst.T)) < p_r).astype(np.uint8)
+    _, cost = oracle.objective(inst, zM, zR)
+    bad = cost == oracle.INF
+    zM[bad], zR[bad] = 1, 0
+    return zM, zR
+
+
+def check(vns, inst, rng, mask=7, options=None, chains=3):
+    sols = []
+    with vns.Context(inst, seed=1, chains=chains, options=options or {}) as ctx:
+        for g, (pm, pr) in enumerate([(0.3, 0.3), (0.1, 0.6), (0.6, 0.15)][:chains]):
+            sols.append(solution(inst, rng, pm, pr))
+            ctx.set_solution(g, *sols[-1])
+        got = ctx.eval_neighbourhood(mask)
+        evals = ctx.stats()["last_eval_evals"]
+    n, total = 4 * inst.K * inst.T, 0
+    for g, (zM, zR) in enumerate(sols):
+        ref, cnt = oracle.price_all(inst, zM, zR, mask)
+        total += cnt
+        mine = got["slot_price"][g * n:(g + 1) * n]
+        assert (mine == ref).all(), (g, np.flatnonzero(mine != ref)[:8])
+        per = ref.reshape(inst.K, -1)
+        assert (got["prod_best"][g * inst.K:(g + 1) * inst.K] == per.min(1)).all()
+        assert (got["prod_best_slot"][g * inst.K:(g + 1) * inst.K] ==
+                np.where(per.min(1) == oracle.INF, -1, per.argmin(1))).all()
+        assert (int(got["best"][g]), int(got["best_slot"][g])) == oracle.argmin(ref)
+    assert evals == total
+
+
+@pytest.mark.parametrize("strict", [False, True])
+@pytest.mark.parametrize("T", HORIZONS)
+def test_horizons(vns, T, strict):
+    rng = np.random.default_rng([T, strict])
+    for kind in ("uniform", "sparse", "big_returns", "no_returns", "zero_demand", "returns_eq_demand"):
+        inst = edge_instance(kind, 7, T, seed=T)
+        inst.strict = strict
+        inst.pM, inst.pR = rng.integers(0, 30, 7).astype(np.int32), rng.integers(0, 30, 7).astype(np.int32)
+        check(vns, inst, rng)
+
+
+@pytest.mark.parametrize("mask", [1, 2, 4, 3, 5, 6])
+@pytest.mark.parametrize("T", [12, 24, 52, 104])
+def test_masks(vns, T, mask):
+    rng = np.random.default_rng([T, mask])
+    check(vns, draw_instance(rng, 5, T), rng, mask)
+
+
+@pytest.mark.parametrize("strict", [False, True])
+@pytest.mark.parametrize("T", [14, 30, 60, 100])
+def test_first_setup_late(vns, T, strict):
+    """No demand in the first third: setups there may be missing or remanufacture only."""
+    rng = np.random.default_rng([T, 9, strict])
+    inst = edge_instance("big_returns", 9, T, seed=3)
+    inst.strict = strict
+    inst.D[:, :T // 3] = 0
+    check(vns, inst, rng)
+
+
+@pytest.mark.parametrize("scale", [1.0, 1.001])
+@pytest.mark.parametrize("T", [12, 40, 90])
+def test_compact_bounds(vns, T, scale):
+    """Demand and returns that sum to just under 2^23 (interval pricing) and just over it (the full decode)."""
+    rng = np.random.default_rng([T, int(scale * 1000)])
+    inst = draw_instance(rng, 5, T)
+    for a in (inst.D, inst.R):
+        w = rng.random((5, T)) + 1e-3
+        a[:] = np.floor(w / w.sum(1, keepdims=True) * (2**23 - 1) * scale).astype(np.int32)
+    inst.hM[:] = rng.integers(1, 3, 5) if T < 50 else 1
+    inst.hR[:] = rng.integers(0, 2, 5)
+    check(vns, inst, rng)
