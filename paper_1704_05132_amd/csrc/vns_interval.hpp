@@ -439,5 +439,147 @@ struct Pattern {
     }
 };
 
+// The VND (Algorithm 1) of one product by one wavefront.  A neighbourhood is priced once per pattern: the pattern's
+// decode is built when a move has been applied, and a neighbourhood met again on the same pattern gives the best
+// move it gave before (it still counts its evaluations, as Algorithm 1 prices it in every pass).  now() is read before a
+// pricing and compared with `round` after it: false means the caller's round moved on and the product was given up.
+// ident: the pattern's own cost is not known yet; it is computed and returned in `start`.
+struct Vnd {
+    int64_t cost;    // in: the pattern's cost (without ident); out: the local optimum's
+    int64_t start;   // out: the pattern's own cost
+    int64_t evals;   // move-evaluations, added to
+    int32_t err;     // out: 1 if the pass guard was hit
+};
+
+template <int NV, bool STRICT, class Now>
+__device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, const int2 *rows, int T, const ProdParams &pp,
+                                    uint32_t nb_list, int n_nb, bool memo, Lds<64, NV> &sh, int32_t round, Now now) {
+    const int lane = threadIdx.x & 63;
+    const Cost c = cost_of(pp);
+    int2 row[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) row[v] = lane + 64 * v < T ? rows[lane + 64 * v] : no_row();
+    Masks<64, NV> k = masks_of<64, NV>(b);
+    Pattern<64, NV, STRICT> pat;
+    pat.build(k, row, T, c, sh);
+    int32_t cost = (int32_t)s.cost;
+    if (ident) {
+        int nM = 0, nR = 0;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            nM += __popcll(k.m[v]);
+            nR += __popcll(k.r[v]);
+        }
+        cost = (int32_t)((uint32_t)pp.C + (uint32_t)pat.own_cost(c) + (uint32_t)c.kM * (uint32_t)nM +
+                         (uint32_t)c.kR * (uint32_t)nR);
+    }
+    s.start = cost;
+    s.err = 0;
+    // per neighbourhood (0 flip zM, 1 flip zR, 2 shift), wavefront-uniform: best change, its slot, moves
+    int32_t best[3] = {0, 0, 0}, slot[3] = {0, 0, 0}, cnt[3] = {0, 0, 0};
+    uint32_t known = 0, clean = 0;
+    bool improved = true, alive = true;
+    for (int passes = 1; improved && alive; ++passes) {
+        if (passes > kMaxPasses) {
+            s.err = 1;
+            break;
+        }
+        improved = false;
+        for (int q = 0; q < n_nb; ++q) {
+            if (memo && ((clean >> q) & 1u)) continue;   // same pattern: nothing to find
+            const uint32_t nb = (nb_list >> (4 * q)) & 0xFu;
+            const int i = nb == 1u ? 0 : nb == 2u ? 1 : 2;
+            if (!((known >> i) & 1u)) {
+                const int32_t seen = now();
+                int32_t x[2][NV];
+                int steps = 0, n = T;
+                if (i == 0) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) x[0][v] = lane + 64 * v < T ? pat.flip_m(pat.p[v], c, steps) : kBad32;
+                } else if (i == 1) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) x[0][v] = lane + 64 * v < T ? pat.flip_r(pat.p[v], c, steps) : kBad32;
+                } else {
+                    typename Pattern<64, NV, STRICT>::Next nx[NV];
+                    pat.next_of(k, nx);
+                    n = 0;
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) {
+                        const uint64_t vm = swap_bits<64, NV>(k.m, v, T), vr = swap_bits<64, NV>(k.r, v, T);
+                        const bool sm = lane_bit<64>(vm), sr = lane_bit<64>(vr);
+                        const int32_t y = pat.swap_m(pat.p[v], nx[v], c, sm, steps);
+                        const int32_t z = pat.swap_r(pat.p[v], nx[v], c, sr, steps);
+                        x[0][v] = sm ? y : kBad32;
+                        x[1][v] = sr ? z : kBad32;
+                        n += __popcll(vm) + __popcll(vr);
+                    }
+                }
+                // the lowest (cost, slot), as the sweep finds it
+                uint32_t low = 0;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    low = max(low, ~((uint32_t)x[0][v] ^ 0x80000000u));
+                    if (i == 2) low = max(low, ~((uint32_t)x[1][v] ^ 0x80000000u));
+                }
+                const int32_t bx = (int32_t)(~(uint32_t)last_lane(scan_max<64>(low)) ^ 0x80000000u);
+                int at = 0;
+                if (i == 2) {
+#pragma unroll
+                    for (int v = NV - 1; v >= 0; --v) {
+                        const uint64_t w = __ballot(x[1][v] == bx);
+                        at = w ? 3 * T + 64 * v + __builtin_ctzll(w) : at;
+                    }
+                }
+                const int off = i * T;
+#pragma unroll
+                for (int v = NV - 1; v >= 0; --v) {
+                    const uint64_t w = __ballot(x[0][v] == bx);
+                    at = w ? off + 64 * v + __builtin_ctzll(w) : at;
+                }
+                if (i == 0) { best[0] = bx; slot[0] = at; cnt[0] = n; }
+                if (i == 1) { best[1] = bx; slot[1] = at; cnt[1] = n; }
+                if (i == 2) { best[2] = bx; slot[2] = at; cnt[2] = n; }
+                known |= 1u << i;
+                if (__builtin_amdgcn_readfirstlane(seen) != round) {
+                    alive = false;
+                    break;
+                }
+            }
+            const int32_t bx = i == 0 ? best[0] : i == 1 ? best[1] : best[2];
+            s.evals += i == 0 ? cnt[0] : i == 1 ? cnt[1] : cnt[2];
+            if (bx < 0) {
+                const int l = i == 0 ? slot[0] : i == 1 ? slot[1] : slot[2];
+                const int blk = (l >= T) + (l >= 2 * T) + (l >= 3 * T), t = l - blk * T;
+                const uint64_t w = blk >= 2 ? 3ull : 1ull;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    uint64_t y = 0;
+                    if (t >> 6 == v) y = w << (t & 63);
+                    else if (v == 1 && t == 63) y = w >> 1;   // a swap of periods 63, 64
+                    if (blk & 1) k.r[v] ^= y;
+                    else k.m[v] ^= y;
+                }
+                cost += bx;
+                improved = true;
+                known = 0;
+                clean = 0;
+                pat.build(k, row, T, c, sh);
+            } else {
+                clean |= 1u << q;
+            }
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < kWords / 2; ++v) {
+        const uint64_t m = v < NV ? k.m[v] : 0, r = v < NV ? k.r[v] : 0;
+        b.m[2 * v] = (uint32_t)m;
+        b.m[2 * v + 1] = (uint32_t)(m >> 32);
+        b.r[2 * v] = (uint32_t)r;
+        b.r[2 * v + 1] = (uint32_t)(r >> 32);
+    }
+    s.cost = cost;
+    return alive;
+}
+
 }  // namespace iv
 }  // namespace vns

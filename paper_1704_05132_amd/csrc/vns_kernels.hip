@@ -675,8 +675,9 @@ __global__ __launch_bounds__(256) void k_chain_best(ChainBestArgs a) {
 // ---------------------------------------------------------------------------------------------------
 namespace {
 
+typedef uint16_t SwapLists[kMaxWaves][2 * kTMax];   // compacted swap moves of each wavefront's product
+
 struct RunShared {
-    uint16_t list[kMaxWaves][2 * kTMax];   // compacted swap moves of each wavefront's product
     Bits db[kShakeMax];                    // shaken products (dirty list): bits after the shake
     int32_t dp[kShakeMax];                 //   and product index
     int64_t part[kMaxWaves];
@@ -729,11 +730,13 @@ struct SpecShared {
     int32_t next;         // next product index to hand out
 };
 
-template <bool SPEC, bool LEARNED, bool COOP = false, int MODEL = 0, bool PACK = false, bool MULTI = false>
-__device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SpecShared &sp, int2 *s_rows) {
+// IV: the plain search's VND by interval pricing, with one (1) or up to two (2) periods per lane; 0: by full decodes.
+template <bool SPEC, bool LEARNED, bool COOP = false, int MODEL = 0, bool PACK = false, bool MULTI = false, int IV = 0>
+__device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapLists &lists, SpecShared &sp, int2 *s_rows) {
     static_assert(!PACK || LEARNED, "the packed form is the learned VND's");
     static_assert(!(SPEC && LEARNED), "the speculative VND prices whole neighbourhoods");
     static_assert(!(COOP && SPEC), "speculative iterations run the sequential VND");
+    static_assert(!IV || !(SPEC || LEARNED || MULTI || (MODEL & kModelDispose)), "interval pricing: the plain VND");
     int g = blockIdx.x, slot = 0;   // chain, and (speculative iterations) the iteration of a round it computes
     if constexpr (COOP) {
         const int m = a.coop_m;
@@ -808,10 +811,13 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SpecS
     int64_t nb_evals = 0, fallbacks = 0;   // learned mode, per wavefront
     // learned search: this wavefront's tiles after the rows region (kept 16-byte aligned), and the scorer's
     // weight fragments
-    const int rows_entries = run_rows_entries(a.lds_rows, W);
+    const int rows_entries = run_rows_entries(a.lds_rows, IV ? 0 : W);
     // (the packed form: one region for the workgroup)
     char *lbase = reinterpret_cast<char *>(s_rows + rows_entries) + (PACK ? 0 : wave * kLearnedWaveBytes);
     LearnedLds L{reinterpret_cast<__bf16 *>(lbase), reinterpret_cast<uint16_t *>(lbase + 64 * 16 * 2)};
+    // interval pricing: this wavefront's states and records, in the same place
+    char *ivbase = reinterpret_cast<char *>(s_rows + rows_entries) +
+                   wave * (IV == 2 ? sizeof(iv::Lds<64, 2>) : sizeof(iv::Lds<64, 1>));
     mlp::Frags fr;
     if constexpr (LEARNED) mlp::load_frags(a.mlp, fr);
     const uint64_t nflip_all = 2ull * (uint64_t)K * (uint64_t)T;
@@ -997,7 +1003,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SpecS
                     uint64_t ckey = kInfKey;
                     int nitems = 0;
                     const Bits b = gr.b;
-                    const uint64_t key = wave_best_move(b, row, T, pp, nb, sh.list[wave], id, &idc, dummy, chash, &ckey,
+                    const uint64_t key = wave_best_move(b, row, T, pp, nb, lists[wave], id, &idc, dummy, chash, &ckey,
                                                         &nitems);
                     if (lane == 0) {
                         gr.res[role] = key;
@@ -1129,6 +1135,42 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SpecS
                     p = idx;
                     for (int q = 0; q < nd; ++q) e = (e < 0 && sh.dp[q] == p) ? q : e;
                 }
+                if constexpr (IV != 0) {
+                    p = __builtin_amdgcn_readfirstlane(p);
+                    const ProdParams pp = load_uniform(a.prod + ci.prod0 + p);
+                    const int2 *row = rows_in_lds ? s_rows + p * T : inst_rows + p * T;
+                    Bits b = e >= 0 ? sh.db[e] : s_cur[p];
+                    const int64_t c_cur = s_cur_cost[p];
+                    iv::Vnd vs{c_cur, 0, evals, 0};
+                    auto round_now = [&]() -> int32_t {
+                        if constexpr (COOP) {
+                            if (may_abandon)
+                                return __hip_atomic_load(&a.coop_ctl[g].round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        }
+                        return coop_round;
+                    };
+                    constexpr bool kStrict = (MODEL & kModelStrict) != 0;
+                    bool done;
+                    if (IV == 1 || T <= 64)
+                        done = iv::vnd<1, kStrict>(b, vs, e >= 0, row, T, pp, a.nb_list, a.n_nb, a.memo != 0,
+                                                   *reinterpret_cast<iv::Lds<64, 1> *>(ivbase), coop_round, round_now);
+                    else if constexpr (IV == 2)
+                        done = iv::vnd<2, kStrict>(b, vs, e >= 0, row, T, pp, a.nb_list, a.n_nb, a.memo != 0,
+                                                   *reinterpret_cast<iv::Lds<64, 2> *>(ivbase), coop_round, round_now);
+                    evals = vs.evals;
+                    vnd_err |= vs.err;
+                    if (e >= 0) shk += vs.start - c_cur;
+                    if (!done) {
+                        stale = true;
+                        break;
+                    }
+                    if (lane == 0) {
+                        s_work[p] = b;
+                        s_work_cost[p] = vs.cost;
+                    }
+                    part += vs.cost - c_cur;
+                    continue;
+                }
                 const ProdParams pp = a.prod[ci.prod0 + p];
                 const int2 *row;
                 if (rows_in_lds) {
@@ -1166,7 +1208,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SpecS
                             int used = 1;
                             const bool id = need_ident;
                             const uint64_t key = wave_best_move_multi<2, MODEL>(b, row, T, pp, a.nb_list, q, a.n_nb,
-                                                                                sh.list[wave], id, cost, evals, used);
+                                                                                lists[wave], id, cost, evals, used);
                             if (id) {
                                 shk += cost - c_cur;
                                 need_ident = false;
@@ -1205,7 +1247,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SpecS
                         if constexpr (LEARNED) {
                             int fb = 0;
                             const bool id = need_ident;
-                            key = learned_best_move(b, row, T, pp, nb, sh.list[wave], L, fr, a.permille, id, cost,
+                            key = learned_best_move(b, row, T, pp, nb, lists[wave], L, fr, a.permille, id, cost,
                                                     evals, fb);
                             ++nb_evals;
                             fallbacks += fb;
@@ -1215,7 +1257,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SpecS
                             }
                         } else {
                             int64_t idc = 0;
-                            key = wave_best_move<MODEL>(b, row, T, pp, nb, sh.list[wave], need_ident, &idc, evals, chash,
+                            key = wave_best_move<MODEL>(b, row, T, pp, nb, lists[wave], need_ident, &idc, evals, chash,
                                                         &ckey,
                                                  &nitems);
                             if (need_ident) {
@@ -1580,9 +1622,10 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SpecS
 template <int MODEL>
 __global__ __launch_bounds__(512) void k_run(RunArgs a) {
     __shared__ RunShared sh;
+    __shared__ SwapLists lists;
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
-    run_chain<false, false, false, MODEL>(a, sh, sp, s_rows);
+    run_chain<false, false, false, MODEL>(a, sh, lists, sp, s_rows);
 }
 
 // The same for batches with short horizons (up to kMultiMaxT): consecutive neighbourhoods priced side by side.
@@ -1590,16 +1633,38 @@ __global__ __launch_bounds__(512) void k_run(RunArgs a) {
 template <int MODEL>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_run_short(RunArgs a) {
     __shared__ RunShared sh;
+    __shared__ SwapLists lists;
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
-    run_chain<false, false, false, MODEL, false, true>(a, sh, sp, s_rows);
+    run_chain<false, false, false, MODEL, false, true>(a, sh, lists, sp, s_rows);
+}
+
+// The plain search with interval pricing (contexts of compact products, no move log), one workgroup per chain and
+// with speculative iterations or best-of-G.  IV: 1 when every horizon is at most 64, else 2.
+template <int IV, int MODEL>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_run_iv(RunArgs a) {
+    __shared__ RunShared sh;
+    __shared__ SwapLists lists;
+    __shared__ SpecShared sp;
+    extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
+    run_chain<false, false, false, MODEL, false, false, IV>(a, sh, lists, sp, s_rows);
+}
+
+template <int IV, int MODEL>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void k_run_coop_iv(RunArgs a) {
+    __shared__ RunShared sh;
+    __shared__ SwapLists lists;
+    __shared__ SpecShared sp;
+    extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
+    run_chain<false, false, true, MODEL, false, false, IV>(a, sh, lists, sp, s_rows);
 }
 
 __global__ __launch_bounds__(1024) void k_run_spec(RunArgs a) {
     __shared__ RunShared sh;
+    __shared__ SwapLists lists;
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
-    run_chain<true, false>(a, sh, sp, s_rows);
+    run_chain<true, false>(a, sh, lists, sp, s_rows);
 }
 
 // speculative iterations: m workgroups per chain compute the next m iterations side by side (cooperative
@@ -1607,40 +1672,45 @@ __global__ __launch_bounds__(1024) void k_run_spec(RunArgs a) {
 template <int MODEL>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void k_run_coop(RunArgs a) {
     __shared__ RunShared sh;
+    __shared__ SwapLists lists;
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
-    run_chain<false, false, true, MODEL>(a, sh, sp, s_rows);
+    run_chain<false, false, true, MODEL>(a, sh, lists, sp, s_rows);
 }
 
 // learned VND: the scorer's weight fragments stay in registers for the whole launch
 // speculative iterations of the learned search
 __global__ __launch_bounds__(512) void k_run_learned_coop(RunArgs a) {
     __shared__ RunShared sh;
+    __shared__ SwapLists lists;
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
-    run_chain<false, true, true>(a, sh, sp, s_rows);
+    run_chain<false, true, true>(a, sh, lists, sp, s_rows);
 }
 
 __global__ __launch_bounds__(512) void k_run_learned(RunArgs a) {
     __shared__ RunShared sh;
+    __shared__ SwapLists lists;
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
-    run_chain<false, true>(a, sh, sp, s_rows);
+    run_chain<false, true>(a, sh, lists, sp, s_rows);
 }
 
 // the packed learned VND (batches of products per wavefront), alone and with speculative iterations
 __global__ __launch_bounds__(512) void k_run_learned_packed(RunArgs a) {
     __shared__ RunShared sh;
+    __shared__ SwapLists lists;
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
-    run_chain<false, true, false, 0, true>(a, sh, sp, s_rows);
+    run_chain<false, true, false, 0, true>(a, sh, lists, sp, s_rows);
 }
 
 __global__ __launch_bounds__(512) void k_run_learned_coop_packed(RunArgs a) {
     __shared__ RunShared sh;
+    __shared__ SwapLists lists;
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
-    run_chain<false, true, true, 0, true>(a, sh, sp, s_rows);
+    run_chain<false, true, true, 0, true>(a, sh, lists, sp, s_rows);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -1773,8 +1843,22 @@ hipError_t launch_eval_learned(const EvalLearnedArgs &a, int64_t cp_begin, int64
     return hipGetLastError();
 }
 
+static const void *interval_kernel(bool coop, bool long_T, int model) {
+#define VNS_IV(K)                                                                                                     \
+    (long_T ? ((model & kModelStrict) ? reinterpret_cast<const void *>(&K<2, 1>) : reinterpret_cast<const void *>(&K<2, 0>)) \
+            : ((model & kModelStrict) ? reinterpret_cast<const void *>(&K<1, 1>) : reinterpret_cast<const void *>(&K<1, 0>)))
+    return coop ? VNS_IV(k_run_coop_iv) : VNS_IV(k_run_iv);
+#undef VNS_IV
+}
+
+int64_t interval_wave_bytes(bool long_T) {
+    return long_T ? (int64_t)sizeof(iv::Lds<64, 2>) : (int64_t)sizeof(iv::Lds<64, 1>);
+}
+
 static const void *run_kernel(RunKind kind, int model) {
     switch (kind) {
+        case RunKind::kInterval: return interval_kernel(false, false, model);
+        case RunKind::kIntervalLong: return interval_kernel(false, true, model);
         case RunKind::kSpec: return reinterpret_cast<const void *>(&k_run_spec);
         case RunKind::kLearned: return reinterpret_cast<const void *>(&k_run_learned);
         case RunKind::kLearnedPacked: return reinterpret_cast<const void *>(&k_run_learned_packed);
@@ -1795,6 +1879,8 @@ hipError_t run_kernel_lds(RunKind kind, size_t *static_bytes, size_t dynamic_byt
 static const void *coop_kernel(RunKind kind, int model) {
     if (kind == RunKind::kLearned) return reinterpret_cast<const void *>(&k_run_learned_coop);
     if (kind == RunKind::kLearnedPacked) return reinterpret_cast<const void *>(&k_run_learned_coop_packed);
+    if (kind == RunKind::kInterval || kind == RunKind::kIntervalLong)
+        return interval_kernel(true, kind == RunKind::kIntervalLong, model);
     return by_model<PickCoop>(model);
 }
 

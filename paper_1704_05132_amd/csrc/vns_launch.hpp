@@ -35,7 +35,11 @@ struct ChainBestArgs {
 // Variants of the search kernel: sequential VND, speculative VND, learned VND.
 // kPlainShort: the plain search kernel with consecutive neighbourhoods priced side by side in one pass at
 // horizons up to kMultiMaxT (launched when an instance has one; the same moves and counts as kPlain).
-enum class RunKind { kPlain = 0, kSpec = 1, kLearned = 2, kLearnedPacked = 3, kPlainShort = 4 };
+// kInterval, kIntervalLong: the plain search by interval pricing (horizons up to 64, or any).
+enum class RunKind { kPlain = 0, kSpec = 1, kLearned = 2, kLearnedPacked = 3, kPlainShort = 4, kInterval = 5, kIntervalLong = 6 };
+
+// LDS of interval pricing per search wavefront.
+int64_t interval_wave_bytes(bool long_T);
 
 // Static LDS bytes of a search kernel variant, and permission for it to request dynamic_bytes more.
 // model: the decode reading (kModelStrict | kModelDispose; the plain sequential VND only).
@@ -95,8 +99,8 @@ hipError_t launch_eval_inc(const EvalArgs &a, const EvalWg *wg, int64_t n_wg, si
 hipError_t launch_chain_best(const ChainBestArgs &a, int n_chains, hipStream_t s);
 // Speculative iterations (a.coop_m workgroups per chain, cooperative launch): whether blocks workgroups of
 // `waves` wavefronts and lds_bytes of dynamic LDS are all resident at once, and the launch itself (then the
-// device iteration counter advances by a.iters).  kind: kPlain (any decode reading `model`), kLearned or
-// kLearnedPacked.
+// device iteration counter advances by a.iters).  kind: kPlain (any decode reading `model`), kInterval,
+// kIntervalLong, kLearned or kLearnedPacked.
 hipError_t coop_fits(int waves, size_t lds_bytes, int64_t blocks, bool *fits, RunKind kind, int model);
 hipError_t launch_run_coop(const RunArgs &a, int n_chains, int waves, size_t lds_bytes, int64_t *it_counter,
                            hipStream_t s, RunKind kind, int model);

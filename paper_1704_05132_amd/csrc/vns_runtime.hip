@@ -1122,14 +1122,20 @@ extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
     // the one-workgroup plain search has a variant for batches with a short horizon
     int32_t min_T = kTMax;
     for (int32_t i = 0; i < c->n_inst; ++i) min_T = std::min<int32_t>(min_T, c->T[(size_t)i]);
-    const RunKind run_k = (kind == RunKind::kPlain && min_T <= kMultiMaxT) ? RunKind::kPlainShort : kind;
+    // interval pricing where it applies (its VND keeps no move log); otherwise full decodes, with the variant for
+    // batches with a short horizon in the one-workgroup search
+    const bool interval = kind == RunKind::kPlain && c->compact && !(c->model & kModelDispose) && ra.log_x == nullptr;
+    const bool long_T = c->max_T > 64;
+    const RunKind coop_k = interval ? (long_T ? RunKind::kIntervalLong : RunKind::kInterval) : kind;
+    const RunKind run_k = interval ? coop_k : (kind == RunKind::kPlain && min_T <= kMultiMaxT) ? RunKind::kPlainShort : kind;
     VNS_HIP(c, run_kernel_lds(run_k, &static_lds, 0, c->model));
     const bool packed = c->permille > 0 && c->learned_pack > 1;
-    const int64_t learned = c->permille <= 0 ? 0
+    const int64_t learned = interval         ? waves * interval_wave_bytes(long_T)   // LDS after the rows
+                            : c->permille <= 0 ? 0
                             : packed         ? (int64_t)pack_region_bytes(waves, c->learned_pack)
                                              : (int64_t)waves * kLearnedWaveBytes;
     const int64_t room = c->max_lds_per_wg - (int64_t)static_lds - learned;   // dynamic LDS left for rows
-    const int64_t slices = (int64_t)waves * kTMax;                   // per-wave rows when the instance does not fit
+    const int64_t slices = interval ? 0 : (int64_t)waves * kTMax;    // per-wave rows when the instance does not fit
     if (room < slices * (int64_t)sizeof(int2)) return fail(c, VNS_EINVAL, "not enough LDS for the search kernel");
     // the chains' solution state (80 bytes per product) when it fits beside the per-wave row slices
     int64_t max_K = 0;
@@ -1142,7 +1148,7 @@ extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
     int64_t min_rows = max_rows;
     for (int32_t i = 0; i < c->n_inst; ++i) min_rows = std::min<int64_t>(min_rows, (int64_t)c->K[(size_t)i] * c->T[(size_t)i]);
     ra.lds_rows = min_rows > budget ? 0 : (int32_t)std::min<int64_t>(max_rows, budget);
-    const size_t rows_bytes = (size_t)run_rows_entries(ra.lds_rows, waves) * sizeof(int2);
+    const size_t rows_bytes = (size_t)run_rows_entries(ra.lds_rows, interval ? 0 : waves) * sizeof(int2);
     ra.state_off = state_bytes > 0 ? (int32_t)(rows_bytes + (size_t)learned) : -1;
     const size_t lds = rows_bytes + (size_t)learned + (size_t)state_bytes;
     VNS_HIP(c, run_kernel_lds(run_k, &static_lds, lds, c->model));
@@ -1153,17 +1159,29 @@ extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
     const int m = best ? std::max<int>(c->best_of, 1) : c->spec_iters;
     bool coop = false;
     // x stays in device memory: no state region; the learned search keeps its per-wavefront tiles
-    const size_t lds_coop = rows_bytes + (size_t)learned;
+    size_t lds_coop = rows_bytes + (size_t)learned;
+    const int32_t rows_one = ra.lds_rows;
+    auto fits = [&](bool *ok) -> hipError_t {
+        hipError_t e = coop_fits(waves, lds_coop, G * m, ok, coop_k, c->model);
+        if (e == hipSuccess && !*ok && interval && ra.lds_rows > 0) {
+            // the rows beside interval pricing's records may be what does not fit: it reads them from device memory too
+            lds_coop = (size_t)learned;
+            ra.lds_rows = 0;
+            e = coop_fits(waves, lds_coop, G * m, ok, coop_k, c->model);
+            if (!*ok) ra.lds_rows = rows_one;
+        }
+        return e;
+    };
     if (best) {
         if (kind != RunKind::kPlain || c->use_graph || ra.log_x != nullptr || c->spec_iters > 1)
             return fail(c, VNS_EINVAL, "best-of-G runs the plain search alone: no learned scorer, speculative VND or "
                                        "iterations, move log or graph capture");
-        VNS_HIP(c, coop_fits(waves, lds_coop, G * m, &coop, RunKind::kPlain, c->model));
+        VNS_HIP(c, fits(&coop));
         if (!coop)
             return fail(c, VNS_EINVAL, "best-of-G needs its G workgroups per chain resident at once: use fewer "
                                        "chains, wavefronts per workgroup or streams");
     } else if (m > 1 && kind != RunKind::kSpec && !c->use_graph && ra.log_x == nullptr) {
-        VNS_HIP(c, coop_fits(waves, lds_coop, G * m, &coop, kind, c->model));
+        VNS_HIP(c, fits(&coop));
     }
     c->stats.last_run_spec_iters = coop && !best ? m : 1;
     CoopCtl *d_ctl = c->d_coop_ctl;
@@ -1222,7 +1240,7 @@ extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
         ra.best_of = best ? 1 : 0;
         ra.best_literal = c->best_literal;
         VNS_HIP(c, hipEventRecord(c->ev0, c->stream));
-        VNS_HIP(c, launch_run_coop(ra, (int)G, waves, lds_coop, c->d_iter, c->stream, kind, c->model));
+        VNS_HIP(c, launch_run_coop(ra, (int)G, waves, lds_coop, c->d_iter, c->stream, coop_k, c->model));
         VNS_HIP(c, hipEventRecord(c->ev1, c->stream));
     } else if (c->use_graph) {
         const int64_t key[5] = {iters, G, waves * 8 + (int64_t)run_k, (int64_t)lds, (int64_t)(intptr_t)ra.trace};
