@@ -72,8 +72,18 @@ __device__ __forceinline__ int32_t next_lane(int32_t x, int32_t last = 0) {
 }
 __device__ __forceinline__ int32_t last_lane(uint32_t x) { return __builtin_amdgcn_readlane((int)x, 63); }
 
-// acc + a * b, a and b signed 24-bit
-__device__ __forceinline__ int32_t mad24(int32_t a, int32_t b, int32_t acc) { return __mul24(a, b) + acc; }
+// a * b and acc + a * b, a and b signed 24-bit.  Written as instructions: where the compiler does not see both ranges
+// in the block of the product, it takes the quarter-rate 32-bit multiply.
+__device__ __forceinline__ int32_t mul24(int32_t a, int32_t b) {
+    int32_t r;
+    asm("v_mul_i32_i24 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ int32_t mad24(int32_t a, int32_t b, int32_t acc) {
+    int32_t r;
+    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(acc));
+    return r;
+}
 
 // A product's parameters in 32 bits (exact for a compact product).
 struct Cost {
@@ -137,11 +147,12 @@ __device__ __forceinline__ Word<G> swap_bits(const Word<G> (&z)[NV], int v, int 
 }
 
 // LDS of one wavefront: per group, pos[k] = (XR, H) before period k, H the units manufactured (the demand before k
-// less XR), and the remanufacturing setups' records with two that end every walk.
+// less XR), and the remanufacturing setups' records with kWalk that end every walk.
+constexpr int kWalk = 4;   // records a walk takes per round: their reads are in flight together
 template <int G, int NV>
 struct Lds {
     static constexpr int kPos = G * NV + 1;
-    static constexpr int kRec = G * NV + 2;
+    static constexpr int kRec = G * NV + kWalk;
     int4 rec[(64 / G) * kRec];
     int2 pos[(64 / G) * kPos];
 };
@@ -264,15 +275,12 @@ struct Pattern {
             q.XRn = an.x;
             q.Hn = an.y;
             q.Hm = pos[q.M1].y;
-            q.w = mad24(c.hM, q.lm, __mul24(c.wd, q.ls));
+            q.w = mad24(c.hM, q.lm, mul24(c.wd, q.ls));
             // 3. the record of a remanufacturing setup (its ls is t itself)
             if (q.r) grec[q.j - 1] = make_int4(q.Hn - q.Hb, q.PR - q.XRn, q.w, STRICT && !q.m ? q.t + 256 : q.t);
         }
         // the horizon's end takes every difference: its units are worth -cXR each
-        if (t0 == 0) {
-            grec[nR] = make_int4(1 << 28, 0, -c.cXR, 255);
-            grec[nR + 1] = make_int4(0, 0, 0, 255);
-        }
+        if (t0 < kWalk) grec[nR + t0] = t0 == 0 ? make_int4(1 << 28, 0, -c.cXR, 255) : make_int4(0, 0, 0, 255);
         lds_fence();
     }
 
@@ -297,32 +305,35 @@ struct Pattern {
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const Period &q = p[v];
-            s += (uint32_t)(__mul24(q.xa - q.xb, q.w) - __mul24(q.D, __mul24(c.hM, q.lm)));
+            s += (uint32_t)(mul24(q.xa - q.xb, q.w) - mul24(q.D, mul24(c.hM, q.lm)));
         }
         s = scan_add<64>(s);
         const int32_t xr = last_lane((uint32_t)p[NV - 1].xa);
-        return last_lane(s) + __mul24(c.cXR, xr);
+        return last_lane(s) + mul24(c.cXR, xr);
     }
 
     // The difference d of the remanufactured units passed on to R setup j and those after it; returns its cost.
-    // dM: what is left of it at M1.  Two records per round: the one after the horizon's changes nothing.
+    // dM: what is left of it at M1.  kWalk records per round: those after the horizon's change nothing.
     template <bool TRACK>
     __device__ __forceinline__ int32_t walk(int j, int32_t d, int32_t M1, int32_t &dM, bool &bad, int &steps) const {
         int32_t acc = 0;
         const int4 *at = rec + j;
         dM = d;
         while (d != 0) {
+            int4 r[kWalk];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int4 q = at[h];
+            for (int h = 0; h < kWalk; ++h) r[h] = at[h];
+#pragma unroll
+            for (int h = 0; h < kWalk; ++h) {
+                const int4 q = r[h];
                 const int32_t dn = min(d + q.x, q.y), du = dn - d;
                 acc = mad24(du, q.z, acc);
                 if constexpr (TRACK) dM = (STRICT ? q.w & 255 : q.w) < M1 ? dn : dM;
                 if constexpr (STRICT) bad |= q.w > 255 && du < 0;   // a remanufacture-only interval runs short
                 d = dn;
             }
-            at += 2;
-            steps += 2;
+            at += kWalk;
+            steps += kWalk;
         }
         return acc;
     }
@@ -333,12 +344,12 @@ struct Pattern {
         const int32_t dseg = (q.XRn + q.Hn) - (q.xb + q.Hb);
         const int32_t v0 = q.reg0 ? min(dseg, q.cap0 - q.xb) : 0;
         const int32_t d = q.r ? 0 : q.m ? v0 : -v0;
-        const int32_t wL = mad24(c.hM, q.lm, __mul24(c.wd, q.lsz));
+        const int32_t wL = mad24(c.hM, q.lm, mul24(c.wd, q.lsz));
         bool bad = false;
         int32_t dM;
         const int32_t x = mad24(d, wL, walk<true>(q.j, d, q.M1, dM, bad, steps));
         const int32_t S = q.Hm - q.Hb - dM;   // shortfalls up to M1, made at t or at the M setup before it
-        const int32_t y = c.kM - __mul24(__mul24(c.hM, q.t - q.lmz), S);
+        const int32_t y = c.kM - mul24(mul24(c.hM, q.t - q.lmz), S);
         bad |= q.m && !q.hm0 && S > 0;
         if constexpr (STRICT) bad |= q.m && (q.r || q.blk0) && dseg - (q.XRn - q.xb + d) > 0;
         return bad ? kBad32 : x + (q.m ? -y : y);
@@ -346,9 +357,9 @@ struct Pattern {
 
     // Cost change of flipping zR(t): the interval remanufactures a units with it, b without.
     __device__ __forceinline__ int32_t flip_r(const Period &q, const Cost &c, int &steps) const {
-        const int32_t dseg = (q.XRn + q.Hn) - (q.xb + q.Hb), hl = __mul24(c.hM, q.lm);
+        const int32_t dseg = (q.XRn + q.Hn) - (q.xb + q.Hb), hl = mul24(c.hM, q.lm);
         const int32_t a = min(dseg, q.PR - q.xb), b = q.reg0 && !q.m ? min(dseg, q.cap0 - q.xb) : 0;
-        const int32_t y = __mul24(a, mad24(c.wd, q.t, hl)) - __mul24(b, mad24(c.wd, q.lsz, hl)) + c.kR;
+        const int32_t y = mul24(a, mad24(c.wd, q.t, hl)) - mul24(b, mad24(c.wd, q.lsz, hl)) + c.kR;
         const int32_t d = q.r ? b - a : a - b;
         bool bad = false;
         int32_t dM, x;
@@ -401,7 +412,7 @@ struct Pattern {
         int32_t dM;
         const int32_t y = mad24(e1, x.w, mad24(e0, q.w, walk<true>(x.j, d, x.M1, dM, bad, steps)));
         const int32_t S = x.Hm - dM - (Ha - e0), made0 = q.D - (x1 - q.xb);
-        const int32_t z = __mul24(c.hM, S) - __mul24(__mul24(c.hM, q.t - q.lmz), made0);
+        const int32_t z = mul24(c.hM, S) - mul24(mul24(c.hM, q.t - q.lmz), made0);
         bad |= q.m && !q.hm0 && made0 > 0;
         if constexpr (STRICT) {
             const bool blk = q.m && (q.r || q.blk0);   // m: the M setup leaves t
@@ -413,14 +424,14 @@ struct Pattern {
 
     // Cost change of swapping zR(t), zR(t + 1), which differ.
     __device__ __forceinline__ int32_t swap_r(const Period &q, const Next &x, const Cost &c, bool valid, int &steps) const {
-        const int32_t hl = __mul24(c.hM, q.lm), Ha = q.Hb + q.D - (q.xa - q.xb), d1 = (x.XRn + x.Hn) - (q.xa + Ha);
+        const int32_t hl = mul24(c.hM, q.lm), Ha = q.Hb + q.D - (q.xa - q.xb), d1 = (x.XRn + x.Hn) - (q.xa + Ha);
         const int32_t a0 = min(q.D, q.PR - q.xb), b0 = q.reg0 && !q.m ? min(q.D, q.cap0 - q.xb) : 0;
-        const int32_t y0 = __mul24(a0, mad24(c.wd, q.t, hl)) - __mul24(b0, mad24(c.wd, q.lsz, hl));
+        const int32_t y0 = mul24(a0, mad24(c.wd, q.t, hl)) - mul24(b0, mad24(c.wd, q.lsz, hl));
         const int32_t u0 = q.r ? b0 : a0, x1 = q.xb + u0;
         const int32_t u1 = q.r ? min(d1, x.PR - x1) : x.m ? 0 : min(d1, q.PR - x1);
-        const int32_t w1 = mad24(c.wd, q.t + (q.r ? 1 : 0), x.m ? __mul24(c.hM, q.t + 1) : hl);
+        const int32_t w1 = mad24(c.wd, q.t + (q.r ? 1 : 0), x.m ? mul24(c.hM, q.t + 1) : hl);
         const int32_t d = valid ? x1 + u1 - x.XRn : 0;
-        int32_t y = mad24(u1, w1, q.r ? -y0 : y0) - __mul24(x.XRn - q.xa, x.w);
+        int32_t y = mad24(u1, w1, q.r ? -y0 : y0) - mul24(x.XRn - q.xa, x.w);
         bool bad = false;
         int32_t dM;
         if (__any(valid && !q.hm)) {
@@ -443,7 +454,9 @@ struct Pattern {
 // decode is built when a move has been applied, and a neighbourhood met again on the same pattern gives the best
 // move it gave before (it still counts its evaluations, as Algorithm 1 prices it in every pass).  now() is read before a
 // pricing and compared with `round` after it: false means the caller's round moved on and the product was given up.
-// ident: the pattern's own cost is not known yet; it is computed and returned in `start`.
+// ident: the pattern's own cost is not known yet; it is computed and returned in `start`.  x, x_cost: a pattern of the
+// product known to be a local optimum of this list, and its cost (with has_x): most shaken products return to it
+// (86 to 91% of single flips at T = 12..104), and no neighbourhood of it improves.
 struct Vnd {
     int64_t cost;    // in: the pattern's cost (without ident); out: the local optimum's
     int64_t start;   // out: the pattern's own cost
@@ -451,18 +464,51 @@ struct Vnd {
     int32_t err;     // out: 1 if the pass guard was hit
 };
 
-template <int NV, bool STRICT, class Now>
-__device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, const int2 *rows, int T, const ProdParams &pp,
-                                    uint32_t nb_list, int n_nb, bool memo, Lds<64, NV> &sh, int32_t round, Now now) {
+template <int NV, bool STRICT, class Row, class Now>
+__device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, Row row_at, int T, const ProdParams &pp,
+                                    bool has_x, const Bits &x, int64_t x_cost, uint32_t nb_list, int n_nb, bool memo,
+                                    Lds<64, NV> &sh, int32_t round, Now now) {
     const int lane = threadIdx.x & 63;
     const Cost c = cost_of(pp);
     int2 row[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) row[v] = lane + 64 * v < T ? rows[lane + 64 * v] : no_row();
+    for (int v = 0; v < NV; ++v) {
+        row[v] = no_row();
+        if (lane + 64 * v < T) row[v] = row_at(lane + 64 * v);
+    }
     Masks<64, NV> k = masks_of<64, NV>(b);
+    const Masks<64, NV> kx = masks_of<64, NV>(x);
+    auto at_x = [&]() {
+        bool same = has_x;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) same = same && k.m[v] == kx.m[v] && k.r[v] == kx.r[v];
+        return same;
+    };
+    // per neighbourhood (0 flip zM, 1 flip zR, 2 shift), wavefront-uniform: best change, its slot, moves
+    int32_t best[3] = {0, 0, 0}, slot[3] = {0, 0, 0}, cnt[3] = {0, 0, 0};
+    uint32_t known = 0, clean = 0;
+    // nothing improves on x: count what is left of this pass after neighbourhood q, and the pass that finds nothing (with
+    // the memo, which skips what this pass has priced on x, its neighbourhoods up to q)
+    auto count_x = [&](int q, bool another) {
+        int n = 0;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) n += __popcll(swap_bits<64, NV>(k.m, v, T)) + __popcll(swap_bits<64, NV>(k.r, v, T));
+        int sum = 0;
+        for (int i = 0; i < n_nb; ++i) {
+            const int moves = ((nb_list >> (4 * i)) & 4u) ? n : T;
+            sum += moves * ((i > q ? 1 : 0) + (another && !(memo && i > q) ? 1 : 0));
+        }
+        s.evals += sum;
+    };
     Pattern<64, NV, STRICT> pat;
-    pat.build(k, row, T, c, sh);
     int32_t cost = (int32_t)s.cost;
+    s.err = 0;
+    if (at_x()) {   // the shake undid itself
+        count_x(-1, false);
+        s.start = s.cost = x_cost;
+        return true;
+    }
+    pat.build(k, row, T, c, sh);
     if (ident) {
         int nM = 0, nR = 0;
 #pragma unroll
@@ -474,10 +520,6 @@ __device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, const int2 *row
                          (uint32_t)c.kR * (uint32_t)nR);
     }
     s.start = cost;
-    s.err = 0;
-    // per neighbourhood (0 flip zM, 1 flip zR, 2 shift), wavefront-uniform: best change, its slot, moves
-    int32_t best[3] = {0, 0, 0}, slot[3] = {0, 0, 0}, cnt[3] = {0, 0, 0};
-    uint32_t known = 0, clean = 0;
     bool improved = true, alive = true;
     for (int passes = 1; improved && alive; ++passes) {
         if (passes > kMaxPasses) {
@@ -491,14 +533,14 @@ __device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, const int2 *row
             const int i = nb == 1u ? 0 : nb == 2u ? 1 : 2;
             if (!((known >> i) & 1u)) {
                 const int32_t seen = now();
-                int32_t x[2][NV];
+                int32_t dx[2][NV];
                 int steps = 0, n = T;
                 if (i == 0) {
 #pragma unroll
-                    for (int v = 0; v < NV; ++v) x[0][v] = lane + 64 * v < T ? pat.flip_m(pat.p[v], c, steps) : kBad32;
+                    for (int v = 0; v < NV; ++v) dx[0][v] = lane + 64 * v < T ? pat.flip_m(pat.p[v], c, steps) : kBad32;
                 } else if (i == 1) {
 #pragma unroll
-                    for (int v = 0; v < NV; ++v) x[0][v] = lane + 64 * v < T ? pat.flip_r(pat.p[v], c, steps) : kBad32;
+                    for (int v = 0; v < NV; ++v) dx[0][v] = lane + 64 * v < T ? pat.flip_r(pat.p[v], c, steps) : kBad32;
                 } else {
                     typename Pattern<64, NV, STRICT>::Next nx[NV];
                     pat.next_of(k, nx);
@@ -509,8 +551,8 @@ __device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, const int2 *row
                         const bool sm = lane_bit<64>(vm), sr = lane_bit<64>(vr);
                         const int32_t y = pat.swap_m(pat.p[v], nx[v], c, sm, steps);
                         const int32_t z = pat.swap_r(pat.p[v], nx[v], c, sr, steps);
-                        x[0][v] = sm ? y : kBad32;
-                        x[1][v] = sr ? z : kBad32;
+                        dx[0][v] = sm ? y : kBad32;
+                        dx[1][v] = sr ? z : kBad32;
                         n += __popcll(vm) + __popcll(vr);
                     }
                 }
@@ -518,22 +560,22 @@ __device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, const int2 *row
                 uint32_t low = 0;
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
-                    low = max(low, ~((uint32_t)x[0][v] ^ 0x80000000u));
-                    if (i == 2) low = max(low, ~((uint32_t)x[1][v] ^ 0x80000000u));
+                    low = max(low, ~((uint32_t)dx[0][v] ^ 0x80000000u));
+                    if (i == 2) low = max(low, ~((uint32_t)dx[1][v] ^ 0x80000000u));
                 }
                 const int32_t bx = (int32_t)(~(uint32_t)last_lane(scan_max<64>(low)) ^ 0x80000000u);
                 int at = 0;
                 if (i == 2) {
 #pragma unroll
                     for (int v = NV - 1; v >= 0; --v) {
-                        const uint64_t w = __ballot(x[1][v] == bx);
+                        const uint64_t w = __ballot(dx[1][v] == bx);
                         at = w ? 3 * T + 64 * v + __builtin_ctzll(w) : at;
                     }
                 }
                 const int off = i * T;
 #pragma unroll
                 for (int v = NV - 1; v >= 0; --v) {
-                    const uint64_t w = __ballot(x[0][v] == bx);
+                    const uint64_t w = __ballot(dx[0][v] == bx);
                     at = w ? off + 64 * v + __builtin_ctzll(w) : at;
                 }
                 if (i == 0) { best[0] = bx; slot[0] = at; cnt[0] = n; }
@@ -563,6 +605,11 @@ __device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, const int2 *row
                 improved = true;
                 known = 0;
                 clean = 0;
+                if (at_x()) {
+                    count_x(q, true);
+                    improved = false;   // the passes are done
+                    break;
+                }
                 pat.build(k, row, T, c, sh);
             } else {
                 clean |= 1u << q;

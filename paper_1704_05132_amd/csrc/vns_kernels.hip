@@ -686,6 +686,8 @@ struct RunShared {
     int64_t fb[kMaxWaves];
     int32_t verr[kMaxWaves];
     int32_t nd;
+    int64_t draw_it;                       // the iteration whose draws are in draw (-1: none)
+    uint32_t draw[64];
     // speculative iterations: the chain's state at a round start (read by one thread, so that the whole
     // workgroup decides alike), the round's accepted slot (-1: none) and abort flag
     ChainState coop_cs;
@@ -729,6 +731,13 @@ struct SpecShared {
     SpecGroup grp[kMaxWaves];
     int32_t next;         // next product index to hand out
 };
+
+// The flip of draw j (< kmax) of iteration it, as product << 8 | its flip slot (K <= 2^20, 2T <= 256).
+__device__ __forceinline__ uint32_t shake_flip(const RunArgs &a, int g, int64_t it, uint64_t stream, int j, uint64_t n, int T) {
+    if (j >= a.kmax) return 0u;
+    const uint32_t f = shake_draw(a.seed, (uint64_t)g, (uint64_t)it, (uint64_t)j, n, stream), p = f / (uint32_t)(2 * T);
+    return p << 8 | (f - p * (uint32_t)(2 * T));
+}
 
 // IV: the plain search's VND by interval pricing, with one (1) or up to two (2) periods per lane; 0: by full decodes.
 template <bool SPEC, bool LEARNED, bool COOP = false, int MODEL = 0, bool PACK = false, bool MULTI = false, int IV = 0>
@@ -777,33 +786,43 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
     }
     // the chain's solution state, indexed by product: in LDS for the whole launch when it fits (copied in
     // here and back at the end), else in device memory
-    Bits *s_cur, *s_work;
-    int64_t *s_cur_cost, *s_work_cost;
+    // (accessors that branch on the place: a pointer that may be either is a flat access, which waits for both
+    // kinds of memory)
+    const bool st_lds = !COOP && a.state_off >= 0;
+    Bits *l_cur = reinterpret_cast<Bits *>(reinterpret_cast<char *>(s_rows) + (st_lds ? a.state_off : 0)), *l_work = l_cur + K;
+    int64_t *l_cur_cost = reinterpret_cast<int64_t *>(l_work + K), *l_work_cost = l_cur_cost + K;
+    Bits *g_cur = a.cur + cp0, *g_work = a.work + cp0;
+    int64_t *g_cur_cost = a.cur_cost + cp0, *g_work_cost = a.work_cost + cp0;
     if (COOP) {   // x in device memory, shared by the chain's workgroups; each iteration's VND into its slot
         const int64_t sb = ((int64_t)g * a.coop_m + slot) * a.coop_kmax;
-        s_cur = a.cur + cp0;
-        s_cur_cost = a.cur_cost + cp0;
-        s_work = a.coop_res + sb;   // (a split round uses slot 0's region)
-        s_work_cost = a.coop_res_cost + sb;
-    } else if (a.state_off >= 0) {
-        char *base = reinterpret_cast<char *>(s_rows) + a.state_off;
-        s_cur = reinterpret_cast<Bits *>(base);
-        s_work = s_cur + K;
-        s_cur_cost = reinterpret_cast<int64_t *>(s_work + K);
-        s_work_cost = s_cur_cost + K;
+        g_work = a.coop_res + sb;   // (a split round uses slot 0's region)
+        g_work_cost = a.coop_res_cost + sb;
+    } else if (st_lds) {
         for (int i = threadIdx.x; i < K; i += blockDim.x) {
-            s_cur[i] = a.cur[cp0 + i];
-            s_work[i] = a.work[cp0 + i];
-            s_cur_cost[i] = a.cur_cost[cp0 + i];
-            s_work_cost[i] = a.work_cost[cp0 + i];
+            l_cur[i] = g_cur[i];
+            l_work[i] = g_work[i];
+            l_cur_cost[i] = g_cur_cost[i];
+            l_work_cost[i] = g_work_cost[i];
         }
         __syncthreads();
-    } else {
-        s_cur = a.cur + cp0;
-        s_work = a.work + cp0;
-        s_cur_cost = a.cur_cost + cp0;
-        s_work_cost = a.work_cost + cp0;
     }
+    auto cur_bits = [&](int p) -> Bits {
+        if (st_lds) return l_cur[p];
+        return g_cur[p];
+    };
+    auto cur_cost = [&](int p) -> int64_t {
+        if (st_lds) return l_cur_cost[p];
+        return g_cur_cost[p];
+    };
+    auto set_work = [&](int p, const Bits &b, int64_t cost) {
+        if (st_lds) {
+            l_work[p] = b;
+            l_work_cost[p] = cost;
+        } else {
+            g_work[p] = b;
+            g_work_cost[p] = cost;
+        }
+    };
 
     ChainState cs = a.cstate[g];
     int64_t evals = 0;   // per wavefront (uniform)
@@ -821,6 +840,9 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
     mlp::Frags fr;
     if constexpr (LEARNED) mlp::load_frags(a.mlp, fr);
     const uint64_t nflip_all = 2ull * (uint64_t)K * (uint64_t)T;
+    const uint64_t stream = COOP && a.best_of ? (uint64_t)slot : 0u;   // best-of-G: each workgroup its own
+    if (threadIdx.x == 0) sh.draw_it = -1;
+    __syncthreads();
 
     int32_t coop_round = 0;   // speculative iterations: the round this workgroup computes
     int32_t coop_known = -1;  //   thread 0: the round counter as last acquired (-1: not yet)
@@ -867,8 +889,8 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
             kshake = cs.k;   // the shake size after this workgroup's slot rejections
             for (int q = 0; q < slot && !split && !a.best_of; ++q) kshake = kshake >= a.kmax ? 1 : kshake + 1;
             const int64_t sb = ((int64_t)g * a.coop_m + (split ? 0 : slot)) * a.coop_kmax;
-            s_work = a.coop_res + sb;
-            s_work_cost = a.coop_res_cost + sb;
+            g_work = a.coop_res + sb;
+            g_work_cost = a.coop_res_cost + sb;
             if (split) {
                 vfirst = slot * W + wave;
                 vstep = a.coop_m * W;
@@ -881,13 +903,12 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
         // ---- Shake(x, k): wavefront 0 draws k flips and keeps the feasible ones in the dirty list ----
         if (wave == 0) {
             const bool draw = lane < kshake;
-            const uint32_t my = draw ? shake_draw(a.seed, (uint64_t)g, (uint64_t)it, (uint64_t)lane, nflip_all,
-                                                  COOP && a.best_of ? (uint64_t)slot : 0u) : 0u;
-            const int pd = (int)(my / (uint32_t)(2 * T));          // lane j: product and flip slot of draw j
-            const int ld = (int)(my - (uint32_t)pd * (uint32_t)(2 * T));
+            // lane j: product and flip slot of draw j, drawn ahead during the last iteration's VND if it guessed this one
+            const uint32_t f = sh.draw_it == it ? sh.draw[lane] : shake_flip(a, g, it, stream, lane, nflip_all, T);
+            const int pd = (int)(f >> 8), ld = (int)(f & 255u);
             bool dup = false;                                        // an earlier draw hit the same product
             for (int j = 0; j < kshake; ++j) {
-                const int pj = __shfl(pd, j, 64);
+                const int pj = __builtin_amdgcn_readlane(pd, j);
                 dup |= draw && j < lane && pj == pd;
             }
             int nd = 0;
@@ -895,7 +916,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                 // distinct products: the draws are independent, so each lane resolves its own and the
                 // feasible ones are compacted in draw order
                 bool ok = false;
-                Bits b = s_cur[draw ? pd : 0];
+                Bits b = cur_bits(draw ? pd : 0);
                 if (draw) {
                     apply_move(b, ld, T);
                     const ProdParams pp = a.prod[ci.prod0 + pd];
@@ -911,12 +932,13 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                 nd = __popcll(okm);
             } else {
                 for (int j = 0; j < kshake; ++j) {
-                    const uint32_t f = (uint32_t)__shfl((int)my, j, 64);
-                    const int p = (int)(f / (uint32_t)(2 * T));
-                    const int l = (int)(f - (uint32_t)p * (uint32_t)(2 * T));
+                    const int p = __builtin_amdgcn_readlane(pd, j);
+                    const int l = __builtin_amdgcn_readlane(ld, j);
                     int e = -1;
                     for (int q = 0; q < nd; ++q) e = (e < 0 && sh.dp[q] == p) ? q : e;
-                    Bits b = e >= 0 ? sh.db[e] : s_cur[p];
+                    Bits b;
+                    if (e >= 0) b = sh.db[e];
+                    else b = cur_bits(p);
                     apply_move(b, l, T);
                     const ProdParams pp = a.prod[ci.prod0 + p];
                     const bool ok = rows_in_lds ? shake_feasible<MODEL>(b, s_rows + p * T, T, pp)
@@ -938,6 +960,14 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
         }
         __syncthreads();
         nd = sh.nd;
+        // the next iteration's draws (ten rounds of 64-bit products, half as long as a short VND), by the last wavefront
+        // beside the others' VND: the iteration is the next one, or with speculative iterations this workgroup's
+        // next one if the round is rejected as a whole; a wrong guess is drawn again
+        if (wave == W - 1) {
+            const int64_t ahead = it + (COOP && !split && !a.best_of ? a.coop_m : 1);
+            sh.draw[lane] = shake_flip(a, g, ahead, stream, lane, nflip_all, T);
+            if (lane == 0) sh.draw_it = ahead;
+        }
 
         // ---- speculative VND: groups of n_nb wavefronts, one neighbourhood each ----
         if constexpr (SPEC) {
@@ -961,8 +991,9 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                     for (int q = 0; q < nd; ++q) e = (e < 0 && sh.dp[q] == p) ? q : e;
                 }
                 gr.p = p;
-                gr.b = e >= 0 ? sh.db[e] : s_cur[p];
-                gr.c_cur = s_cur_cost[p];
+                if (e >= 0) gr.b = sh.db[e];
+                else gr.b = cur_bits(p);
+                gr.c_cur = cur_cost(p);
                 gr.cost = e >= 0 ? kInf : gr.c_cur;
                 gr.need_ident = e >= 0;
                 gr.q = 0;
@@ -1051,8 +1082,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                             gr.improved = 0;
                         } else {
                             if (gr.improved) vnd_err = 1;
-                            s_work[gr.p] = gr.b;
-                            s_work_cost[gr.p] = gr.cost;
+                            set_work(gr.p, gr.b, gr.cost);
                             part += gr.cost - gr.c_cur;
                             take(gr);
                         }
@@ -1097,8 +1127,9 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                             }
                             PackProd &pr = PL.pk[i];
                             pr.p = p;
-                            pr.b = e >= 0 ? sh.db[e] : s_cur[p];
-                            pr.c_cur = s_cur_cost[p];
+                            if (e >= 0) pr.b = sh.db[e];
+                            else pr.b = cur_bits(p);
+                            pr.c_cur = cur_cost(p);
                             pr.cost = e >= 0 ? kInf : pr.c_cur;   // a shaken product is priced with its first list
                             pr.need_ident = e >= 0 ? 1 : 0;
                         }
@@ -1112,10 +1143,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                     }
                     for (int i = 0; i < cnt; ++i) {
                         const PackProd &pr = PL.pk[i];
-                        if (threadIdx.x == 0) {
-                            s_work[pr.p] = pr.b;
-                            s_work_cost[pr.p] = pr.cost;
-                        }
+                        if (threadIdx.x == 0) set_work(pr.p, pr.b, pr.cost);
                         if (wave == 0) {   // the per-wavefront sums, once
                             part += pr.cost - pr.c_cur;
                             shk += pr.shk;
@@ -1138,9 +1166,11 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                 if constexpr (IV != 0) {
                     p = __builtin_amdgcn_readfirstlane(p);
                     const ProdParams pp = load_uniform(a.prod + ci.prod0 + p);
-                    const int2 *row = rows_in_lds ? s_rows + p * T : inst_rows + p * T;
-                    Bits b = e >= 0 ? sh.db[e] : s_cur[p];
-                    const int64_t c_cur = s_cur_cost[p];
+                    const Bits xb = cur_bits(p);
+                    const int64_t c_cur = cur_cost(p);
+                    Bits b = xb;
+                    if (e >= 0) b = sh.db[e];
+                    const bool has_x = cs.lopt && a.x_opt;
                     iv::Vnd vs{c_cur, 0, evals, 0};
                     auto round_now = [&]() -> int32_t {
                         if constexpr (COOP) {
@@ -1150,12 +1180,16 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                         return coop_round;
                     };
                     constexpr bool kStrict = (MODEL & kModelStrict) != 0;
+                    auto row_at = [&](int t) -> int2 {
+                        if (rows_in_lds) return s_rows[p * T + t];
+                        return inst_rows[p * T + t];
+                    };
                     bool done;
                     if (IV == 1 || T <= 64)
-                        done = iv::vnd<1, kStrict>(b, vs, e >= 0, row, T, pp, a.nb_list, a.n_nb, a.memo != 0,
+                        done = iv::vnd<1, kStrict>(b, vs, e >= 0, row_at, T, pp, has_x, xb, c_cur, a.nb_list, a.n_nb, a.memo != 0,
                                                    *reinterpret_cast<iv::Lds<64, 1> *>(ivbase), coop_round, round_now);
                     else if constexpr (IV == 2)
-                        done = iv::vnd<2, kStrict>(b, vs, e >= 0, row, T, pp, a.nb_list, a.n_nb, a.memo != 0,
+                        done = iv::vnd<2, kStrict>(b, vs, e >= 0, row_at, T, pp, has_x, xb, c_cur, a.nb_list, a.n_nb, a.memo != 0,
                                                    *reinterpret_cast<iv::Lds<64, 2> *>(ivbase), coop_round, round_now);
                     evals = vs.evals;
                     vnd_err |= vs.err;
@@ -1164,10 +1198,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                         stale = true;
                         break;
                     }
-                    if (lane == 0) {
-                        s_work[p] = b;
-                        s_work_cost[p] = vs.cost;
-                    }
+                    if (lane == 0) set_work(p, b, vs.cost);
                     part += vs.cost - c_cur;
                     continue;
                 }
@@ -1181,8 +1212,10 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                     wave_sync_lds();
                     row = slice;
                 }
-                Bits b = e >= 0 ? sh.db[e] : s_cur[p];
-                const int64_t c_cur = s_cur_cost[p];
+                Bits b;
+                if (e >= 0) b = sh.db[e];
+                else b = cur_bits(p);
+                const int64_t c_cur = cur_cost(p);
                 int64_t cost = e >= 0 ? kInf : c_cur;   // a shaken product is priced with its first move list
                 bool need_ident = e >= 0;
                 bool improved = true;
@@ -1293,10 +1326,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                     }
                 }
                 if (stale) break;
-                if (lane == 0) {
-                    s_work[p] = b;
-                    s_work_cost[p] = cost;
-                }
+                if (lane == 0) set_work(p, b, cost);
                 part += cost - c_cur;
             }
             }
@@ -1515,16 +1545,28 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
         // the best solution follows x when x becomes the cheapest so far: the touched products when it held
         // x before, all of x otherwise
         const int bmode = (accepted && F_local < cs.F_best) ? (cs.bsync ? 1 : 2) : 0;
-        const int ntouch = cs.lopt ? nd : K;
-        for (int idx = threadIdx.x; idx < ntouch; idx += blockDim.x) {
-            const int p = cs.lopt ? sh.dp[idx] : idx;
-            if (accepted) {
-                s_cur[p] = s_work[p];
-                s_cur_cost[p] = s_work_cost[p];
-                if (bmode == 1) a.best[cp0 + p] = s_work[p];
+        // once x is a local optimum only the shaken products were touched: wavefront 0, which shakes next, takes them
+        // alone, and the others go on to wait for its shake
+        const bool few = cs.lopt != 0;
+        const int ntouch = few ? nd : K;
+        for (int idx = few ? (wave == 0 ? lane : ntouch) : (int)threadIdx.x; idx < ntouch; idx += few ? 64 : (int)blockDim.x) {
+            const int p = few ? sh.dp[idx] : idx;
+            if (st_lds) {
+                if (accepted) {
+                    l_cur[p] = l_work[p];
+                    l_cur_cost[p] = l_work_cost[p];
+                    if (bmode == 1) a.best[cp0 + p] = l_work[p];
+                } else {
+                    l_work[p] = l_cur[p];
+                    l_work_cost[p] = l_cur_cost[p];
+                }
+            } else if (accepted) {
+                g_cur[p] = g_work[p];
+                g_cur_cost[p] = g_work_cost[p];
+                if (bmode == 1) a.best[cp0 + p] = g_work[p];
             } else {
-                s_work[p] = s_cur[p];
-                s_work_cost[p] = s_cur_cost[p];
+                g_work[p] = g_cur[p];
+                g_work_cost[p] = g_cur_cost[p];
             }
         }
         if (a.trace && threadIdx.x == 0) {
@@ -1540,7 +1582,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
         }
         if (bmode == 2) {
             __syncthreads();
-            for (int q = threadIdx.x; q < K; q += blockDim.x) a.best[cp0 + q] = s_cur[q];
+            for (int q = threadIdx.x; q < K; q += blockDim.x) a.best[cp0 + q] = cur_bits(q);
         }
         if (accepted) {
             cs.F = F_local;
@@ -1551,7 +1593,10 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
             cs.k = cs.k >= a.kmax ? 1 : cs.k + 1;
         }
         cs.F_best = cs.F < cs.F_best ? cs.F : cs.F_best;
-        __syncthreads();
+        // (what the next iteration writes first, its shake, is read after the shake's barrier; its sums are written
+        // after that one)
+        if (few && bmode != 2) wave_sync_lds();
+        else __syncthreads();
     }
 
     if constexpr (COOP) {
@@ -1584,12 +1629,13 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
         }
         return;
     }
-    if (a.state_off >= 0) {   // every iteration ended with a barrier
+    __syncthreads();
+    if (st_lds) {
         for (int i = threadIdx.x; i < K; i += blockDim.x) {
-            a.cur[cp0 + i] = s_cur[i];
-            a.work[cp0 + i] = s_work[i];
-            a.cur_cost[cp0 + i] = s_cur_cost[i];
-            a.work_cost[cp0 + i] = s_work_cost[i];
+            g_cur[i] = l_cur[i];
+            g_work[i] = l_work[i];
+            g_cur_cost[i] = l_cur_cost[i];
+            g_work_cost[i] = l_work_cost[i];
         }
     }
     if (lane == 0) {
@@ -1642,7 +1688,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 // The plain search with interval pricing (contexts of compact products, no move log), one workgroup per chain and
 // with speculative iterations or best-of-G.  IV: 1 when every horizon is at most 64, else 2.
 template <int IV, int MODEL>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_run_iv(RunArgs a) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(IV == 2 ? 3 : 4))) void k_run_iv(RunArgs a) {
     __shared__ RunShared sh;
     __shared__ SwapLists lists;
     __shared__ SpecShared sp;

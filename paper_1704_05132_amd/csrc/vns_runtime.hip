@@ -84,6 +84,7 @@ struct vns_ctx {
     std::vector<int64_t> sum_returns;     // each product's returns over the horizon
     bool compact = false;                 // every product is compact: interval pricing applies (vns_interval.hpp)
     int32_t max_T = 1;
+    bool x_opt = true;                    // every run since the chains were set up searched with nb_list
     int64_t n_prod = 0;
     uint64_t seed = 0;
     int device = 0;
@@ -354,6 +355,7 @@ static vns_status setup_chains(vns_ctx *c) {
     VNS_HIP(c, launch_init(ia, (int)G, c->stream, c->model));
     VNS_HIP(c, hipStreamSynchronize(c->stream));
     c->iteration = 0;
+    c->x_opt = true;
     c->stats = vns_stats{};
     return VNS_OK;
 }
@@ -539,6 +541,8 @@ extern "C" vns_status vns_set_option(vns_ctx *c, int32_t key, int64_t v) {
                 ++n;
                 x >>= 4;
             }
+            // solutions found so far are local optima of the old list, which an evaluation under the new one may improve
+            if ((uint32_t)v != c->nb_list && c->iteration > 0) c->x_opt = false;
             c->nb_list = (uint32_t)v;
             c->n_nb = n;
             return VNS_OK;
@@ -1105,6 +1109,7 @@ extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
     ra.log_n = c->d_log_n;
     ra.log_cap = c->log_cap;
     ra.memo = c->vnd_memo;
+    ra.x_opt = c->x_opt ? 1 : 0;
     int64_t max_rows = 0;
     for (int32_t i = 0; i < c->n_inst; ++i) max_rows = std::max<int64_t>(max_rows, (int64_t)c->K[(size_t)i] * c->T[(size_t)i]);
     // instance rows in LDS for every chain whose instance fits the budget; the others stage one row per wave

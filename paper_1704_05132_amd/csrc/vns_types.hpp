@@ -128,6 +128,7 @@ struct RunArgs {
     int64_t log_cap;
     int32_t state_off;      // byte offset in dynamic LDS of the chain's solution state (cur, work, their
                             // costs: 80 bytes per product, 16-byte aligned); -1 = kept in device memory
+    int32_t x_opt;          // 1 = a chain's x, once a local optimum (ChainState.lopt), is one of nb_list
     int32_t memo;           // 1 = skip a neighbourhood priced without improvement on the current pattern
     // speculative iterations (cooperative launch): m workgroups per chain, see CoopCtl
     int32_t coop_m;             // iterations speculated per round
