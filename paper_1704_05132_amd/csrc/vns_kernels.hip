@@ -626,9 +626,26 @@ __global__ __launch_bounds__(256) void k_eval_prep(EvalPrepArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// k_chain_best: one workgroup per chain; per-product (price, slot) and the chain's lexicographic minimum.
+// k_chain_best: one workgroup per chain; per-product (price, slot) and the chain's lexicographic minimum.  One more
+// workgroup sums the pricing launch's counters and clears them.  Results go where the host reads them (mapped host memory
+// when they are small), so that a call ends with the launch and one wait: six copies and a memset of up to 16 KB
+// each waited for the one before and were 120 of a small call's 131 us.
 // ---------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_chain_best(ChainBestArgs a) {
+    if ((int)blockIdx.x == a.n_chains) {
+        static_assert(kCounterSlots == 256, "one slot per thread");
+        __shared__ unsigned long long s_sum[3][4];
+        unsigned long long *c = a.counters + (size_t)threadIdx.x * kCounterStride;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int64_t n = wave_sum_i64((int64_t)c[i]);
+            if ((threadIdx.x & 63) == 0) s_sum[i][threadIdx.x >> 6] = (unsigned long long)n;
+            c[i] = 0ull;
+        }
+        __syncthreads();
+        if (threadIdx.x < 3) a.totals[threadIdx.x] = s_sum[threadIdx.x][0] + s_sum[threadIdx.x][1] + s_sum[threadIdx.x][2] + s_sum[threadIdx.x][3];
+        return;
+    }
     const int g = a.chain0 + blockIdx.x;
     const ChainInfo ci = a.chains[g];
     const int64_t F = a.cstate[g].F;
@@ -643,8 +660,8 @@ __global__ __launch_bounds__(256) void k_chain_best(ChainBestArgs a) {
             price = F - a.cur_cost[cp] + (int64_t)(key >> kSlotBits);
             slot = (int32_t)(key & ((1u << kSlotBits) - 1));
         }
-        a.prod_price[cp] = price;
-        a.prod_slot[cp] = slot;
+        if (a.prod_price) a.prod_price[cp] = price;
+        if (a.prod_slot) a.prod_slot[cp] = slot;
         const int64_t gs = slot < 0 ? -1 : (int64_t)p * 4 * ci.T + slot;
         if (slot >= 0 && (price < bp || (price == bp && gs < bs))) { bp = price; bs = gs; }
     }
@@ -1794,8 +1811,63 @@ __global__ __launch_bounds__(64) void k_eval_learned(EvalLearnedArgs a, int64_t 
     }
 }
 
-// k_advance: the iteration counter moves on once every chain of the launch has read it.
-__global__ void k_advance(int64_t *it, int32_t iters) { *it += iters; }
+// k_run_done: the iteration counter moves on once every chain of the launch has read it, and the chains' counts are
+// summed for the host (one workgroup: 16384 chains are 16 rounds of it).
+__global__ __launch_bounds__(1024) void k_run_done(RunDoneArgs a) {
+    int64_t v[5] = {0, 0, 0, 0, 0};
+    int err = 0;
+    for (int64_t g = threadIdx.x; g < a.n_chains; g += blockDim.x) {
+        const ChainState cs = a.cstate[g];
+        v[0] += cs.evals;
+        v[1] += cs.evals * a.chains[g].T;
+        v[2] += cs.discarded;
+        v[3] += cs.nb_evals;
+        v[4] += cs.fallbacks;
+        err |= cs.err;
+    }
+    __shared__ int64_t s_v[5][16];
+    __shared__ int s_err[16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int e = (__any(err & 1) ? 1 : 0) | (__any(err & 2) ? 2 : 0);
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        const int64_t n = wave_sum_i64(v[i]);
+        if (lane == 0) s_v[i][wave] = n;
+    }
+    if (lane == 0) s_err[wave] = e;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        RunTotals t{};
+        for (int w = 0; w < 16; ++w) {
+            t.evals += s_v[0][w];
+            t.steps += s_v[1][w];
+            t.discarded += s_v[2][w];
+            t.nb_evals += s_v[3][w];
+            t.fallbacks += s_v[4][w];
+            t.err |= s_err[w];
+        }
+        *a.out = t;
+        *a.it_counter += a.iters;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_rows_out(RowsOutArgs a) {
+    const int64_t n = (int64_t)a.K * a.T;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int k = (int)(i / a.T), t = (int)(i - (int64_t)k * a.T);
+        const Bits &b = a.x[k];
+        a.zM[i] = (uint8_t)((b.m[t >> 5] >> (t & 31)) & 1u);
+        a.zR[i] = (uint8_t)((b.r[t >> 5] >> (t & 31)) & 1u);
+    }
+}
+
+__global__ __launch_bounds__(256) void k_costs_out(CostsOutArgs a) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= a.n) return;
+    const ChainState &cs = a.cstate[i];
+    a.F[i] = cs.F;
+    a.F_best[i] = cs.F_best;
+}
 
 // ---------------------------------------------------------------------------------------------------
 // Host-side launchers (called by the runtime).
@@ -1877,9 +1949,24 @@ hipError_t launch_eval_inc(const EvalArgs &a, const EvalWg *wg, int64_t n_wg, si
     return hipGetLastError();
 }
 
-hipError_t launch_chain_best(const ChainBestArgs &a, int n_chains, hipStream_t s) {
-    if (n_chains <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_chain_best, dim3(n_chains), dim3(256), 0, s, a);
+hipError_t launch_chain_best(const ChainBestArgs &a, hipStream_t s) {
+    hipLaunchKernelGGL(k_chain_best, dim3(a.n_chains + 1), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_run_done(const RunDoneArgs &a, hipStream_t s) {
+    hipLaunchKernelGGL(k_run_done, dim3(1), dim3(1024), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_rows_out(const RowsOutArgs &a, hipStream_t s) {
+    const int64_t n = (int64_t)a.K * a.T;
+    hipLaunchKernelGGL(k_rows_out, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1024)), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_costs_out(const CostsOutArgs &a, hipStream_t s) {
+    hipLaunchKernelGGL(k_costs_out, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -1946,28 +2033,20 @@ hipError_t coop_fits(int waves, size_t lds_bytes, int64_t blocks, bool *fits, Ru
     return hipSuccess;
 }
 
-hipError_t launch_run_coop(const RunArgs &a, int n_chains, int waves, size_t lds_bytes, int64_t *it_counter,
-                           hipStream_t s, RunKind kind, int model) {
+hipError_t launch_run_coop(const RunArgs &a, int n_chains, int waves, size_t lds_bytes, hipStream_t s, RunKind kind,
+                           int model) {
     if (n_chains <= 0 || a.iters <= 0) return hipSuccess;
     RunArgs args = a;
     void *params[] = {&args};
-    hipError_t e = hipLaunchCooperativeKernel(coop_kernel(kind, model),
-                                              dim3((unsigned)(n_chains * a.coop_m)), dim3(64 * waves), params,
-                                              (unsigned)lds_bytes, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_advance, dim3(1), dim3(1), 0, s, it_counter, a.iters);
-    return hipGetLastError();
+    return hipLaunchCooperativeKernel(coop_kernel(kind, model), dim3((unsigned)(n_chains * a.coop_m)), dim3(64 * waves),
+                                      params, (unsigned)lds_bytes, s);
 }
 
-hipError_t launch_run(const RunArgs &a, RunKind kind, int n_chains, int waves, size_t lds_bytes, int64_t *it_counter,
-                      hipStream_t s, int model) {
+hipError_t launch_run(const RunArgs &a, RunKind kind, int n_chains, int waves, size_t lds_bytes, hipStream_t s, int model) {
     if (n_chains <= 0 || a.iters <= 0) return hipSuccess;
     RunArgs args = a;
     void *params[] = {&args};
-    hipError_t e = hipLaunchKernel(run_kernel(kind, model), dim3(n_chains), dim3(64 * waves), params, lds_bytes, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_advance, dim3(1), dim3(1), 0, s, it_counter, a.iters);
-    return hipGetLastError();
+    return hipLaunchKernel(run_kernel(kind, model), dim3(n_chains), dim3(64 * waves), params, lds_bytes, s);
 }
 
 }  // namespace vns

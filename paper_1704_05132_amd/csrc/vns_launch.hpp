@@ -25,11 +25,40 @@ struct ChainBestArgs {
     const ChainState *cstate;
     const int64_t *cur_cost;
     const uint64_t *prod_key;
-    int64_t *prod_price;   // [cp] price of each product's best move
-    int32_t *prod_slot;    // [cp] its local slot
+    int64_t *prod_price;   // [cp] price of each product's best move (or null)
+    int32_t *prod_slot;    // [cp] its local slot (or null)
     int64_t *best;         // [chains of the launch]
     int32_t *best_slot;
     int32_t chain0;
+    int32_t n_chains;
+    unsigned long long *counters;   // the launch's spread counters: summed into totals and set to zero for the next call
+    unsigned long long *totals;     // [3]
+};
+
+// The totals of a search over every chain, and the device iteration counter moved on by `iters`.
+struct RunTotals {
+    int64_t evals, steps, discarded, nb_evals, fallbacks;
+    int32_t err, pad;
+};
+struct RunDoneArgs {
+    const ChainInfo *chains;
+    const ChainState *cstate;
+    int64_t n_chains;
+    int64_t *it_counter;
+    int32_t iters;
+    RunTotals *out;
+};
+
+// Rows of a solution as bytes, and the chains' costs, written where the host reads them.
+struct RowsOutArgs {
+    const Bits *x;          // [K]
+    int32_t K, T;
+    uint8_t *zM, *zR;       // [K][T]
+};
+struct CostsOutArgs {
+    const ChainState *cstate;
+    int64_t n;
+    int64_t *F, *F_best;
 };
 
 // Variants of the search kernel: sequential VND, speculative VND, learned VND.
@@ -96,17 +125,18 @@ hipError_t launch_eval_prep(const EvalPrepArgs &a, hipStream_t s);
 // Incremental pricing of the same sweep; lds_bytes of dynamic LDS hold each workgroup's base snapshots
 // (kSnapBytes per chain and period 0..T).
 hipError_t launch_eval_inc(const EvalArgs &a, const EvalWg *wg, int64_t n_wg, size_t lds_bytes, hipStream_t s);
-hipError_t launch_chain_best(const ChainBestArgs &a, int n_chains, hipStream_t s);
+// The argmins of n_chains chains (none: only the counters' totals).
+hipError_t launch_chain_best(const ChainBestArgs &a, hipStream_t s);
+hipError_t launch_run_done(const RunDoneArgs &a, hipStream_t s);
+hipError_t launch_rows_out(const RowsOutArgs &a, hipStream_t s);
+hipError_t launch_costs_out(const CostsOutArgs &a, hipStream_t s);
 // Speculative iterations (a.coop_m workgroups per chain, cooperative launch): whether blocks workgroups of
-// `waves` wavefronts and lds_bytes of dynamic LDS are all resident at once, and the launch itself (then the
-// device iteration counter advances by a.iters).  kind: kPlain (any decode reading `model`), kInterval,
+// `waves` wavefronts and lds_bytes of dynamic LDS are all resident at once, and the launch itself.  kind: kPlain (any decode reading `model`), kInterval,
 // kIntervalLong, kLearned or kLearnedPacked.
 hipError_t coop_fits(int waves, size_t lds_bytes, int64_t blocks, bool *fits, RunKind kind, int model);
-hipError_t launch_run_coop(const RunArgs &a, int n_chains, int waves, size_t lds_bytes, int64_t *it_counter,
-                           hipStream_t s, RunKind kind, int model);
-// The search kernel variant `kind` over n_chains workgroups, then the device iteration counter advances by a.iters (two kernels on s;
-// both can be captured in a graph).
-hipError_t launch_run(const RunArgs &a, RunKind kind, int n_chains, int waves, size_t lds_bytes, int64_t *it_counter,
-                      hipStream_t s, int model);
+hipError_t launch_run_coop(const RunArgs &a, int n_chains, int waves, size_t lds_bytes, hipStream_t s, RunKind kind,
+                           int model);
+// The search kernel variant `kind` over n_chains workgroups (launch_run_done then moves the device iteration counter on).
+hipError_t launch_run(const RunArgs &a, RunKind kind, int n_chains, int waves, size_t lds_bytes, hipStream_t s, int model);
 
 }  // namespace vns

@@ -66,11 +66,8 @@ void *scratch_of(int device) {
 thread_local int32_t g_inject_alloc = 0;
 thread_local int32_t g_inject_device = 0;
 
-template <class T>
-struct DevBuf {
-    T *p = nullptr;
-    size_t n = 0;
-};
+constexpr size_t kStageBytes = 256u << 10;
+constexpr size_t kScorerKeep = 64u << 20;
 
 }  // namespace
 
@@ -166,6 +163,14 @@ struct vns_ctx {
     char *ws = nullptr;                   // caller-owned workspace (vns_bind_workspace), its size and flags
     size_t ws_bytes = 0;
     uint32_t ws_flags = 0;
+
+    // Small results are written by the kernels straight into this pinned, device-mapped buffer (kStageBytes, held for
+    // the context's life) and copied to the caller's arrays after the call's one wait.
+    unsigned char *h_stage = nullptr, *d_stage = nullptr;
+    // scorer calls: device copies of the caller's rows, targets and scores and the gradient's scratch, kept between calls
+    // up to kScorerKeep bytes each
+    float *d_x = nullptr, *d_y = nullptr, *d_s = nullptr, *d_part = nullptr, *d_grad = nullptr;
+    size_t cap_x = 0, cap_y = 0, cap_s = 0, cap_part = 0;
 
     hipStream_t own_stream = nullptr, stream = nullptr;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -276,6 +281,13 @@ static void free_all(vns_ctx *c) {
     dfree(c->d_rows);
     dfree(c->d_prod);
     dfree(c->d_evals);
+    dfree(c->d_x);
+    dfree(c->d_y);
+    dfree(c->d_s);
+    dfree(c->d_part);
+    dfree(c->d_grad);
+    if (c->h_stage) (void)hipHostFree(c->h_stage);
+    c->h_stage = c->d_stage = nullptr;
     dfree(c->d_coop_ctl);
     dfree(c->d_coop_slot);
     dfree(c->d_coop_res);
@@ -484,6 +496,9 @@ extern "C" vns_status vns_create_batch(int32_t n_inst, const int32_t *K, const i
     VNS_CREATE_HIP(dmalloc(&c->d_rows, (size_t)n_rows));
     VNS_CREATE_HIP(dmalloc(&c->d_prod, (size_t)n_prod));
     VNS_CREATE_HIP(dmalloc(&c->d_evals, (size_t)counter_words()));
+    VNS_CREATE_HIP(hipMemsetAsync(c->d_evals, 0, sizeof(unsigned long long) * counter_words(), c->stream));
+    VNS_CREATE_HIP(hipHostMalloc((void **)&c->h_stage, kStageBytes, hipHostMallocMapped));
+    VNS_CREATE_HIP(hipHostGetDevicePointer((void **)&c->d_stage, c->h_stage, 0));
     VNS_CREATE_HIP(dmalloc(&c->d_mlp, (size_t)mlp::kParams));
     VNS_CREATE_HIP(dmalloc(&c->d_adam_m, (size_t)mlp::kParams));
     VNS_CREATE_HIP(dmalloc(&c->d_adam_v, (size_t)mlp::kParams));
@@ -767,19 +782,72 @@ static vns_status ws_check(vns_ctx *c, WsLayout *L) {
 // ---------------------------------------------------------------------------------------------------
 // pricing
 // ---------------------------------------------------------------------------------------------------
-// Sums of the spread workgroup counters (waits for the stream).
-static hipError_t read_counters(vns_ctx *c, unsigned long long (&ev)[3]) {
-    std::vector<unsigned long long> h((size_t)counter_words());
-    hipError_t e = hipMemcpyAsync(h.data(), c->d_evals, sizeof(unsigned long long) * h.size(), hipMemcpyDeviceToHost,
-                                  c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    ev[0] = ev[1] = ev[2] = 0;
-    for (int s = 0; s < kCounterSlots; ++s) {
-        ev[0] += h[(size_t)s * kCounterStride];
-        ev[1] += h[(size_t)s * kCounterStride + 1];
-        ev[2] += h[(size_t)s * kCounterStride + 2];
+// What a pricing call returns, and where its kernels put it: in the pinned stage what fits, in stage order totals, best,
+// best_slot, prod_best, prod_best_slot, slot_price.
+struct EvalOut {
+    int64_t *slot_price, *prod_best;
+    int32_t *prod_best_slot;
+    int64_t *best;
+    int32_t *best_slot;
+    size_t o_best = 0, o_slot = 0, o_pb = 0, o_ps = 0, o_sp = 0;   // stage offsets (0: not in the stage)
+    size_t used = 64;                                              // the totals' part
+
+    size_t place(size_t bytes) {
+        const size_t at = used, end = (at + bytes + 63) & ~(size_t)63;
+        if (end > kStageBytes) return 0;
+        used = end;
+        return at;
     }
-    return e;
+    EvalOut(int64_t *sp, int64_t *pb, int32_t *ps, int64_t *b, int32_t *bs, int64_t ng, int64_t n_cp)
+        : slot_price(sp), prod_best(pb), prod_best_slot(ps), best(b), best_slot(bs) {
+        if (best) o_best = place(sizeof(int64_t) * (size_t)ng);
+        if (best_slot) o_slot = place(sizeof(int32_t) * (size_t)ng);
+        if (prod_best) o_pb = place(sizeof(int64_t) * (size_t)n_cp);
+        if (prod_best_slot) o_ps = place(sizeof(int32_t) * (size_t)n_cp);
+    }
+};
+
+// The argmins and counts of a pricing launch (keys and counters as it left them), its outputs to the caller, and the
+// call's statistics.  d_sp: the slot prices in device memory, when they are not in the stage.
+static vns_status finish_eval(vns_ctx *c, EvalOut &o, int32_t g0, int32_t ng, int64_t cp_begin, int64_t n_cp, int64_t n_slots,
+                              const uint64_t *keys, unsigned long long *counters, const int64_t *d_sp) {
+    ChainBestArgs cb{};
+    cb.chains = c->d_chains;
+    cb.cstate = c->d_cs;
+    cb.cur_cost = c->d_cur_cost;
+    cb.prod_key = keys;
+    cb.prod_price = !o.prod_best ? nullptr : o.o_pb ? reinterpret_cast<int64_t *>(c->d_stage + o.o_pb) - cp_begin : c->d_prod_price;
+    cb.prod_slot = !o.prod_best_slot ? nullptr : o.o_ps ? reinterpret_cast<int32_t *>(c->d_stage + o.o_ps) - cp_begin : c->d_prod_slot;
+    cb.best = o.o_best ? reinterpret_cast<int64_t *>(c->d_stage + o.o_best) : c->d_best;
+    cb.best_slot = o.o_slot ? reinterpret_cast<int32_t *>(c->d_stage + o.o_slot) : c->d_best_slot;
+    cb.chain0 = g0;
+    cb.n_chains = ng;
+    cb.counters = counters;
+    cb.totals = reinterpret_cast<unsigned long long *>(c->d_stage);
+    VNS_HIP(c, launch_chain_best(cb, c->stream));
+    auto big = [&](void *dst, const void *src, size_t bytes) {
+        return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, c->stream);
+    };
+    if (o.slot_price && !o.o_sp) VNS_HIP(c, big(o.slot_price, d_sp, sizeof(int64_t) * (size_t)n_slots));
+    if (o.prod_best && !o.o_pb) VNS_HIP(c, big(o.prod_best, c->d_prod_price + cp_begin, sizeof(int64_t) * (size_t)n_cp));
+    if (o.prod_best_slot && !o.o_ps) VNS_HIP(c, big(o.prod_best_slot, c->d_prod_slot + cp_begin, sizeof(int32_t) * (size_t)n_cp));
+    if (o.best && !o.o_best) VNS_HIP(c, big(o.best, c->d_best, sizeof(int64_t) * (size_t)ng));
+    if (o.best_slot && !o.o_slot) VNS_HIP(c, big(o.best_slot, c->d_best_slot, sizeof(int32_t) * (size_t)ng));
+    VNS_HIP(c, hipStreamSynchronize(c->stream));
+    float ms = 0.f;
+    VNS_HIP(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));
+    if (o.o_best) std::memcpy(o.best, c->h_stage + o.o_best, sizeof(int64_t) * (size_t)ng);
+    if (o.o_slot) std::memcpy(o.best_slot, c->h_stage + o.o_slot, sizeof(int32_t) * (size_t)ng);
+    if (o.o_pb) std::memcpy(o.prod_best, c->h_stage + o.o_pb, sizeof(int64_t) * (size_t)n_cp);
+    if (o.o_ps) std::memcpy(o.prod_best_slot, c->h_stage + o.o_ps, sizeof(int32_t) * (size_t)n_cp);
+    if (o.o_sp) std::memcpy(o.slot_price, c->h_stage + o.o_sp, sizeof(int64_t) * (size_t)n_slots);
+    unsigned long long ev[3];
+    std::memcpy(ev, c->h_stage, sizeof(ev));
+    c->stats.last_eval_evals = (int64_t)ev[0];
+    c->stats.last_eval_period_steps = (int64_t)ev[1];
+    c->stats.last_eval_decoded_steps = (int64_t)ev[2];
+    c->stats.last_eval_ms = ms;
+    return VNS_OK;
 }
 
 extern "C" vns_status vns_eval_neighbourhood(vns_ctx *c, uint32_t nb_mask, int32_t chain, int64_t *slot_price,
@@ -811,8 +879,14 @@ extern "C" vns_status vns_eval_neighbourhood(vns_ctx *c, uint32_t nb_mask, int32
         vns_status s = ws_check(c, &wl);
         if (s != VNS_OK) return s;
     }
-    int64_t *d_sp = ws_price ? reinterpret_cast<int64_t *>(c->ws + wl.price_off) : c->d_slot_price;
-    if (slot_price && !ws_price && (size_t)n_slots > c->slot_price_cap) {
+    const bool interval = c->compact && !(c->model & kModelDispose);
+    EvalOut out(slot_price, prod_best, prod_best_slot, best, best_slot, ng, n_cp);
+    // (only interval pricing writes every slot once; the full decode clears them first)
+    if (slot_price && interval) out.o_sp = out.place(sizeof(int64_t) * (size_t)n_slots);
+    int64_t *d_sp = out.o_sp   ? reinterpret_cast<int64_t *>(c->d_stage + out.o_sp)
+                    : ws_price ? reinterpret_cast<int64_t *>(c->ws + wl.price_off)
+                               : c->d_slot_price;
+    if (slot_price && !out.o_sp && !ws_price && (size_t)n_slots > c->slot_price_cap) {
         dfree(c->d_slot_price);
         c->slot_price_cap = 0;
         VNS_HIP(c, dmalloc(&c->d_slot_price, (size_t)n_slots));
@@ -829,7 +903,6 @@ extern "C" vns_status vns_eval_neighbourhood(vns_ctx *c, uint32_t nb_mask, int32
     const int32_t spread = c->eval_inc ? 0 : c->eval_spread;
     const int64_t key[4] = {g0, ng, group, c->eval_inc ? 1 : 2 + spread};
     EvalWg *d_tab = ws_tab ? reinterpret_cast<EvalWg *>(c->ws + wl.eval_off) : c->d_eval_wg;
-    const bool interval = c->compact && !(c->model & kModelDispose);
     if (!interval &&
         !(key[0] == c->eval_wg_key[0] && key[1] == c->eval_wg_key[1] && key[2] == c->eval_wg_key[2] &&
           key[3] == c->eval_wg_key[3])) {
@@ -929,7 +1002,6 @@ extern "C" vns_status vns_eval_neighbourhood(vns_ctx *c, uint32_t nb_mask, int32
     ea.prod_key = c->d_prod_key;
     ea.evals = c->d_evals;
     ea.nb_mask = nb_mask;
-    VNS_HIP(c, hipMemsetAsync(c->d_evals, 0, sizeof(unsigned long long) * counter_words(), c->stream));
     VNS_HIP(c, hipEventRecord(c->ev0, c->stream));
     if (interval)
         VNS_HIP(c, launch_eval_iv(ea, cp_begin, n_cp, c->n_cu, maxT > 64, c->eval_inc != 0, c->stream, c->model));
@@ -939,27 +1011,7 @@ extern "C" vns_status vns_eval_neighbourhood(vns_ctx *c, uint32_t nb_mask, int32
     else
         VNS_HIP(c, launch_eval(ea, d_tab, c->eval_wg_n, c->stream, c->model, spread ? spread : 4));
     VNS_HIP(c, hipEventRecord(c->ev1, c->stream));
-    ChainBestArgs cb{c->d_chains, c->d_cs, c->d_cur_cost, c->d_prod_key, c->d_prod_price, c->d_prod_slot,
-                     c->d_best, c->d_best_slot, g0};
-    VNS_HIP(c, launch_chain_best(cb, ng, c->stream));
-    if (slot_price)
-        VNS_HIP(c, hipMemcpyAsync(slot_price, d_sp, sizeof(int64_t) * (size_t)n_slots, hipMemcpyDeviceToHost, c->stream));
-    if (prod_best)
-        VNS_HIP(c, hipMemcpyAsync(prod_best, c->d_prod_price + cp_begin, sizeof(int64_t) * (size_t)n_cp, hipMemcpyDeviceToHost, c->stream));
-    if (prod_best_slot)
-        VNS_HIP(c, hipMemcpyAsync(prod_best_slot, c->d_prod_slot + cp_begin, sizeof(int32_t) * (size_t)n_cp, hipMemcpyDeviceToHost, c->stream));
-    if (best) VNS_HIP(c, hipMemcpyAsync(best, c->d_best, sizeof(int64_t) * (size_t)ng, hipMemcpyDeviceToHost, c->stream));
-    if (best_slot)
-        VNS_HIP(c, hipMemcpyAsync(best_slot, c->d_best_slot, sizeof(int32_t) * (size_t)ng, hipMemcpyDeviceToHost, c->stream));
-    unsigned long long ev[3] = {0, 0, 0};
-    VNS_HIP(c, read_counters(c, ev));
-    float ms = 0.f;
-    VNS_HIP(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));
-    c->stats.last_eval_evals = (int64_t)ev[0];
-    c->stats.last_eval_period_steps = (int64_t)ev[1];
-    c->stats.last_eval_decoded_steps = (int64_t)ev[2];
-    c->stats.last_eval_ms = ms;
-    return VNS_OK;
+    return finish_eval(c, out, g0, ng, cp_begin, n_cp, n_slots, c->d_prod_key, c->d_evals, d_sp);
 }
 
 // The same pricing with its scratch in the per-GPU static array: no device or host allocation.  The table
@@ -1013,7 +1065,13 @@ extern "C" vns_status vns_eval_neighbourhood_noalloc(vns_ctx *c, uint32_t nb_mas
     pa.chains_per_inst = (int32_t)c->chains_per_inst;
     pa.table = tab;
     pa.counters = ctr;
-    VNS_HIP(c, launch_eval_prep(pa, c->stream));
+    // interval pricing has no table, and counts into the context's own counters
+    const bool interval = c->compact && !(c->model & kModelDispose);
+    if (!interval) VNS_HIP(c, launch_eval_prep(pa, c->stream));
+    EvalOut out(slot_price, prod_best, prod_best_slot, best, best_slot, ng, n_cp);
+    if (slot_price && interval) out.o_sp = out.place(sizeof(int64_t) * (size_t)n_slots);
+    if (out.o_sp) sp = reinterpret_cast<int64_t *>(c->d_stage + out.o_sp);
+    if (interval) ctr = c->d_evals;
     EvalArgs ea{};
     ea.cp_chain = c->d_cp_chain;
     ea.chains = c->d_chains;
@@ -1028,7 +1086,7 @@ extern "C" vns_status vns_eval_neighbourhood_noalloc(vns_ctx *c, uint32_t nb_mas
     ea.evals = ctr;
     ea.nb_mask = nb_mask;
     VNS_HIP(c, hipEventRecord(c->ev0, c->stream));
-    if (c->compact && !(c->model & kModelDispose)) {
+    if (interval) {
         int32_t maxT = 1;
         for (int32_t g = g0; g < g0 + ng; ++g) maxT = std::max<int32_t>(maxT, c->chains[(size_t)g].T);
         VNS_HIP(c, launch_eval_iv(ea, cp_begin, n_cp, c->n_cu, maxT > 64, false, c->stream, c->model));
@@ -1036,31 +1094,7 @@ extern "C" vns_status vns_eval_neighbourhood_noalloc(vns_ctx *c, uint32_t nb_mas
         VNS_HIP(c, launch_eval(ea, tab, n_cp, c->stream, c->model));
     }
     VNS_HIP(c, hipEventRecord(c->ev1, c->stream));
-    ChainBestArgs cb{c->d_chains, c->d_cs, c->d_cur_cost, keys - cp_begin, c->d_prod_price, c->d_prod_slot, c->d_best,
-                     c->d_best_slot, g0};
-    VNS_HIP(c, launch_chain_best(cb, ng, c->stream));
-    if (slot_price)
-        VNS_HIP(c, hipMemcpyAsync(slot_price, sp, sizeof(int64_t) * (size_t)n_slots, hipMemcpyDeviceToHost, c->stream));
-    if (prod_best)
-        VNS_HIP(c, hipMemcpyAsync(prod_best, c->d_prod_price + cp_begin, sizeof(int64_t) * (size_t)n_cp, hipMemcpyDeviceToHost, c->stream));
-    if (prod_best_slot)
-        VNS_HIP(c, hipMemcpyAsync(prod_best_slot, c->d_prod_slot + cp_begin, sizeof(int32_t) * (size_t)n_cp, hipMemcpyDeviceToHost, c->stream));
-    if (best) VNS_HIP(c, hipMemcpyAsync(best, c->d_best, sizeof(int64_t) * (size_t)ng, hipMemcpyDeviceToHost, c->stream));
-    if (best_slot)
-        VNS_HIP(c, hipMemcpyAsync(best_slot, c->d_best_slot, sizeof(int32_t) * (size_t)ng, hipMemcpyDeviceToHost, c->stream));
-    unsigned long long h[counter_words()];
-    VNS_HIP(c, hipMemcpyAsync(h, ctr, sizeof(h), hipMemcpyDeviceToHost, c->stream));
-    VNS_HIP(c, hipStreamSynchronize(c->stream));
-    unsigned long long ev[3] = {0, 0, 0};
-    for (int q = 0; q < kCounterSlots; ++q)
-        for (int w = 0; w < 3; ++w) ev[w] += h[(size_t)q * kCounterStride + (size_t)w];
-    float ms = 0.f;
-    VNS_HIP(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));
-    c->stats.last_eval_evals = (int64_t)ev[0];
-    c->stats.last_eval_period_steps = (int64_t)ev[1];
-    c->stats.last_eval_decoded_steps = (int64_t)ev[2];
-    c->stats.last_eval_ms = ms;
-    return VNS_OK;
+    return finish_eval(c, out, g0, ng, cp_begin, n_cp, n_slots, keys - cp_begin, ctr, sp);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -1245,8 +1279,7 @@ extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
         ra.best_of = best ? 1 : 0;
         ra.best_literal = c->best_literal;
         VNS_HIP(c, hipEventRecord(c->ev0, c->stream));
-        VNS_HIP(c, launch_run_coop(ra, (int)G, waves, lds_coop, c->d_iter, c->stream, coop_k, c->model));
-        VNS_HIP(c, hipEventRecord(c->ev1, c->stream));
+        VNS_HIP(c, launch_run_coop(ra, (int)G, waves, lds_coop, c->stream, coop_k, c->model));
     } else if (c->use_graph) {
         const int64_t key[5] = {iters, G, waves * 8 + (int64_t)run_k, (int64_t)lds, (int64_t)(intptr_t)ra.trace};
         bool same = true;
@@ -1254,7 +1287,7 @@ extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
         if (!same || !c->graph_exec) {
             drop_graph(c);
             VNS_HIP(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-            hipError_t le = launch_run(ra, run_k, (int)G, waves, lds, c->d_iter, c->stream, c->model);
+            hipError_t le = launch_run(ra, run_k, (int)G, waves, lds, c->stream, c->model);
             hipGraph_t gr = nullptr;
             hipError_t ce = hipStreamEndCapture(c->stream, &gr);
             if (le != hipSuccess) {
@@ -1268,27 +1301,20 @@ extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
         }
         VNS_HIP(c, hipEventRecord(c->ev0, c->stream));
         VNS_HIP(c, hipGraphLaunch(c->graph_exec, c->stream));
-        VNS_HIP(c, hipEventRecord(c->ev1, c->stream));
     } else {
         VNS_HIP(c, hipEventRecord(c->ev0, c->stream));
-        VNS_HIP(c, launch_run(ra, run_k, (int)G, waves, lds, c->d_iter, c->stream, c->model));
-        VNS_HIP(c, hipEventRecord(c->ev1, c->stream));
+        VNS_HIP(c, launch_run(ra, run_k, (int)G, waves, lds, c->stream, c->model));
     }
-    std::vector<ChainState> cs((size_t)G);
-    VNS_HIP(c, hipMemcpyAsync(cs.data(), c->d_cs, sizeof(ChainState) * (size_t)G, hipMemcpyDeviceToHost, c->stream));
+    const RunDoneArgs rd{c->d_chains, c->d_cs, G, c->d_iter, iters, reinterpret_cast<RunTotals *>(c->d_stage)};
+    VNS_HIP(c, launch_run_done(rd, c->stream));
+    VNS_HIP(c, hipEventRecord(c->ev1, c->stream));
     VNS_HIP(c, hipStreamSynchronize(c->stream));
     float ms = 0.f;
     VNS_HIP(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));
-    int64_t ev = 0, steps = 0, nbe = 0, fbs = 0, thrown = 0;
-    int32_t err = 0;
-    for (size_t g = 0; g < cs.size(); ++g) {
-        ev += cs[g].evals;
-        thrown += cs[g].discarded;
-        steps += cs[g].evals * c->chains[g].T;
-        nbe += cs[g].nb_evals;
-        fbs += cs[g].fallbacks;
-        err |= cs[g].err;
-    }
+    RunTotals tot;
+    std::memcpy(&tot, c->h_stage, sizeof(tot));
+    const int64_t ev = tot.evals, steps = tot.steps, nbe = tot.nb_evals, fbs = tot.fallbacks, thrown = tot.discarded;
+    const int32_t err = tot.err;
     c->stats.last_run_learned_evals = nbe;
     c->stats.last_run_fallbacks = fbs;
     c->stats.last_run_discarded_evals = thrown;
@@ -1320,10 +1346,19 @@ extern "C" vns_status vns_get_cost(vns_ctx *c, int32_t chain, int64_t *F, int64_
 
 extern "C" vns_status vns_get_costs(vns_ctx *c, int64_t *F, int64_t *F_best) {
     VNS_LIVE(c);
-    std::vector<ChainState> cs(c->chains.size());
-    VNS_HIP(c, hipMemcpyAsync(cs.data(), c->d_cs, sizeof(ChainState) * cs.size(), hipMemcpyDeviceToHost, c->stream));
+    const size_t n = c->chains.size(), bytes = sizeof(int64_t) * n;
+    if (2 * bytes <= kStageBytes) {
+        int64_t *d = reinterpret_cast<int64_t *>(c->d_stage);
+        VNS_HIP(c, launch_costs_out(CostsOutArgs{c->d_cs, (int64_t)n, d, d + n}, c->stream));
+        VNS_HIP(c, hipStreamSynchronize(c->stream));
+        if (F) std::memcpy(F, c->h_stage, bytes);
+        if (F_best) std::memcpy(F_best, c->h_stage + bytes, bytes);
+        return VNS_OK;
+    }
+    std::vector<ChainState> cs(n);
+    VNS_HIP(c, hipMemcpyAsync(cs.data(), c->d_cs, sizeof(ChainState) * n, hipMemcpyDeviceToHost, c->stream));
     VNS_HIP(c, hipStreamSynchronize(c->stream));
-    for (size_t g = 0; g < cs.size(); ++g) {
+    for (size_t g = 0; g < n; ++g) {
         if (F) F[g] = cs[g].F;
         if (F_best) F_best[g] = cs[g].F_best;
     }
@@ -1337,8 +1372,16 @@ extern "C" vns_status vns_get_solution(vns_ctx *c, int32_t chain, int32_t which,
     if (which != VNS_SOLUTION_CURRENT && which != VNS_SOLUTION_BEST) return fail(c, VNS_EINVAL, "which must be 0 or 1");
     if (!zM || !zR) return fail(c, VNS_EINVAL, "NULL output");
     const ChainInfo &ci = c->chains[(size_t)chain];
-    std::vector<Bits> b((size_t)ci.K);
+    const size_t bytes = (size_t)ci.K * (size_t)ci.T;
     const Bits *src = (which == VNS_SOLUTION_BEST ? c->d_bestx : c->d_cur) + ci.cp0;
+    if (2 * bytes <= kStageBytes) {
+        VNS_HIP(c, launch_rows_out(RowsOutArgs{src, ci.K, ci.T, c->d_stage, c->d_stage + bytes}, c->stream));
+        VNS_HIP(c, hipStreamSynchronize(c->stream));
+        std::memcpy(zM, c->h_stage, bytes);
+        std::memcpy(zR, c->h_stage + bytes, bytes);
+        return VNS_OK;
+    }
+    std::vector<Bits> b((size_t)ci.K);
     VNS_HIP(c, hipMemcpyAsync(b.data(), src, sizeof(Bits) * (size_t)ci.K, hipMemcpyDeviceToHost, c->stream));
     VNS_HIP(c, hipStreamSynchronize(c->stream));
     for (int32_t k = 0; k < ci.K; ++k)
@@ -1430,9 +1473,12 @@ extern "C" vns_status vns_get_trajectory(vns_ctx *c, int32_t chain, vns_record *
     if (n) *n = avail;
     const int64_t m = std::min<int64_t>(avail, cap < 0 ? 0 : cap);
     if (rec && m > 0) {
-        VNS_HIP(c, hipMemcpyAsync(rec, c->d_trace + (int64_t)chain * c->trace_iters, sizeof(vns_record) * (size_t)m,
+        const size_t bytes = sizeof(vns_record) * (size_t)m;
+        const bool staged = bytes <= kStageBytes;
+        VNS_HIP(c, hipMemcpyAsync(staged ? (void *)c->h_stage : rec, c->d_trace + (int64_t)chain * c->trace_iters, bytes,
                                   hipMemcpyDeviceToHost, c->stream));
         VNS_HIP(c, hipStreamSynchronize(c->stream));
+        if (staged) std::memcpy(rec, c->h_stage, bytes);
     }
     return VNS_OK;
 }
@@ -1537,54 +1583,74 @@ static vns_status record_mlp_time(vns_ctx *c, int64_t rows) {
     return VNS_OK;
 }
 
+// A device buffer of at least n floats that the context keeps for the next call (up to kScorerKeep bytes: trim_scorer).
+static hipError_t scorer_buf(float *&p, size_t &cap, size_t n) {
+    if (n <= cap) return hipSuccess;
+    dfree(p);
+    cap = 0;
+    const hipError_t e = dmalloc(&p, n);
+    if (e == hipSuccess) cap = n;
+    return e;
+}
+static void trim_scorer(vns_ctx *c) {
+    auto trim = [](float *&p, size_t &cap) {
+        if (cap * sizeof(float) > kScorerKeep) {
+            dfree(p);
+            cap = 0;
+        }
+    };
+    trim(c->d_x, c->cap_x);
+    trim(c->d_y, c->cap_y);
+    trim(c->d_s, c->cap_s);
+    trim(c->d_part, c->cap_part);
+}
+struct ScorerCall {   // gives back what a large call needed, however it ends
+    vns_ctx *c;
+    ~ScorerCall() { trim_scorer(c); }
+};
+// The caller's rows (and targets) on the device, and the gradient's scratch for minibatches of up to `batch` rows.
+static vns_status scorer_data(vns_ctx *c, const float *feats, const float *targets, int64_t n, int64_t batch) {
+    VNS_HIP(c, scorer_buf(c->d_x, c->cap_x, (size_t)n * mlp::kF));
+    VNS_HIP(c, hipMemcpyAsync(c->d_x, feats, sizeof(float) * mlp::kF * (size_t)n, hipMemcpyHostToDevice, c->stream));
+    if (!targets) return VNS_OK;
+    VNS_HIP(c, scorer_buf(c->d_y, c->cap_y, (size_t)n));
+    VNS_HIP(c, hipMemcpyAsync(c->d_y, targets, sizeof(float) * (size_t)n, hipMemcpyHostToDevice, c->stream));
+    VNS_HIP(c, scorer_buf(c->d_part, c->cap_part, (size_t)(mlp_grad_partials(batch) * (mlp::kParams + 1))));
+    if (!c->d_grad) VNS_HIP(c, dmalloc(&c->d_grad, (size_t)(mlp::kParams + 1)));
+    return VNS_OK;
+}
+
 extern "C" vns_status vns_mlp_score(vns_ctx *c, const float *feats, int64_t n, float *scores) {
     VNS_LIVE(c);
     if (n < 0 || (n > 0 && (!feats || !scores))) return fail(c, VNS_EINVAL, "bad arguments");
     if (n == 0) return VNS_OK;
-    Scoped<float> X, S;
-    VNS_HIP(c, dmalloc(&X.p, (size_t)n * mlp::kF));
-    VNS_HIP(c, dmalloc(&S.p, (size_t)n));
-    VNS_HIP(c, hipMemcpyAsync(X.p, feats, sizeof(float) * mlp::kF * (size_t)n, hipMemcpyHostToDevice, c->stream));
+    ScorerCall guard{c};
+    vns_status st = scorer_data(c, feats, nullptr, n, 0);
+    if (st != VNS_OK) return st;
+    VNS_HIP(c, scorer_buf(c->d_s, c->cap_s, (size_t)n));
     VNS_HIP(c, hipEventRecord(c->ev0, c->stream));
-    VNS_HIP(c, launch_mlp_score(c->d_mlp, X.p, n, S.p, c->stream));
+    VNS_HIP(c, launch_mlp_score(c->d_mlp, c->d_x, n, c->d_s, c->stream));
     VNS_HIP(c, hipEventRecord(c->ev1, c->stream));
-    VNS_HIP(c, hipMemcpyAsync(scores, S.p, sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, c->stream));
+    VNS_HIP(c, hipMemcpyAsync(scores, c->d_s, sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, c->stream));
     VNS_HIP(c, hipStreamSynchronize(c->stream));
     return record_mlp_time(c, n);
 }
-
-// Device scratch of one gradient evaluation over up to n rows.
-struct GradScratch {
-    Scoped<float> part, grad;
-    vns_status alloc(vns_ctx *c, int64_t n) {
-        const int64_t nb = mlp_grad_partials(n);
-        VNS_HIP(c, dmalloc(&part.p, (size_t)(nb * (mlp::kParams + 1))));
-        VNS_HIP(c, dmalloc(&grad.p, (size_t)(mlp::kParams + 1)));
-        return VNS_OK;
-    }
-};
 
 extern "C" vns_status vns_mlp_grad(vns_ctx *c, const float *feats, const float *targets, int64_t n, float *grads,
                                    float *loss) {
     VNS_LIVE(c);
     if (n <= 0 || !feats || !targets) return fail(c, VNS_EINVAL, "bad arguments");
-    Scoped<float> X, Y;
-    VNS_HIP(c, dmalloc(&X.p, (size_t)n * mlp::kF));
-    VNS_HIP(c, dmalloc(&Y.p, (size_t)n));
-    VNS_HIP(c, hipMemcpyAsync(X.p, feats, sizeof(float) * mlp::kF * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    VNS_HIP(c, hipMemcpyAsync(Y.p, targets, sizeof(float) * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    GradScratch gs;
-    vns_status st = gs.alloc(c, n);
+    ScorerCall guard{c};
+    vns_status st = scorer_data(c, feats, targets, n, n);
     if (st != VNS_OK) return st;
     VNS_HIP(c, hipEventRecord(c->ev0, c->stream));
-    VNS_HIP(c, launch_mlp_grad(c->d_mlp, X.p, Y.p, nullptr, n, gs.part.p, gs.grad.p,
-                               c->stream));
+    VNS_HIP(c, launch_mlp_grad(c->d_mlp, c->d_x, c->d_y, nullptr, n, c->d_part, c->d_grad, c->stream));
     VNS_HIP(c, hipEventRecord(c->ev1, c->stream));
-    std::vector<float> g((size_t)mlp::kParams + 1);
-    VNS_HIP(c, hipMemcpyAsync(g.data(), gs.grad.p, sizeof(float) * g.size(), hipMemcpyDeviceToHost, c->stream));
+    float *g = reinterpret_cast<float *>(c->h_stage);
+    VNS_HIP(c, hipMemcpyAsync(g, c->d_grad, sizeof(float) * (mlp::kParams + 1), hipMemcpyDeviceToHost, c->stream));
     VNS_HIP(c, hipStreamSynchronize(c->stream));
-    if (grads) std::memcpy(grads, g.data(), sizeof(float) * mlp::kParams);
-    if (loss) *loss = g[(size_t)mlp::kParams];
+    if (grads) std::memcpy(grads, g, sizeof(float) * mlp::kParams);
+    if (loss) *loss = g[mlp::kParams];
     return record_mlp_time(c, n);
 }
 
@@ -1592,14 +1658,9 @@ extern "C" vns_status vns_mlp_train(vns_ctx *c, const float *feats, const float 
                                     int32_t batch, float lr, uint64_t seed, float *last_loss) {
     VNS_LIVE(c);
     if (n <= 0 || !feats || !targets || epochs < 0 || batch < 1 || !(lr > 0.f)) return fail(c, VNS_EINVAL, "bad arguments");
-    Scoped<float> X, Y;
-    VNS_HIP(c, dmalloc(&X.p, (size_t)n * mlp::kF));
-    VNS_HIP(c, dmalloc(&Y.p, (size_t)n));
-    VNS_HIP(c, hipMemcpyAsync(X.p, feats, sizeof(float) * mlp::kF * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    VNS_HIP(c, hipMemcpyAsync(Y.p, targets, sizeof(float) * (size_t)n, hipMemcpyHostToDevice, c->stream));
     const int64_t bmax = std::min<int64_t>(batch, n);
-    GradScratch gs;
-    vns_status st = gs.alloc(c, bmax);
+    ScorerCall guard{c};
+    vns_status st = scorer_data(c, feats, targets, n, bmax);
     if (st != VNS_OK) return st;
     // rows of each epoch in the order (mul * i + add) mod n, mul coprime to n, add drawn per epoch
     uint64_t mul = 1000003ull;
@@ -1614,13 +1675,13 @@ extern "C" vns_status vns_mlp_train(vns_ctx *c, const float *feats, const float 
         for (int64_t s0 = 0; s0 < n; s0 += bmax) {
             const int64_t cnt = std::min<int64_t>(bmax, n - s0);
             // the minibatch's rows (mul i + add) mod n, i = s0 .. s0 + cnt - 1, are computed in the gradient kernel
-            VNS_HIP(c, launch_mlp_train_step(c->d_mlp, c->d_adam_m, c->d_adam_v, X.p, Y.p, RowPerm{mul, add, s0, n}, cnt,
-                                             gs.part.p, gs.grad.p, lr, ++c->adam_step, c->stream));
+            VNS_HIP(c, launch_mlp_train_step(c->d_mlp, c->d_adam_m, c->d_adam_v, c->d_x, c->d_y, RowPerm{mul, add, s0, n}, cnt,
+                                             c->d_part, c->d_grad, lr, ++c->adam_step, c->stream));
         }
     }
     VNS_HIP(c, hipEventRecord(c->ev1, c->stream));
     if (epochs > 0) {
-        VNS_HIP(c, hipMemcpyAsync(&loss, gs.grad.p + mlp::kParams, sizeof(float), hipMemcpyDeviceToHost, c->stream));
+        VNS_HIP(c, hipMemcpyAsync(&loss, c->d_grad + mlp::kParams, sizeof(float), hipMemcpyDeviceToHost, c->stream));
     }
     VNS_HIP(c, hipStreamSynchronize(c->stream));
     drop_graph(c);
@@ -1674,7 +1735,6 @@ extern "C" vns_status vns_eval_learned(vns_ctx *c, uint32_t nb, int32_t chain, i
     hipLaunchKernelGGL(k_fill_nan, dim3((unsigned)((n_slots + 255) / 256)), dim3(256), 0, c->stream, S.p, n_slots);
     VNS_HIP(c, hipGetLastError());
     VNS_HIP(c, hipMemsetAsync(Sel.p, 0, (size_t)n_slots, c->stream));
-    VNS_HIP(c, hipMemsetAsync(c->d_evals, 0, sizeof(unsigned long long) * counter_words(), c->stream));
     EvalLearnedArgs a{};
     a.cp_chain = c->d_cp_chain;
     a.chains = c->d_chains;
@@ -1699,9 +1759,14 @@ extern "C" vns_status vns_eval_learned(vns_ctx *c, uint32_t nb, int32_t chain, i
     if (prod_best) VNS_HIP(c, hipMemcpyAsync(prod_best, c->d_prod_price + ci.cp0, sizeof(int64_t) * (size_t)ci.K, hipMemcpyDeviceToHost, c->stream));
     if (prod_best_slot) VNS_HIP(c, hipMemcpyAsync(prod_best_slot, c->d_prod_slot + ci.cp0, sizeof(int32_t) * (size_t)ci.K, hipMemcpyDeviceToHost, c->stream));
     if (fallback) VNS_HIP(c, hipMemcpyAsync(fallback, Fb.p, (size_t)ci.K, hipMemcpyDeviceToHost, c->stream));
-    unsigned long long ev[3] = {0, 0, 0};
-    VNS_HIP(c, read_counters(c, ev));
-    c->stats.last_eval_evals = (int64_t)ev[0];
-    c->stats.last_eval_period_steps = (int64_t)ev[0] * ci.T;
+    ChainBestArgs cb{};
+    cb.counters = c->d_evals;
+    cb.totals = reinterpret_cast<unsigned long long *>(c->d_stage);
+    VNS_HIP(c, launch_chain_best(cb, c->stream));
+    VNS_HIP(c, hipStreamSynchronize(c->stream));
+    unsigned long long ev = 0;
+    std::memcpy(&ev, c->h_stage, sizeof(ev));
+    c->stats.last_eval_evals = (int64_t)ev;
+    c->stats.last_eval_period_steps = (int64_t)ev * ci.T;
     return VNS_OK;
 }
