@@ -457,17 +457,25 @@ struct Pattern {
 // ident: the pattern's own cost is not known yet; it is computed and returned in `start`.  x, x_cost: a pattern of the
 // product known to be a local optimum of this list, and its cost (with has_x): most shaken products return to it
 // (86 to 91% of single flips at T = 12..104), and no neighbourhood of it improves.
+// Choose: how a neighbourhood's move is chosen from the exact changes dx of its moves (NoChoice: the best one).  The
+// learned VND's choice ranks the moves by the scorer, takes the best of the best-ranked if it improves and the best of all
+// otherwise; it is handed the pattern and returns the changes of its ranked moves alone.
+struct NoChoice {
+    static constexpr bool kRanks = false;
+    __device__ __forceinline__ int count(int) const { return 0; }   // moves ranked of a neighbourhood's
+};
 struct Vnd {
     int64_t cost;    // in: the pattern's cost (without ident); out: the local optimum's
     int64_t start;   // out: the pattern's own cost
     int64_t evals;   // move-evaluations, added to
     int32_t err;     // out: 1 if the pass guard was hit
+    int64_t ranked = 0, fallbacks = 0;   // learned: neighbourhood evaluations, and those priced whole
 };
 
-template <int NV, bool STRICT, class Row, class Now>
+template <int NV, bool STRICT, class Row, class Choose, class Now>
 __device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, Row row_at, int T, const ProdParams &pp,
                                     bool has_x, const Bits &x, int64_t x_cost, uint32_t nb_list, int n_nb, bool memo,
-                                    Lds<64, NV> &sh, int32_t round, Now now) {
+                                    Lds<64, NV> &sh, Choose &choose, int32_t round, Now now) {
     const int lane = threadIdx.x & 63;
     const Cost c = cost_of(pp);
     int2 row[NV];
@@ -484,6 +492,18 @@ __device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, Row row_at, int
         for (int v = 0; v < NV; ++v) same = same && k.m[v] == kx.m[v] && k.r[v] == kx.r[v];
         return same;
     };
+    auto pack = [](const Masks<64, NV> &z) {
+        Bits o;
+#pragma unroll
+        for (int v = 0; v < kWords / 2; ++v) {
+            const uint64_t m = v < NV ? z.m[v] : 0, r = v < NV ? z.r[v] : 0;
+            o.m[2 * v] = (uint32_t)m;
+            o.m[2 * v + 1] = (uint32_t)(m >> 32);
+            o.r[2 * v] = (uint32_t)r;
+            o.r[2 * v + 1] = (uint32_t)(r >> 32);
+        }
+        return o;
+    };
     // per neighbourhood (0 flip zM, 1 flip zR, 2 shift), wavefront-uniform: best change, its slot, moves
     int32_t best[3] = {0, 0, 0}, slot[3] = {0, 0, 0}, cnt[3] = {0, 0, 0};
     uint32_t known = 0, clean = 0;
@@ -493,12 +513,19 @@ __device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, Row row_at, int
         int n = 0;
 #pragma unroll
         for (int v = 0; v < NV; ++v) n += __popcll(swap_bits<64, NV>(k.m, v, T)) + __popcll(swap_bits<64, NV>(k.r, v, T));
-        int sum = 0;
+        int sum = 0, ranked = 0, whole = 0;
         for (int i = 0; i < n_nb; ++i) {
             const int moves = ((nb_list >> (4 * i)) & 4u) ? n : T;
-            sum += moves * ((i > q ? 1 : 0) + (another && !(memo && i > q) ? 1 : 0));
+            const int times = (i > q ? 1 : 0) + (another && !(memo && i > q) ? 1 : 0);
+            sum += (moves + choose.count(moves)) * times;
+            ranked += times;
+            whole += moves > 0 ? times : 0;
         }
         s.evals += sum;
+        if constexpr (Choose::kRanks) {
+            s.ranked += ranked;
+            s.fallbacks += whole;
+        }
     };
     Pattern<64, NV, STRICT> pat;
     int32_t cost = (int32_t)s.cost;
@@ -556,6 +583,32 @@ __device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, Row row_at, int
                         n += __popcll(vm) + __popcll(vr);
                     }
                 }
+                if constexpr (Choose::kRanks) {
+                    // the best-ranked moves; if none of them improves, all of them (priced already)
+                    uint64_t keep[2][NV] = {};
+                    int counted = 0;
+                    ++s.ranked;
+                    if (n > 0) {
+                        counted = choose.rank(pack(k), nb, keep);
+                        bool better = false;
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) {
+                            better |= (__ballot(dx[0][v] < 0) & keep[0][v]) != 0;
+                            if (i == 2) better |= (__ballot(dx[1][v] < 0) & keep[1][v]) != 0;
+                        }
+                        if (better) {
+#pragma unroll
+                            for (int v = 0; v < NV; ++v) {
+                                dx[0][v] = lane_bit<64>(keep[0][v]) ? dx[0][v] : kBad32;
+                                dx[1][v] = lane_bit<64>(keep[1][v]) ? dx[1][v] : kBad32;
+                            }
+                            n = counted;
+                        } else {
+                            ++s.fallbacks;
+                            n += counted;
+                        }
+                    }
+                }
                 // the lowest (cost, slot), as the sweep finds it
                 uint32_t low = 0;
 #pragma unroll
@@ -586,6 +639,9 @@ __device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, Row row_at, int
                     alive = false;
                     break;
                 }
+            } else if constexpr (Choose::kRanks) {
+                ++s.ranked;   // priced before on this pattern without an improving move
+                s.fallbacks += (i == 2 ? cnt[2] : T) > 0 ? 1 : 0;
             }
             const int32_t bx = i == 0 ? best[0] : i == 1 ? best[1] : best[2];
             s.evals += i == 0 ? cnt[0] : i == 1 ? cnt[1] : cnt[2];
@@ -616,14 +672,7 @@ __device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, Row row_at, int
             }
         }
     }
-#pragma unroll
-    for (int v = 0; v < kWords / 2; ++v) {
-        const uint64_t m = v < NV ? k.m[v] : 0, r = v < NV ? k.r[v] : 0;
-        b.m[2 * v] = (uint32_t)m;
-        b.m[2 * v + 1] = (uint32_t)(m >> 32);
-        b.r[2 * v] = (uint32_t)r;
-        b.r[2 * v + 1] = (uint32_t)(r >> 32);
-    }
+    b = pack(k);
     s.cost = cost;
     return alive;
 }

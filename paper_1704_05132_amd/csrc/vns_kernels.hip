@@ -762,7 +762,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
     static_assert(!PACK || LEARNED, "the packed form is the learned VND's");
     static_assert(!(SPEC && LEARNED), "the speculative VND prices whole neighbourhoods");
     static_assert(!(COOP && SPEC), "speculative iterations run the sequential VND");
-    static_assert(!IV || !(SPEC || LEARNED || MULTI || (MODEL & kModelDispose)), "interval pricing: the plain VND");
+    static_assert(!IV || !(SPEC || PACK || MULTI || (MODEL & kModelDispose)), "interval pricing: one product per wavefront");
     int g = blockIdx.x, slot = 0;   // chain, and (speculative iterations) the iteration of a round it computes
     if constexpr (COOP) {
         const int m = a.coop_m;
@@ -847,13 +847,13 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
     int64_t nb_evals = 0, fallbacks = 0;   // learned mode, per wavefront
     // learned search: this wavefront's tiles after the rows region (kept 16-byte aligned), and the scorer's
     // weight fragments
-    const int rows_entries = run_rows_entries(a.lds_rows, IV ? 0 : W);
-    // (the packed form: one region for the workgroup)
-    char *lbase = reinterpret_cast<char *>(s_rows + rows_entries) + (PACK ? 0 : wave * kLearnedWaveBytes);
+    const int rows_entries = run_rows_entries(a.lds_rows, IV && !LEARNED ? 0 : W);
+    // (the packed form: one region for the workgroup), and interval pricing's states and records after them
+    constexpr int kTiles = LEARNED ? kLearnedWaveBytes : 0;
+    constexpr int kIvBytes = IV == 2 ? (int)sizeof(iv::Lds<64, 2>) : IV == 1 ? (int)sizeof(iv::Lds<64, 1>) : 0;
+    char *lbase = reinterpret_cast<char *>(s_rows + rows_entries) + (PACK ? 0 : wave * (kTiles + kIvBytes));
+    char *ivbase = lbase + kTiles;
     LearnedLds L{reinterpret_cast<__bf16 *>(lbase), reinterpret_cast<uint16_t *>(lbase + 64 * 16 * 2)};
-    // interval pricing: this wavefront's states and records, in the same place
-    char *ivbase = reinterpret_cast<char *>(s_rows + rows_entries) +
-                   wave * (IV == 2 ? sizeof(iv::Lds<64, 2>) : sizeof(iv::Lds<64, 1>));
     mlp::Frags fr;
     if constexpr (LEARNED) mlp::load_frags(a.mlp, fr);
     const uint64_t nflip_all = 2ull * (uint64_t)K * (uint64_t)T;
@@ -1202,12 +1202,30 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                         return inst_rows[p * T + t];
                     };
                     bool done;
-                    if (IV == 1 || T <= 64)
-                        done = iv::vnd<1, kStrict>(b, vs, e >= 0, row_at, T, pp, has_x, xb, c_cur, a.nb_list, a.n_nb, a.memo != 0,
-                                                   *reinterpret_cast<iv::Lds<64, 1> *>(ivbase), coop_round, round_now);
-                    else if constexpr (IV == 2)
-                        done = iv::vnd<2, kStrict>(b, vs, e >= 0, row_at, T, pp, has_x, xb, c_cur, a.nb_list, a.n_nb, a.memo != 0,
-                                                   *reinterpret_cast<iv::Lds<64, 2> *>(ivbase), coop_round, round_now);
+                    auto vnd = [&](auto &choose) {
+                        if (IV == 1 || T <= 64)
+                            done = iv::vnd<1, kStrict>(b, vs, e >= 0, row_at, T, pp, has_x, xb, c_cur, a.nb_list, a.n_nb, a.memo != 0,
+                                                       *reinterpret_cast<iv::Lds<64, 1> *>(ivbase), choose, coop_round, round_now);
+                        else if constexpr (IV == 2)
+                            done = iv::vnd<2, kStrict>(b, vs, e >= 0, row_at, T, pp, has_x, xb, c_cur, a.nb_list, a.n_nb, a.memo != 0,
+                                                       *reinterpret_cast<iv::Lds<64, 2> *>(ivbase), choose, coop_round, round_now);
+                    };
+                    if constexpr (LEARNED) {
+                        const int2 *row = s_rows + p * T;   // the scorer reads any period: a row in LDS
+                        if (!rows_in_lds) {
+                            int2 *slice = s_rows + wave * kTMax;
+                            for (int t = lane; t < T; t += 64) slice[t] = inst_rows[p * T + t];
+                            wave_sync_lds();
+                            row = slice;
+                        }
+                        LearnedChoice choose{row, T, pp, lists[wave], L, fr, a.permille};
+                        vnd(choose);
+                        nb_evals += vs.ranked;
+                        fallbacks += vs.fallbacks;
+                    } else {
+                        iv::NoChoice choose;
+                        vnd(choose);
+                    }
                     evals = vs.evals;
                     vnd_err |= vs.err;
                     if (e >= 0) shk += vs.start - c_cur;
@@ -1722,6 +1740,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void k
     run_chain<false, false, true, MODEL, false, false, IV>(a, sh, lists, sp, s_rows);
 }
 
+// The learned search with interval pricing.
+template <int IV, bool COOP>
+__global__ __launch_bounds__(512) void k_run_learned_iv(RunArgs a) {
+    __shared__ RunShared sh;
+    __shared__ SwapLists lists;
+    __shared__ SpecShared sp;
+    extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
+    run_chain<false, true, COOP, 0, false, false, IV>(a, sh, lists, sp, s_rows);
+}
+
 __global__ __launch_bounds__(1024) void k_run_spec(RunArgs a) {
     __shared__ RunShared sh;
     __shared__ SwapLists lists;
@@ -1992,6 +2020,8 @@ static const void *run_kernel(RunKind kind, int model) {
     switch (kind) {
         case RunKind::kInterval: return interval_kernel(false, false, model);
         case RunKind::kIntervalLong: return interval_kernel(false, true, model);
+        case RunKind::kLearnedInterval: return reinterpret_cast<const void *>(&k_run_learned_iv<1, false>);
+        case RunKind::kLearnedIntervalLong: return reinterpret_cast<const void *>(&k_run_learned_iv<2, false>);
         case RunKind::kSpec: return reinterpret_cast<const void *>(&k_run_spec);
         case RunKind::kLearned: return reinterpret_cast<const void *>(&k_run_learned);
         case RunKind::kLearnedPacked: return reinterpret_cast<const void *>(&k_run_learned_packed);
@@ -2012,6 +2042,8 @@ hipError_t run_kernel_lds(RunKind kind, size_t *static_bytes, size_t dynamic_byt
 static const void *coop_kernel(RunKind kind, int model) {
     if (kind == RunKind::kLearned) return reinterpret_cast<const void *>(&k_run_learned_coop);
     if (kind == RunKind::kLearnedPacked) return reinterpret_cast<const void *>(&k_run_learned_coop_packed);
+    if (kind == RunKind::kLearnedInterval) return reinterpret_cast<const void *>(&k_run_learned_iv<1, true>);
+    if (kind == RunKind::kLearnedIntervalLong) return reinterpret_cast<const void *>(&k_run_learned_iv<2, true>);
     if (kind == RunKind::kInterval || kind == RunKind::kIntervalLong)
         return interval_kernel(true, kind == RunKind::kIntervalLong, model);
     return by_model<PickCoop>(model);

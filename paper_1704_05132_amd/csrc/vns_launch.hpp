@@ -64,8 +64,10 @@ struct CostsOutArgs {
 // Variants of the search kernel: sequential VND, speculative VND, learned VND.
 // kPlainShort: the plain search kernel with consecutive neighbourhoods priced side by side in one pass at
 // horizons up to kMultiMaxT (launched when an instance has one; the same moves and counts as kPlain).
-// kInterval, kIntervalLong: the plain search by interval pricing (horizons up to 64, or any).
-enum class RunKind { kPlain = 0, kSpec = 1, kLearned = 2, kLearnedPacked = 3, kPlainShort = 4, kInterval = 5, kIntervalLong = 6 };
+// kInterval, kIntervalLong: the plain search by interval pricing (horizons up to 64, or any); kLearnedInterval,
+// kLearnedIntervalLong: the learned one.
+enum class RunKind { kPlain = 0, kSpec = 1, kLearned = 2, kLearnedPacked = 3, kPlainShort = 4, kInterval = 5, kIntervalLong = 6,
+                     kLearnedInterval = 7, kLearnedIntervalLong = 8 };
 
 // LDS of interval pricing per search wavefront.
 int64_t interval_wave_bytes(bool long_T);
@@ -132,7 +134,7 @@ hipError_t launch_rows_out(const RowsOutArgs &a, hipStream_t s);
 hipError_t launch_costs_out(const CostsOutArgs &a, hipStream_t s);
 // Speculative iterations (a.coop_m workgroups per chain, cooperative launch): whether blocks workgroups of
 // `waves` wavefronts and lds_bytes of dynamic LDS are all resident at once, and the launch itself.  kind: kPlain (any decode reading `model`), kInterval,
-// kIntervalLong, kLearned or kLearnedPacked.
+// kIntervalLong, kLearned, kLearnedInterval, kLearnedIntervalLong or kLearnedPacked.
 hipError_t coop_fits(int waves, size_t lds_bytes, int64_t blocks, bool *fits, RunKind kind, int model);
 hipError_t launch_run_coop(const RunArgs &a, int n_chains, int waves, size_t lds_bytes, hipStream_t s, RunKind kind,
                            int model);

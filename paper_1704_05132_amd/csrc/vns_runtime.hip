@@ -1163,18 +1163,23 @@ extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
     for (int32_t i = 0; i < c->n_inst; ++i) min_T = std::min<int32_t>(min_T, c->T[(size_t)i]);
     // interval pricing where it applies (its VND keeps no move log); otherwise full decodes, with the variant for
     // batches with a short horizon in the one-workgroup search
-    const bool interval = kind == RunKind::kPlain && c->compact && !(c->model & kModelDispose) && ra.log_x == nullptr;
+    const bool interval = (kind == RunKind::kPlain || kind == RunKind::kLearned) && c->compact &&
+                          !(c->model & kModelDispose) && ra.log_x == nullptr;
     const bool long_T = c->max_T > 64;
-    const RunKind coop_k = interval ? (long_T ? RunKind::kIntervalLong : RunKind::kInterval) : kind;
-    const RunKind run_k = interval ? coop_k : (kind == RunKind::kPlain && min_T <= kMultiMaxT) ? RunKind::kPlainShort : kind;
+    const RunKind coop_k = !interval                   ? kind
+                           : kind == RunKind::kLearned ? (long_T ? RunKind::kLearnedIntervalLong : RunKind::kLearnedInterval)
+                                                       : (long_T ? RunKind::kIntervalLong : RunKind::kInterval);
+    const RunKind run_k = (!interval && kind == RunKind::kPlain && min_T <= kMultiMaxT) ? RunKind::kPlainShort : coop_k;
     VNS_HIP(c, run_kernel_lds(run_k, &static_lds, 0, c->model));
     const bool packed = c->permille > 0 && c->learned_pack > 1;
-    const int64_t learned = interval         ? waves * interval_wave_bytes(long_T)   // LDS after the rows
-                            : c->permille <= 0 ? 0
-                            : packed         ? (int64_t)pack_region_bytes(waves, c->learned_pack)
-                                             : (int64_t)waves * kLearnedWaveBytes;
+    // LDS after the rows
+    const int64_t learned = (c->permille <= 0 ? 0
+                             : packed         ? (int64_t)pack_region_bytes(waves, c->learned_pack)
+                                              : (int64_t)waves * kLearnedWaveBytes) +
+                            (interval ? waves * interval_wave_bytes(long_T) : 0);
     const int64_t room = c->max_lds_per_wg - (int64_t)static_lds - learned;   // dynamic LDS left for rows
-    const int64_t slices = interval ? 0 : (int64_t)waves * kTMax;    // per-wave rows when the instance does not fit
+    const bool no_slices = interval && kind == RunKind::kPlain;
+    const int64_t slices = no_slices ? 0 : (int64_t)waves * kTMax;    // per-wave rows when the instance does not fit
     if (room < slices * (int64_t)sizeof(int2)) return fail(c, VNS_EINVAL, "not enough LDS for the search kernel");
     // the chains' solution state (80 bytes per product) when it fits beside the per-wave row slices
     int64_t max_K = 0;
@@ -1187,7 +1192,7 @@ extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
     int64_t min_rows = max_rows;
     for (int32_t i = 0; i < c->n_inst; ++i) min_rows = std::min<int64_t>(min_rows, (int64_t)c->K[(size_t)i] * c->T[(size_t)i]);
     ra.lds_rows = min_rows > budget ? 0 : (int32_t)std::min<int64_t>(max_rows, budget);
-    const size_t rows_bytes = (size_t)run_rows_entries(ra.lds_rows, interval ? 0 : waves) * sizeof(int2);
+    const size_t rows_bytes = (size_t)run_rows_entries(ra.lds_rows, no_slices ? 0 : waves) * sizeof(int2);
     ra.state_off = state_bytes > 0 ? (int32_t)(rows_bytes + (size_t)learned) : -1;
     const size_t lds = rows_bytes + (size_t)learned + (size_t)state_bytes;
     VNS_HIP(c, run_kernel_lds(run_k, &static_lds, lds, c->model));
@@ -1204,8 +1209,8 @@ extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
         hipError_t e = coop_fits(waves, lds_coop, G * m, ok, coop_k, c->model);
         if (e == hipSuccess && !*ok && interval && ra.lds_rows > 0) {
             // the rows beside interval pricing's records may be what does not fit: it reads them from device memory too
-            lds_coop = (size_t)learned;
             ra.lds_rows = 0;
+            lds_coop = (size_t)run_rows_entries(0, no_slices ? 0 : waves) * sizeof(int2) + (size_t)learned;
             e = coop_fits(waves, lds_coop, G * m, ok, coop_k, c->model);
             if (!*ok) ra.lds_rows = rows_one;
         }

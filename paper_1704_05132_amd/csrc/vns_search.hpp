@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include "vns_device.hpp"
+#include "vns_interval.hpp"
 #include "vns_mlp.hpp"
 
 namespace vns {
@@ -242,8 +243,10 @@ __device__ __forceinline__ int learned_select(const Bits &b, const int2 *row, in
                                               int nflip, bool fm, const uint16_t *list, __bf16 *sx, uint16_t *sel,
                                               const mlp::Frags &fr, int permille, float *score_out, uint8_t *sel_out) {
     const int lane = threadIdx.x & 63;
-    // 1. scores of every move, kept as (sortable score << 32 | slot) keys, up to four per lane
-    uint64_t sk[4] = {kInfKey, kInfKey, kInfKey, kInfKey};
+    // 1. scores of every move, up to four per lane, as order-preserving integers; the moves not selected yet
+    uint32_t sc[4] = {~0u, ~0u, ~0u, ~0u};
+    uint64_t left[4] = {0, 0, 0, 0};   // (wavefront-uniform)
+    int slots[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int ch = 0; ch < 4; ++ch) {
         if (ch * 64 >= nitems) break;
@@ -260,23 +263,37 @@ __device__ __forceinline__ int learned_select(const Bits &b, const int2 *row, in
         for (int i = 0; i < mlp::kF; ++i) sx[lane * mlp::kF + i] = (__bf16)f[i];
         wave_sync_lds();
         const float s = mlp::forward64(sx, fr);
+        slots[ch] = slot;
+        left[ch] = __ballot(idx < nitems);
         if (idx < nitems) {
-            sk[ch] = ((uint64_t)mlp::sortable(s) << 32) | (uint64_t)slot;
+            sc[ch] = mlp::sortable(s);
             if (score_out) score_out[slot] = s;
         }
     }
-    // 2. the best-ranked moves, by repeated wavefront minima
+    // 2. the best-ranked moves: the lowest score of those left, by a scan; of equal ones the lowest slot, which is the
+    // first item (the minimum of (score, slot) keys over 64-bit shuffles took 12 LDS round trips a move)
     int n_sel = (permille * nitems + 999) / 1000;   // nitems >= 1 here
     n_sel = n_sel < 1 ? 1 : (n_sel > nitems ? nitems : n_sel);
     for (int r = 0; r < n_sel; ++r) {
-        uint64_t my = sk[0];
+        uint32_t my = 0;
 #pragma unroll
-        for (int ch = 1; ch < 4; ++ch) my = sk[ch] < my ? sk[ch] : my;
-        const uint64_t m = wave_min_u64(my);
+        for (int ch = 0; ch < 4; ++ch)
+            if (ch * 64 < nitems) my = max(my, iv::lane_bit<64>(left[ch]) ? ~sc[ch] : 0u);
+        const uint32_t low = ~(uint32_t)iv::last_lane(iv::scan_max<64>(my));
+        int slot = 0;
+        bool found = false;
 #pragma unroll
-        for (int ch = 0; ch < 4; ++ch) sk[ch] = sk[ch] == m ? kInfKey : sk[ch];
-        if (lane == 0) sel[r] = (uint16_t)(m & 0xFFFFu);
-        if (sel_out && lane == 0 && m != kInfKey) sel_out[m & 0xFFFFu] = 1;
+        for (int ch = 0; ch < 4; ++ch) {
+            const uint64_t at = __ballot(sc[ch] == low) & left[ch];
+            if (!found && at) {
+                found = true;
+                const int l = __builtin_ctzll(at);
+                slot = __builtin_amdgcn_readlane(slots[ch], l);
+                left[ch] &= ~(1ull << l);
+            }
+        }
+        if (lane == 0) sel[r] = (uint16_t)slot;
+        if (sel_out && lane == 0) sel_out[slot] = 1;
     }
     wave_sync_lds();
     return n_sel;
@@ -364,6 +381,43 @@ __device__ __forceinline__ uint64_t learned_best_move(const Bits &b, const int2 
     fallback = 1;
     return wave_best_move(b, row, T, pp, nb, list, false, nullptr, evals);
 }
+
+// The learned choice of interval pricing's VND (vns_interval.hpp): every move of the neighbourhood is priced already;
+// rank() marks the best-ranked ones by period, flips or zM swaps in keep[0], zR swaps in keep[1].
+struct LearnedChoice {
+    static constexpr bool kRanks = true;
+    const int2 *row;      // the product's rows (LDS)
+    int T;
+    const ProdParams &pp;
+    uint16_t *list;
+    LearnedLds L;
+    const mlp::Frags &fr;
+    int permille;
+
+    // how many of a neighbourhood's moves are ranked
+    __device__ __forceinline__ int count(int moves) const {
+        const int n = (permille * moves + 999) / 1000;
+        return moves <= 0 ? 0 : n < 1 ? 1 : n > moves ? moves : n;
+    }
+    template <int NV>
+    __device__ __forceinline__ int rank(const Bits &b, uint32_t nb, uint64_t (&keep)[2][NV]) const {
+        int nflip;
+        bool fm;
+        const int n = move_list(b, T, nb, list, nflip, fm);
+        const int n_sel = learned_select(b, row, T, pp, n, nflip, fm, list, L.sx, L.sel, fr, permille, nullptr, nullptr);
+        for (int r = 0; r < n_sel; ++r) {
+            const int slot = __builtin_amdgcn_readfirstlane((int)L.sel[r]);
+            const int blk = (slot >= T) + (slot >= 2 * T) + (slot >= 3 * T), t = slot - blk * T;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const uint64_t bit = t >> 6 == v ? 1ull << (t & 63) : 0ull;
+                keep[0][v] |= blk == 3 ? 0ull : bit;
+                keep[1][v] |= blk == 3 ? bit : 0ull;
+            }
+        }
+        return n_sel;
+    }
+};
 
 // ---------------------------------------------------------------------------------------------------
 // The learned VND of several products at once, by the workgroup's wavefronts together (packed form).  The
