@@ -71,6 +71,14 @@ __global__ __launch_bounds__(64) void k_mlp_score(const float *__restrict__ P, c
 // the wavefront's tiles; bias gradients as per-lane sums over rows, added across lanes at the end.
 constexpr int kGradLd = 64 + 8;   // padded row (bfloat16) of the transposed tiles: 16-byte reads stay aligned
 
+// Row r of a minibatch.  mul is little above 10^6, so the sum stays below 2^64 for any training set that fits memory,
+// and the 128-bit remainder (a long software division) is for larger ones only.
+__device__ __forceinline__ int64_t perm_row(const RowPerm &perm, int64_t r) {
+    const uint64_t i = (uint64_t)(perm.start + r), n = (uint64_t)perm.n;
+    if (n < (1ull << 31) && perm.mul < (1ull << 32)) return (int64_t)((perm.mul * i + perm.add) % n);
+    return (int64_t)(((unsigned __int128)perm.mul * i + perm.add) % n);
+}
+
 __global__ __launch_bounds__(64) void k_mlp_grad(const float *__restrict__ P, const float *__restrict__ X,
                                                  const float *__restrict__ y, const int64_t *__restrict__ idx,
                                                  RowPerm perm, int64_t n, float inv_n, float *__restrict__ part) {
@@ -109,8 +117,7 @@ __global__ __launch_bounds__(64) void k_mlp_grad(const float *__restrict__ P, co
         const bool in = r < n;
         const int64_t src = !in ? 0
                             : idx ? idx[r]
-                            : perm.n > 0 ? (int64_t)(((unsigned __int128)perm.mul * (uint64_t)(perm.start + r) + perm.add) %
-                                                     (uint64_t)perm.n)
+                            : perm.n > 0 ? perm_row(perm, r)
                                          : r;
         const float yl = in ? y[src] : 0.f;
         const float4 *xs = reinterpret_cast<const float4 *>(X + src * kF);
@@ -269,26 +276,40 @@ __global__ __launch_bounds__(64) void k_mlp_grad(const float *__restrict__ P, co
     }
 }
 
+// sum_b part[b][e] in the order of b.  The loads of 16 partials are in flight together: one at a time, the 64 of a
+// 4096-row minibatch were 64 memory latencies (16 us of a 37 us training step).
+__device__ __forceinline__ float sum_partials(const float *__restrict__ part, int64_t nb, int e) {
+    const float *p = part + e;
+    float acc = 0.f;
+    int64_t b = 0;
+    for (; b + 16 <= nb; b += 16) {
+        float v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = p[(b + i) * (kParams + 1)];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc += v[i];
+    }
+    for (; b < nb; ++b) acc += p[b * (kParams + 1)];
+    return acc;
+}
+
 // Fixed-order sum of the partial gradients of nb workgroups: out[e] = sum_b part[b][e].
-__global__ __launch_bounds__(256) void k_mlp_reduce(const float *__restrict__ part, int64_t nb, float *__restrict__ out) {
+__global__ __launch_bounds__(64) void k_mlp_reduce(const float *__restrict__ part, int64_t nb, float *__restrict__ out) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e > kParams) return;
-    float acc = 0.f;
-    for (int64_t b = 0; b < nb; ++b) acc += part[b * (kParams + 1) + e];
-    out[e] = acc;
+    out[e] = sum_partials(part, nb, e);
 }
 
 // The fixed-order sum of the partial gradients (as k_mlp_reduce) and the Adam step on each parameter, in one
 // pass: thread e sums parameter e's partials, stores the gradient (and the loss at e = kParams) and updates
 // the parameter and its moments.
-__global__ __launch_bounds__(256) void k_mlp_reduce_adam(const float *__restrict__ part, int64_t nb, float *__restrict__ out,
+__global__ __launch_bounds__(64) void k_mlp_reduce_adam(const float *__restrict__ part, int64_t nb, float *__restrict__ out,
                                                          float *__restrict__ P, float *__restrict__ m,
                                                          float *__restrict__ v, float lr, float beta1, float beta2,
                                                          float eps, float corr1, float corr2) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e > kParams) return;
-    float g = 0.f;
-    for (int64_t b = 0; b < nb; ++b) g += part[b * (kParams + 1) + e];
+    const float g = sum_partials(part, nb, e);
     out[e] = g;
     if (e == kParams) return;
     const float mm = beta1 * m[e] + (1.f - beta1) * g;
@@ -316,7 +337,7 @@ hipError_t launch_mlp_grad(const float *P, const float *X, const float *y, const
                        1.f / (float)n, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mlp::k_mlp_reduce, dim3((mlp::kParams + 1 + 255) / 256), dim3(256), 0, s, part, nb, grad_out);
+    hipLaunchKernelGGL(mlp::k_mlp_reduce, dim3((mlp::kParams + 1 + 63) / 64), dim3(64), 0, s, part, nb, grad_out);
     return hipGetLastError();
 }
 
@@ -332,7 +353,7 @@ hipError_t launch_mlp_train_step(float *P, float *m, float *v, const float *X, c
     if (e != hipSuccess) return e;
     const float b1 = 0.9f, b2 = 0.999f;
     const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
-    hipLaunchKernelGGL(mlp::k_mlp_reduce_adam, dim3((mlp::kParams + 1 + 255) / 256), dim3(256), 0, s, part, nb, grad_out,
+    hipLaunchKernelGGL(mlp::k_mlp_reduce_adam, dim3((mlp::kParams + 1 + 63) / 64), dim3(64), 0, s, part, nb, grad_out,
                        P, m, v, lr, b1, b2, 1e-8f, c1, c2);
     return hipGetLastError();
 }
