@@ -378,23 +378,22 @@ struct Pattern {
         int32_t PR, M1, XRn, Hn, Hm, j, w;
         bool m, r;
     };
-    __device__ __forceinline__ void next_of(const Masks<G, NV> &k, Next (&x)[NV]) const {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            const Period &q = p[v], &o = p[NV - 1];   // the second word's lane 0 follows lane 63
-            auto nx = [&](int32_t a, int32_t b) {
-                return next_lane(a, NV > 1 && v == 0 ? __builtin_amdgcn_readlane(b, 0) : 0);
-            };
-            x[v].PR = nx(q.PR, o.PR);
-            x[v].M1 = nx(q.M1, o.M1);
-            x[v].XRn = nx(q.XRn, o.XRn);
-            x[v].Hn = nx(q.Hn, o.Hn);
-            x[v].Hm = nx(q.Hm, o.Hm);
-            x[v].w = nx(q.w, o.w);
-            x[v].m = lane_bit<G>(next_bits<G, NV>(k.m, v));
-            x[v].r = lane_bit<G>(next_bits<G, NV>(k.r, v));
-            x[v].j = q.j + (x[v].r ? 1 : 0);
-        }
+    __device__ __forceinline__ Next next_of(const Masks<G, NV> &k, int v) const {
+        const Period &q = p[v], &o = p[NV - 1];   // the second word's lane 0 follows lane 63
+        auto nx = [&](int32_t a, int32_t b) {
+            return next_lane(a, NV > 1 && v == 0 ? __builtin_amdgcn_readlane(b, 0) : 0);
+        };
+        Next x;
+        x.PR = nx(q.PR, o.PR);
+        x.M1 = nx(q.M1, o.M1);
+        x.XRn = nx(q.XRn, o.XRn);
+        x.Hn = nx(q.Hn, o.Hn);
+        x.Hm = nx(q.Hm, o.Hm);
+        x.w = nx(q.w, o.w);
+        x.m = lane_bit<G>(next_bits<G, NV>(k.m, v));
+        x.r = lane_bit<G>(next_bits<G, NV>(k.r, v));
+        x.j = q.j + (x.r ? 1 : 0);
+        return x;
     }
 
     // Cost change of swapping zM(t), zM(t + 1), which differ.  e0, e1: more units remanufactured for period t and for
@@ -451,12 +450,13 @@ struct Pattern {
 };
 
 // The VND (Algorithm 1) of one product by one wavefront.  A neighbourhood is priced once per pattern: the pattern's
-// decode is built when a move has been applied, and a neighbourhood met again on the same pattern gives the best
-// move it gave before (it still counts its evaluations, as Algorithm 1 prices it in every pass).  now() is read before a
-// pricing and compared with `round` after it: false means the caller's round moved on and the product was given up.
-// ident: the pattern's own cost is not known yet; it is computed and returned in `start`.  x, x_cost: a pattern of the
-// product known to be a local optimum of this list, and its cost (with has_x): most shaken products return to it
-// (86 to 91% of single flips at T = 12..104), and no neighbourhood of it improves.
+// decode is built when a move has been applied, and a neighbourhood met again on the same pattern finds nothing again
+// (it still counts its evaluations, as Algorithm 1 prices it in every pass).  now() is read before a pricing and
+// compared with `round` after it: false means the caller's round moved on and the product was given up.
+// ident: the pattern's own cost is not known yet; the local optimum's is computed instead (x's is known) and the
+// pattern's follows from the moves applied.  x, x_cost: with has_x, a pattern of the product known to be a local optimum
+// of this list, and its cost: most shaken products return to it (86 to 91% of single flips at T = 12..104), and no
+// neighbourhood of it improves.
 // Choose: how a neighbourhood's move is chosen from the exact changes dx of its moves (NoChoice: the best one).  The
 // learned VND's choice ranks the moves by the scorer, takes the best of the best-ranked if it improves and the best of all
 // otherwise; it is handed the pattern and returns the changes of its ranked moves alone.
@@ -504,176 +504,173 @@ __device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, Row row_at, int
         }
         return o;
     };
-    // per neighbourhood (0 flip zM, 1 flip zR, 2 shift), wavefront-uniform: best change, its slot, moves
-    int32_t best[3] = {0, 0, 0}, slot[3] = {0, 0, 0}, cnt[3] = {0, 0, 0};
-    uint32_t known = 0, clean = 0;
-    // nothing improves on x: count what is left of this pass after neighbourhood q, and the pass that finds nothing (with
-    // the memo, which skips what this pass has priced on x, its neighbourhoods up to q)
-    auto count_x = [&](int q, bool another) {
+    auto shifts = [&]() {
         int n = 0;
 #pragma unroll
         for (int v = 0; v < NV; ++v) n += __popcll(swap_bits<64, NV>(k.m, v, T)) + __popcll(swap_bits<64, NV>(k.r, v, T));
-        int sum = 0, ranked = 0, whole = 0;
-        for (int i = 0; i < n_nb; ++i) {
-            const int moves = ((nb_list >> (4 * i)) & 4u) ? n : T;
-            const int times = (i > q ? 1 : 0) + (another && !(memo && i > q) ? 1 : 0);
-            sum += (moves + choose.count(moves)) * times;
-            ranked += times;
-            whole += moves > 0 ? times : 0;
-        }
-        s.evals += sum;
+        return n;
+    };
+    // counts the neighbourhoods in `list` (one id per nibble: 1, 2 or 4) as priced without an improving move
+    auto count = [&](uint32_t list, int n_shift) {
+        const int flips = __popc(list & 0x3333u), shift = __popc(list & 0x4444u);
+        s.evals += flips * (T + choose.count(T)) + shift * (n_shift + choose.count(n_shift));
         if constexpr (Choose::kRanks) {
-            s.ranked += ranked;
-            s.fallbacks += whole;
+            s.ranked += flips + shift;
+            s.fallbacks += flips + (n_shift > 0 ? shift : 0);
         }
     };
-    Pattern<64, NV, STRICT> pat;
-    int32_t cost = (int32_t)s.cost;
     s.err = 0;
-    if (at_x()) {   // the shake undid itself
-        count_x(-1, false);
+    s.start = s.cost;
+    if (at_x()) {   // the shake undid itself: one pass finds nothing
+        count(nb_list, shifts());
         s.start = s.cost = x_cost;
         return true;
     }
-    pat.build(k, row, T, c, sh);
-    if (ident) {
+    Pattern<64, NV, STRICT> pat;
+    int32_t gain = 0;                  // cost change of the moves applied
+    int q = 0, passes = 1;             // place in the list, pass
+    bool improved = false, alive = true, back = false;
+    for (;;) {   // one pattern
+        pat.build(k, row, T, c, sh);
+        uint32_t priced = 0, clean = 0;   // ids priced on this pattern, and list places passed on it, without improving
+        int n_shift = 0;                  // the pattern's shifts, once priced
+        int32_t best = 0;
+        uint32_t nb = 0;
+        int32_t dx[2][NV];   // changes of the flips or zM swaps, and of the zR swaps
+        for (;;) {
+            if (q == n_nb) {   // the pass is over
+                if (!improved) break;
+                if (++passes > kMaxPasses) {
+                    s.err = 1;
+                    break;
+                }
+                improved = false;
+                q = 0;
+            }
+            if (memo && ((clean >> q) & 1u)) {   // same pattern: nothing to find
+                ++q;
+                continue;
+            }
+            nb = (nb_list >> (4 * q)) & 0xFu;
+            if (priced & nb) {
+                count(nb, n_shift);
+                clean |= 1u << q++;
+                continue;
+            }
+            const int32_t seen = now();
+            int steps = 0, n = T;
+            if (nb == 1u) {
+#pragma unroll
+                for (int v = 0; v < NV; ++v) dx[0][v] = lane + 64 * v < T ? pat.flip_m(pat.p[v], c, steps) : kBad32;
+            } else if (nb == 2u) {
+#pragma unroll
+                for (int v = 0; v < NV; ++v) dx[0][v] = lane + 64 * v < T ? pat.flip_r(pat.p[v], c, steps) : kBad32;
+            } else {
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    const typename Pattern<64, NV, STRICT>::Next nx = pat.next_of(k, v);
+                    const bool sm = lane_bit<64>(swap_bits<64, NV>(k.m, v, T)), sr = lane_bit<64>(swap_bits<64, NV>(k.r, v, T));
+                    const int32_t y = pat.swap_m(pat.p[v], nx, c, sm, steps);
+                    const int32_t z = pat.swap_r(pat.p[v], nx, c, sr, steps);
+                    dx[0][v] = sm ? y : kBad32;
+                    dx[1][v] = sr ? z : kBad32;
+                }
+                n = n_shift = shifts();
+            }
+            if constexpr (Choose::kRanks) {
+                // the best-ranked moves; if none of them improves, all of them (priced already)
+                uint64_t keep[2][NV] = {};
+                ++s.ranked;
+                if (n > 0) {
+                    const int counted = choose.rank(pack(k), nb, keep);
+                    bool better = false;
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) {
+                        better |= (__ballot(dx[0][v] < 0) & keep[0][v]) != 0;
+                        if (nb == 4u) better |= (__ballot(dx[1][v] < 0) & keep[1][v]) != 0;
+                    }
+                    if (better) {
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) {
+                            dx[0][v] = lane_bit<64>(keep[0][v]) ? dx[0][v] : kBad32;
+                            dx[1][v] = lane_bit<64>(keep[1][v]) ? dx[1][v] : kBad32;
+                        }
+                        n = counted;
+                    } else {
+                        ++s.fallbacks;
+                        n += counted;
+                    }
+                }
+            }
+            s.evals += n;
+            if (__builtin_amdgcn_readfirstlane(seen) != round) {
+                alive = false;
+                break;
+            }
+            // the lowest (cost, slot), as the sweep finds it
+            uint32_t low = 0;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                low = max(low, ~((uint32_t)dx[0][v] ^ 0x80000000u));
+                if (nb == 4u) low = max(low, ~((uint32_t)dx[1][v] ^ 0x80000000u));
+            }
+            best = (int32_t)(~(uint32_t)last_lane(scan_max<64>(low)) ^ 0x80000000u);
+            if (best < 0) break;
+            priced |= nb;
+            clean |= 1u << q++;
+        }
+        if (best >= 0 || !alive) break;   // a local optimum (or given up)
+        // apply it: a flip, or a swap, zM's before zR's
+        bool on_r = nb == 2u;
+        int t = -1;
+#pragma unroll
+        for (int v = NV - 1; v >= 0; --v) {
+            const uint64_t w = __ballot(dx[0][v] == best);
+            t = w ? 64 * v + (int)__builtin_ctzll(w) : t;
+        }
+        if (nb == 4u && t < 0) {
+            on_r = true;
+#pragma unroll
+            for (int v = NV - 1; v >= 0; --v) {
+                const uint64_t w = __ballot(dx[1][v] == best);
+                t = w ? 64 * v + (int)__builtin_ctzll(w) : t;
+            }
+        }
+        const uint64_t w = nb == 4u ? 3ull : 1ull;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const uint64_t y = t >> 6 == v ? w << (t & 63) : v == 1 && t == 63 ? w >> 1 : 0ull;   // 63 reaches the next word
+            k.m[v] ^= on_r ? 0ull : y;
+            k.r[v] ^= on_r ? y : 0ull;
+        }
+        gain += best;
+        improved = true;
+        ++q;
+        if (at_x()) {
+            // nothing improves on x: the rest of this pass, and the pass that finds nothing (with the memo, which skips what
+            // this pass has passed on x, only its places up to the move's)
+            const int m = shifts();
+            count(nb_list, m);
+            if (!memo && q < n_nb) count(nb_list >> (4 * q), m);
+            back = true;
+            break;
+        }
+    }
+    if (back) {
+        s.cost = x_cost;
+    } else if (ident) {
         int nM = 0, nR = 0;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             nM += __popcll(k.m[v]);
             nR += __popcll(k.r[v]);
         }
-        cost = (int32_t)((uint32_t)pp.C + (uint32_t)pat.own_cost(c) + (uint32_t)c.kM * (uint32_t)nM +
-                         (uint32_t)c.kR * (uint32_t)nR);
+        s.cost = (int32_t)((uint32_t)pp.C + (uint32_t)pat.own_cost(c) + (uint32_t)c.kM * (uint32_t)nM + (uint32_t)c.kR * (uint32_t)nR);
+    } else {
+        s.cost += gain;
     }
-    s.start = cost;
-    bool improved = true, alive = true;
-    for (int passes = 1; improved && alive; ++passes) {
-        if (passes > kMaxPasses) {
-            s.err = 1;
-            break;
-        }
-        improved = false;
-        for (int q = 0; q < n_nb; ++q) {
-            if (memo && ((clean >> q) & 1u)) continue;   // same pattern: nothing to find
-            const uint32_t nb = (nb_list >> (4 * q)) & 0xFu;
-            const int i = nb == 1u ? 0 : nb == 2u ? 1 : 2;
-            if (!((known >> i) & 1u)) {
-                const int32_t seen = now();
-                int32_t dx[2][NV];
-                int steps = 0, n = T;
-                if (i == 0) {
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) dx[0][v] = lane + 64 * v < T ? pat.flip_m(pat.p[v], c, steps) : kBad32;
-                } else if (i == 1) {
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) dx[0][v] = lane + 64 * v < T ? pat.flip_r(pat.p[v], c, steps) : kBad32;
-                } else {
-                    typename Pattern<64, NV, STRICT>::Next nx[NV];
-                    pat.next_of(k, nx);
-                    n = 0;
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        const uint64_t vm = swap_bits<64, NV>(k.m, v, T), vr = swap_bits<64, NV>(k.r, v, T);
-                        const bool sm = lane_bit<64>(vm), sr = lane_bit<64>(vr);
-                        const int32_t y = pat.swap_m(pat.p[v], nx[v], c, sm, steps);
-                        const int32_t z = pat.swap_r(pat.p[v], nx[v], c, sr, steps);
-                        dx[0][v] = sm ? y : kBad32;
-                        dx[1][v] = sr ? z : kBad32;
-                        n += __popcll(vm) + __popcll(vr);
-                    }
-                }
-                if constexpr (Choose::kRanks) {
-                    // the best-ranked moves; if none of them improves, all of them (priced already)
-                    uint64_t keep[2][NV] = {};
-                    int counted = 0;
-                    ++s.ranked;
-                    if (n > 0) {
-                        counted = choose.rank(pack(k), nb, keep);
-                        bool better = false;
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) {
-                            better |= (__ballot(dx[0][v] < 0) & keep[0][v]) != 0;
-                            if (i == 2) better |= (__ballot(dx[1][v] < 0) & keep[1][v]) != 0;
-                        }
-                        if (better) {
-#pragma unroll
-                            for (int v = 0; v < NV; ++v) {
-                                dx[0][v] = lane_bit<64>(keep[0][v]) ? dx[0][v] : kBad32;
-                                dx[1][v] = lane_bit<64>(keep[1][v]) ? dx[1][v] : kBad32;
-                            }
-                            n = counted;
-                        } else {
-                            ++s.fallbacks;
-                            n += counted;
-                        }
-                    }
-                }
-                // the lowest (cost, slot), as the sweep finds it
-                uint32_t low = 0;
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    low = max(low, ~((uint32_t)dx[0][v] ^ 0x80000000u));
-                    if (i == 2) low = max(low, ~((uint32_t)dx[1][v] ^ 0x80000000u));
-                }
-                const int32_t bx = (int32_t)(~(uint32_t)last_lane(scan_max<64>(low)) ^ 0x80000000u);
-                int at = 0;
-                if (i == 2) {
-#pragma unroll
-                    for (int v = NV - 1; v >= 0; --v) {
-                        const uint64_t w = __ballot(dx[1][v] == bx);
-                        at = w ? 3 * T + 64 * v + __builtin_ctzll(w) : at;
-                    }
-                }
-                const int off = i * T;
-#pragma unroll
-                for (int v = NV - 1; v >= 0; --v) {
-                    const uint64_t w = __ballot(dx[0][v] == bx);
-                    at = w ? off + 64 * v + __builtin_ctzll(w) : at;
-                }
-                if (i == 0) { best[0] = bx; slot[0] = at; cnt[0] = n; }
-                if (i == 1) { best[1] = bx; slot[1] = at; cnt[1] = n; }
-                if (i == 2) { best[2] = bx; slot[2] = at; cnt[2] = n; }
-                known |= 1u << i;
-                if (__builtin_amdgcn_readfirstlane(seen) != round) {
-                    alive = false;
-                    break;
-                }
-            } else if constexpr (Choose::kRanks) {
-                ++s.ranked;   // priced before on this pattern without an improving move
-                s.fallbacks += (i == 2 ? cnt[2] : T) > 0 ? 1 : 0;
-            }
-            const int32_t bx = i == 0 ? best[0] : i == 1 ? best[1] : best[2];
-            s.evals += i == 0 ? cnt[0] : i == 1 ? cnt[1] : cnt[2];
-            if (bx < 0) {
-                const int l = i == 0 ? slot[0] : i == 1 ? slot[1] : slot[2];
-                const int blk = (l >= T) + (l >= 2 * T) + (l >= 3 * T), t = l - blk * T;
-                const uint64_t w = blk >= 2 ? 3ull : 1ull;
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    uint64_t y = 0;
-                    if (t >> 6 == v) y = w << (t & 63);
-                    else if (v == 1 && t == 63) y = w >> 1;   // a swap of periods 63, 64
-                    if (blk & 1) k.r[v] ^= y;
-                    else k.m[v] ^= y;
-                }
-                cost += bx;
-                improved = true;
-                known = 0;
-                clean = 0;
-                if (at_x()) {
-                    count_x(q, true);
-                    improved = false;   // the passes are done
-                    break;
-                }
-                pat.build(k, row, T, c, sh);
-            } else {
-                clean |= 1u << q;
-            }
-        }
-    }
+    if (ident) s.start = s.cost - gain;
     b = pack(k);
-    s.cost = cost;
     return alive;
 }
 

@@ -483,8 +483,6 @@ __device__ __forceinline__ void eval_unit(const EvalArgs &a, const ChainInfo &ci
     iv::Word<G> vm[NV], vr[NV];
     int steps = 0;
     uint32_t n = (fm ? T : 0) + (fr ? T : 0);
-    typename iv::Pattern<G, NV, STRICT>::Next nx[NV];
-    if (shift) pat.next_of(k, nx);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
         const iv::Period &q = pat.p[v];
@@ -502,7 +500,8 @@ __device__ __forceinline__ void eval_unit(const EvalArgs &a, const ChainInfo &ci
             vm[v] = iv::swap_bits<G, NV>(k.m, v, T);
             vr[v] = iv::swap_bits<G, NV>(k.r, v, T);
             const bool sm = iv::lane_bit<G>(vm[v]), sr = iv::lane_bit<G>(vr[v]);
-            const int32_t y = pat.swap_m(q, nx[v], c, sm, steps), z = pat.swap_r(q, nx[v], c, sr, steps);
+            const typename iv::Pattern<G, NV, STRICT>::Next nx = pat.next_of(k, v);
+            const int32_t y = pat.swap_m(q, nx, c, sm, steps), z = pat.swap_r(q, nx, c, sr, steps);
             x[2][v] = sm ? y : kBad32;
             x[3][v] = sr ? z : kBad32;
             n += G < 64 ? __popc((uint32_t)vm[v]) + __popc((uint32_t)vr[v]) : __popcll(vm[v]) + __popcll(vr[v]);
@@ -749,6 +748,31 @@ struct SpecShared {
     int32_t next;         // next product index to hand out
 };
 
+// A value in LDS, through pointers that say so.  (Two accesses of one branch each, to LDS and to device memory through
+// generic pointers, are merged into one flat access before their address spaces are known.)
+template <class T>
+__device__ __forceinline__ T lds_load(const T *p) {
+    static_assert(sizeof(T) % 8 == 0, "8-byte words");
+    typedef const __attribute__((address_space(3))) uint64_t *Words;
+    const Words w = (Words)p;
+    uint64_t r[sizeof(T) / 8];
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 8; ++i) r[i] = w[i];
+    T out;
+    __builtin_memcpy(&out, r, sizeof(T));
+    return out;
+}
+template <class T>
+__device__ __forceinline__ void lds_store(T *p, const T &v) {
+    static_assert(sizeof(T) % 8 == 0, "8-byte words");
+    typedef __attribute__((address_space(3))) uint64_t *Words;
+    const Words w = (Words)p;
+    uint64_t r[sizeof(T) / 8];
+    __builtin_memcpy(r, &v, sizeof(T));
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 8; ++i) w[i] = r[i];
+}
+
 // The flip of draw j (< kmax) of iteration it, as product << 8 | its flip slot (K <= 2^20, 2T <= 256).
 __device__ __forceinline__ uint32_t shake_flip(const RunArgs &a, int g, int64_t it, uint64_t stream, int j, uint64_t n, int T) {
     if (j >= a.kmax) return 0u;
@@ -824,17 +848,17 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
         __syncthreads();
     }
     auto cur_bits = [&](int p) -> Bits {
-        if (st_lds) return l_cur[p];
+        if (st_lds) return lds_load(l_cur + p);
         return g_cur[p];
     };
     auto cur_cost = [&](int p) -> int64_t {
-        if (st_lds) return l_cur_cost[p];
+        if (st_lds) return lds_load(l_cur_cost + p);
         return g_cur_cost[p];
     };
     auto set_work = [&](int p, const Bits &b, int64_t cost) {
         if (st_lds) {
-            l_work[p] = b;
-            l_work_cost[p] = cost;
+            lds_store(l_work + p, b);
+            lds_store(l_work_cost + p, cost);
         } else {
             g_work[p] = b;
             g_work_cost[p] = cost;
@@ -1171,7 +1195,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                 }
             } else {
             for (int idx = vfirst; idx < nprod && !stale;
-                 idx = dyn ? __builtin_amdgcn_readfirstlane(next_index(sh.next_prod, lane)) : idx + vstep) {
+                 idx = !dyn ? idx + vstep : nprod <= W ? nprod : __builtin_amdgcn_readfirstlane(next_index(sh.next_prod, lane))) {
                 int p, e = -1;
                 if (cs.lopt) {
                     p = sh.dp[idx];
@@ -1198,7 +1222,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                     };
                     constexpr bool kStrict = (MODEL & kModelStrict) != 0;
                     auto row_at = [&](int t) -> int2 {
-                        if (rows_in_lds) return s_rows[p * T + t];
+                        if (rows_in_lds) return lds_load(s_rows + p * T + t);
                         return inst_rows[p * T + t];
                     };
                     bool done;
@@ -1588,12 +1612,13 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
             const int p = few ? sh.dp[idx] : idx;
             if (st_lds) {
                 if (accepted) {
-                    l_cur[p] = l_work[p];
-                    l_cur_cost[p] = l_work_cost[p];
-                    if (bmode == 1) a.best[cp0 + p] = l_work[p];
+                    const Bits b = lds_load(l_work + p);
+                    lds_store(l_cur + p, b);
+                    lds_store(l_cur_cost + p, lds_load(l_work_cost + p));
+                    if (bmode == 1) a.best[cp0 + p] = b;
                 } else {
-                    l_work[p] = l_cur[p];
-                    l_work_cost[p] = l_cur_cost[p];
+                    lds_store(l_work + p, lds_load(l_cur + p));
+                    lds_store(l_work_cost + p, lds_load(l_cur_cost + p));
                 }
             } else if (accepted) {
                 g_cur[p] = g_work[p];
