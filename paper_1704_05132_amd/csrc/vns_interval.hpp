@@ -146,6 +146,9 @@ __device__ __forceinline__ Word<G> swap_bits(const Word<G> (&z)[NV], int v, int 
     return (z[v] ^ next_bits<G, NV>(z, v)) & keep;
 }
 
+// The n lowest bits (n <= 64, none below 1).
+__device__ __forceinline__ uint64_t first_bits(int n) { return n <= 0 ? 0ull : n >= 64 ? ~0ull : ~(~0ull << n); }
+
 // LDS of one wavefront: per group, pos[k] = (XR, H) before period k, H the units manufactured (the demand before k
 // less XR), and the remanufacturing setups' records with kWalk that end every walk.
 constexpr int kWalk = 4;   // records a walk takes per round: their reads are in flight together
@@ -457,9 +460,8 @@ struct Pattern {
 // pattern's follows from the moves applied.  x, x_cost: with has_x, a pattern of the product known to be a local optimum
 // of this list, and its cost: most shaken products return to it (86 to 91% of single flips at T = 12..104), and no
 // neighbourhood of it improves.
-// Choose: how a neighbourhood's move is chosen from the exact changes dx of its moves (NoChoice: the best one).  The
-// learned VND's choice ranks the moves by the scorer, takes the best of the best-ranked if it improves and the best of all
-// otherwise; it is handed the pattern and returns the changes of its ranked moves alone.
+// Choose: NoChoice takes a neighbourhood's best move; the learned VND's choice (kRanks) gives the moves' scores, and takes
+// the best of the best-ranked if it improves and the best of all otherwise.
 struct NoChoice {
     static constexpr bool kRanks = false;
     __device__ __forceinline__ int count(int) const { return 0; }   // moves ranked of a neighbourhood's
@@ -537,6 +539,24 @@ __device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, Row row_at, int
         int32_t best = 0;
         uint32_t nb = 0;
         int32_t dx[2][NV];   // changes of the flips or zM swaps, and of the zR swaps
+        // the lowest slot whose change in x is x0: zR swap, period
+        auto place = [&](const int32_t (&x)[2][NV], int32_t x0, int &z, int &t) {
+            z = 0;
+            t = -1;
+#pragma unroll
+            for (int v = NV - 1; v >= 0; --v) {
+                const uint64_t w = __ballot(x[0][v] == x0);
+                t = w ? 64 * v + (int)__builtin_ctzll(w) : t;
+            }
+            if (nb == 4u && t < 0) {
+                z = 1;
+#pragma unroll
+                for (int v = NV - 1; v >= 0; --v) {
+                    const uint64_t w = __ballot(x[1][v] == x0);
+                    t = w ? 64 * v + (int)__builtin_ctzll(w) : t;
+                }
+            }
+        };
         for (;;) {
             if (q == n_nb) {   // the pass is over
                 if (!improved) break;
@@ -577,65 +597,89 @@ __device__ __forceinline__ bool vnd(Bits &b, Vnd &s, bool ident, Row row_at, int
                 }
                 n = n_shift = shifts();
             }
-            if constexpr (Choose::kRanks) {
-                // the best-ranked moves; if none of them improves, all of them (priced already)
-                uint64_t keep[2][NV] = {};
-                ++s.ranked;
-                if (n > 0) {
-                    const int counted = choose.rank(pack(k), nb, keep);
-                    bool better = false;
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        better |= (__ballot(dx[0][v] < 0) & keep[0][v]) != 0;
-                        if (nb == 4u) better |= (__ballot(dx[1][v] < 0) & keep[1][v]) != 0;
-                    }
-                    if (better) {
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) {
-                            dx[0][v] = lane_bit<64>(keep[0][v]) ? dx[0][v] : kBad32;
-                            dx[1][v] = lane_bit<64>(keep[1][v]) ? dx[1][v] : kBad32;
-                        }
-                        n = counted;
-                    } else {
-                        ++s.fallbacks;
-                        n += counted;
-                    }
-                }
-            }
-            s.evals += n;
             if (__builtin_amdgcn_readfirstlane(seen) != round) {
                 alive = false;
                 break;
             }
-            // the lowest (cost, slot), as the sweep finds it
-            uint32_t low = 0;
+            // the lowest change, as the sweep finds it
+            auto lowest = [&](const int32_t (&x)[2][NV]) {
+                uint32_t low = 0;
 #pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                low = max(low, ~((uint32_t)dx[0][v] ^ 0x80000000u));
-                if (nb == 4u) low = max(low, ~((uint32_t)dx[1][v] ^ 0x80000000u));
+                for (int v = 0; v < NV; ++v) {
+                    low = max(low, ~((uint32_t)x[0][v] ^ 0x80000000u));
+                    if (nb == 4u) low = max(low, ~((uint32_t)x[1][v] ^ 0x80000000u));
+                }
+                return (int32_t)(~(uint32_t)last_lane(scan_max<64>(low)) ^ 0x80000000u);
+            };
+            best = lowest(dx);
+            if constexpr (Choose::kRanks) {
+                const int n_sel = choose.count(n);
+                ++s.ranked;
+                bool whole = n > 0;   // the neighbourhood was priced whole
+                if (best < 0) {
+                    // The choice is the best improving move among the n_sel best-ranked, or the best of all if none of them
+                    // improves.  So scores are needed only when a move improves, and then the improving moves are tried
+                    // in the order of their prices: the first with fewer than n_sel moves ranked before it is the choice.
+                    uint32_t sc[2][NV];
+                    uint64_t is[2][NV];   // the moves by period: flips or zM swaps, and zR swaps
+                    int32_t left[2][NV];  // the changes of those not tried yet
+                    const Bits pb = pack(k);
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) {
+                        is[0][v] = nb == 4u ? swap_bits<64, NV>(k.m, v, T) : first_bits(T - 64 * v);
+                        is[1][v] = nb == 4u ? swap_bits<64, NV>(k.r, v, T) : 0ull;
+                        sc[0][v] = choose.score(pb, nb == 4u ? 2 : nb == 2u ? 1 : 0, lane + 64 * v, lane_bit<64>(is[0][v]));
+                        sc[1][v] = nb == 4u ? choose.score(pb, 3, lane + 64 * v, lane_bit<64>(is[1][v])) : 0u;
+                        left[0][v] = dx[0][v];
+                        left[1][v] = nb == 4u ? dx[1][v] : kBad32;
+                    }
+                    for (int32_t x0 = best; x0 < 0; x0 = lowest(left)) {
+                        int z, t;
+                        place(left, x0, z, t);
+                        uint32_t mine = 0;   // its score
+#pragma unroll
+                        for (int v = 0; v < NV; ++v)
+                            if (t >> 6 == v) mine = (uint32_t)__builtin_amdgcn_readlane((int)(z ? sc[1][v] : sc[0][v]), t & 63);
+                        int before = 0;
+#pragma unroll
+                        for (int v = 0; v < NV; ++v)
+#pragma unroll
+                            for (int y = 0; y < 2; ++y) {
+                                // of equal scores the lower slots
+                                const uint64_t lower = y < z || (y == z && v < t >> 6) ? ~0ull : y == z && v == t >> 6 ? (1ull << (t & 63)) - 1 : 0ull;
+                                before += __popcll((__ballot(sc[y][v] < mine) | (__ballot(sc[y][v] == mine) & lower)) & is[y][v]);
+                            }
+                        if (before < n_sel) {
+                            // the choice: what improves more was not among the best-ranked
+                            best = x0;
+#pragma unroll
+                            for (int v = 0; v < NV; ++v) {
+                                dx[0][v] = left[0][v];
+                                dx[1][v] = left[1][v];
+                            }
+                            whole = false;
+                            break;
+                        }
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) {
+                            const bool here = lane + 64 * v == t;
+                            left[0][v] = here && !z ? kBad32 : left[0][v];
+                            left[1][v] = here && z ? kBad32 : left[1][v];
+                        }
+                    }
+                }
+                s.fallbacks += whole ? 1 : 0;
+                n = n_sel + (whole ? n : 0);
             }
-            best = (int32_t)(~(uint32_t)last_lane(scan_max<64>(low)) ^ 0x80000000u);
+            s.evals += n;
             if (best < 0) break;
             priced |= nb;
             clean |= 1u << q++;
         }
         if (best >= 0 || !alive) break;   // a local optimum (or given up)
-        // apply it: a flip, or a swap, zM's before zR's
-        bool on_r = nb == 2u;
-        int t = -1;
-#pragma unroll
-        for (int v = NV - 1; v >= 0; --v) {
-            const uint64_t w = __ballot(dx[0][v] == best);
-            t = w ? 64 * v + (int)__builtin_ctzll(w) : t;
-        }
-        if (nb == 4u && t < 0) {
-            on_r = true;
-#pragma unroll
-            for (int v = NV - 1; v >= 0; --v) {
-                const uint64_t w = __ballot(dx[1][v] == best);
-                t = w ? 64 * v + (int)__builtin_ctzll(w) : t;
-            }
-        }
+        int at_z, t;
+        place(dx, best, at_z, t);
+        const bool on_r = nb == 2u || at_z;
         const uint64_t w = nb == 4u ? 3ull : 1ull;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {

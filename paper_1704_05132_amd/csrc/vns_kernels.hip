@@ -1242,7 +1242,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                             wave_sync_lds();
                             row = slice;
                         }
-                        LearnedChoice choose{row, T, pp, lists[wave], L, fr, a.permille};
+                        LearnedChoice choose{row, T, pp, L.sx, fr, a.permille};
                         vnd(choose);
                         nb_evals += vs.ranked;
                         fallbacks += vs.fallbacks;

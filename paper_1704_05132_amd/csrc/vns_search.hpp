@@ -382,40 +382,32 @@ __device__ __forceinline__ uint64_t learned_best_move(const Bits &b, const int2 
     return wave_best_move(b, row, T, pp, nb, list, false, nullptr, evals);
 }
 
-// The learned choice of interval pricing's VND (vns_interval.hpp): every move of the neighbourhood is priced already;
-// rank() marks the best-ranked ones by period, flips or zM swaps in keep[0], zR swaps in keep[1].
+// The learned choice of interval pricing's VND (vns_interval.hpp), where every move of the neighbourhood is priced.
 struct LearnedChoice {
     static constexpr bool kRanks = true;
     const int2 *row;      // the product's rows (LDS)
     int T;
     const ProdParams &pp;
-    uint16_t *list;
-    LearnedLds L;
+    __bf16 *sx;           // this wavefront's feature tile
     const mlp::Frags &fr;
     int permille;
 
-    // how many of a neighbourhood's moves are ranked
+    // how many of a neighbourhood's moves are taken as best-ranked
     __device__ __forceinline__ int count(int moves) const {
         const int n = (permille * moves + 999) / 1000;
         return moves <= 0 ? 0 : n < 1 ? 1 : n > moves ? moves : n;
     }
-    template <int NV>
-    __device__ __forceinline__ int rank(const Bits &b, uint32_t nb, uint64_t (&keep)[2][NV]) const {
-        int nflip;
-        bool fm;
-        const int n = move_list(b, T, nb, list, nflip, fm);
-        const int n_sel = learned_select(b, row, T, pp, n, nflip, fm, list, L.sx, L.sel, fr, permille, nullptr, nullptr);
-        for (int r = 0; r < n_sel; ++r) {
-            const int slot = __builtin_amdgcn_readfirstlane((int)L.sel[r]);
-            const int blk = (slot >= T) + (slot >= 2 * T) + (slot >= 3 * T), t = slot - blk * T;
+    // The score of each lane's move (slot block, period t; lanes that hold one), as an order-preserving integer.
+    __device__ __forceinline__ uint32_t score(const Bits &b, int block, int t, bool is) const {
+        const int lane = threadIdx.x & 63;
+        float f[mlp::kF];
 #pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                const uint64_t bit = t >> 6 == v ? 1ull << (t & 63) : 0ull;
-                keep[0][v] |= blk == 3 ? 0ull : bit;
-                keep[1][v] |= blk == 3 ? bit : 0ull;
-            }
-        }
-        return n_sel;
+        for (int i = 0; i < mlp::kF; ++i) f[i] = 0.f;
+        if (is) mlp::move_features(b, row, T, pp, block * T + t, f);
+#pragma unroll
+        for (int i = 0; i < mlp::kF; ++i) sx[lane * mlp::kF + i] = (__bf16)f[i];
+        wave_sync_lds();
+        return mlp::sortable(mlp::forward64(sx, fr));
     }
 };
 
