@@ -69,7 +69,50 @@ __global__ __launch_bounds__(64) void k_mlp_score(const float *__restrict__ P, c
 // layer inputs and deltas go to LDS transposed (unit-major, rows contiguous), so that dW2 = sum over rows of
 // h1 dz2^T and dW1 = x dz1^T are products with the rows as K.  Weight gradients accumulate in registers over
 // the wavefront's tiles; bias gradients as per-lane sums over rows, added across lanes at the end.
+// The sum over each 16 lanes, valid in their first one: pairs, quads, halves, in the order of a butterfly, by lane
+// permutations within the row (through 64-bit shuffles the 48 sums were 192 LDS round trips, half of a one-tile launch).
+template <int CTRL>
+__device__ __forceinline__ float row_lane(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float sum16(float x) {
+    x += row_lane<0xB1>(x);    // lane ^ 1
+    x += row_lane<0x4E>(x);    // lane ^ 2
+    x += row_lane<0x104>(x);   // lane + 4
+    x += row_lane<0x108>(x);   // lane + 8
+    return x;
+}
+
 constexpr int kGradLd = 64 + 8;   // padded row (bfloat16) of the transposed tiles: 16-byte reads stay aligned
+
+// The gradient kernel's weight fragments, laid out as its lanes hold them (bfloat16, 16 bytes per lane and fragment):
+// w1t[mt], w2t[mt][kt] as in Frags, then w2b[mi][kt], the A fragments of W2 for W2 dz2.  Gathered from the parameters they
+// were 96 strided loads per lane, a few at a time between the registers' other uses, and most of a one-tile launch.
+constexpr int kPkW2t = 4 * 512, kPkW2b = kPkW2t + 8 * 512;
+static_assert(kPkW2b + 8 * 512 == kPackedWeights, "packed weights");
+
+// Writes parameter e's value to its places.
+__device__ __forceinline__ void put_packed(__bf16 *pk, int e, float v) {
+    const __bf16 b = (__bf16)v;
+    if (e < oB1) {
+        const int k = e >> 6, o = e & 63;
+        pk[((o >> 4) * 64 + (k >> 3) * 16 + (o & 15)) * 8 + (k & 7)] = b;
+    } else if (e >= oW2 && e < oB2) {
+        const int i = (e - oW2) >> 6, o = (e - oW2) & 63;   // input i, output o
+        auto slot = [](int row, int in) {   // row 16 m + c, inputs in the order pi
+            return (((row >> 4) * 2 + (in >> 5)) * 64 + ((in >> 2) & 3) * 16 + (row & 15)) * 8 + ((in >> 4) & 1) * 4 + (in & 3);
+        };
+        pk[kPkW2t + slot(o, i)] = b;
+        pk[kPkW2b + slot(i, o)] = b;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_mlp_pack(const float *__restrict__ P, __bf16 *__restrict__ pk) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < kParams) put_packed(pk, e, P[e]);
+    // features 16 and up (lane groups 2, 3 of w1t) are zero
+    if (e < 4 * 32 * 8) pk[((e >> 8) * 64 + 32) * 8 + (e & 255)] = (__bf16)0.f;
+}
 
 // Row r of a minibatch.  mul is little above 10^6, so the sum stays below 2^64 for any training set that fits memory,
 // and the 128-bit remainder (a long software division) is for larger ones only.
@@ -79,7 +122,8 @@ __device__ __forceinline__ int64_t perm_row(const RowPerm &perm, int64_t r) {
     return (int64_t)(((unsigned __int128)perm.mul * i + perm.add) % n);
 }
 
-__global__ __launch_bounds__(64) void k_mlp_grad(const float *__restrict__ P, const float *__restrict__ X,
+__global__ __launch_bounds__(64) void k_mlp_grad(const float *__restrict__ P, const __bf16 *__restrict__ pk,
+                                                 const float *__restrict__ X,
                                                  const float *__restrict__ y, const int64_t *__restrict__ idx,
                                                  RowPerm perm, int64_t n, float inv_n, float *__restrict__ part) {
     __shared__ __attribute__((aligned(16))) __bf16 sx[64 * kF];        // [row][feature]: forward input
@@ -89,15 +133,23 @@ __global__ __launch_bounds__(64) void k_mlp_grad(const float *__restrict__ P, co
     __shared__ __attribute__((aligned(16))) __bf16 d1T[kH * kGradLd];  // [unit][row]: dz1
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     Frags fr;
-    load_frags(P, fr);
     bf8 w2b[4][2];   // A fragments of W2 for W2 dz2: rows i = 16 mi + c, inputs j in the order pi(kt, 8g + e)
+    const bf8 *pf = reinterpret_cast<const bf8 *>(pk) + lane;
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
+    for (int mt = 0; mt < 4; ++mt) {
+        fr.w1t[mt] = pf[mt * 64];
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
+        for (int kt = 0; kt < 2; ++kt) {
+            fr.w2t[mt][kt] = pf[(kPkW2t / 8) + (mt * 2 + kt) * 64];
+            w2b[mt][kt] = pf[(kPkW2b / 8) + (mt * 2 + kt) * 64];
+        }
+        fr.b1[mt] = *reinterpret_cast<const f4 *>(P + oB1 + 16 * mt + 4 * g);
+        fr.b2[mt] = *reinterpret_cast<const f4 *>(P + oB2 + 16 * mt + 4 * g);
+        const f4 w3 = *reinterpret_cast<const f4 *>(P + oW3 + 16 * mt + 4 * g);
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                w2b[mi][kt][e] = (__bf16)P[oW2 + (16 * mi + c) * kH + 32 * kt + 16 * (e >> 2) + 4 * g + (e & 3)];
+        for (int e = 0; e < 4; ++e) fr.w3[mt][e >> 1][e & 1] = (__bf16)w3[e];
+    }
+    fr.b3 = P[oB3];
     const f4 z4 = {0.f, 0.f, 0.f, 0.f};
     const bf8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
     f4 gW2[4][4];                  // [mi][nj]: dW2[16 mi + 4g + e][16 nj + c]
@@ -252,13 +304,7 @@ __global__ __launch_bounds__(64) void k_mlp_grad(const float *__restrict__ P, co
             for (int u = 0; u < 4; ++u) out[oW2 + (16 * t + 4 * g + e) * kH + 16 * u + c] = gW2[t][u][e];
             out[oW1 + (4 * g + e) * kH + 16 * t + c] = gW1[t][e];
             // bias and W3 gradients: the sum over the 16 lanes (rows) of each lane group
-            float b1 = gb1[t][e], b2 = gb2[t][e], w3 = gw3[t][e];
-#pragma unroll
-            for (int off = 1; off < 16; off <<= 1) {
-                b1 += __shfl_xor(b1, off, 64);
-                b2 += __shfl_xor(b2, off, 64);
-                w3 += __shfl_xor(w3, off, 64);
-            }
+            const float b1 = sum16(gb1[t][e]), b2 = sum16(gb2[t][e]), w3 = sum16(gw3[t][e]);
             if (c == 0) {
                 out[oB1 + 16 * t + 4 * g + e] = b1;
                 out[oB2 + 16 * t + 4 * g + e] = b2;
@@ -304,7 +350,7 @@ __global__ __launch_bounds__(64) void k_mlp_reduce(const float *__restrict__ par
 // pass: thread e sums parameter e's partials, stores the gradient (and the loss at e = kParams) and updates
 // the parameter and its moments.
 __global__ __launch_bounds__(64) void k_mlp_reduce_adam(const float *__restrict__ part, int64_t nb, float *__restrict__ out,
-                                                         float *__restrict__ P, float *__restrict__ m,
+                                                         float *__restrict__ P, __bf16 *__restrict__ pk, float *__restrict__ m,
                                                          float *__restrict__ v, float lr, float beta1, float beta2,
                                                          float eps, float corr1, float corr2) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
@@ -316,7 +362,9 @@ __global__ __launch_bounds__(64) void k_mlp_reduce_adam(const float *__restrict_
     const float vv = beta2 * v[e] + (1.f - beta2) * g * g;
     m[e] = mm;
     v[e] = vv;
-    P[e] -= lr * (mm / corr1) / (sqrtf(vv / corr2) + eps);
+    const float p = P[e] - lr * (mm / corr1) / (sqrtf(vv / corr2) + eps);
+    P[e] = p;
+    put_packed(pk, e, p);
 }
 
 }  // namespace mlp
@@ -329,11 +377,16 @@ hipError_t launch_mlp_score(const float *P, const float *X, int64_t n, float *ou
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_grad(const float *P, const float *X, const float *y, const int64_t *idx, int64_t n, float *part,
-                           float *grad_out, hipStream_t s) {
+hipError_t launch_mlp_pack(const float *P, void *packed, hipStream_t s) {
+    hipLaunchKernelGGL(mlp::k_mlp_pack, dim3((mlp::kParams + 255) / 256), dim3(256), 0, s, P, (__bf16 *)packed);
+    return hipGetLastError();
+}
+
+hipError_t launch_mlp_grad(const float *P, const void *packed, const float *X, const float *y, const int64_t *idx, int64_t n,
+                           float *part, float *grad_out, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const int64_t nb = mlp_grad_partials(n);
-    hipLaunchKernelGGL(mlp::k_mlp_grad, dim3((unsigned)nb), dim3(64), 0, s, P, X, y, idx, RowPerm{0, 0, 0, 0}, n,
+    hipLaunchKernelGGL(mlp::k_mlp_grad, dim3((unsigned)nb), dim3(64), 0, s, P, (const __bf16 *)packed, X, y, idx, RowPerm{0, 0, 0, 0}, n,
                        1.f / (float)n, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -343,18 +396,19 @@ hipError_t launch_mlp_grad(const float *P, const float *X, const float *y, const
 
 int64_t mlp_grad_partials(int64_t n) { return std::min<int64_t>((n + 63) / 64, mlp::kGradWaves); }
 
-hipError_t launch_mlp_train_step(float *P, float *m, float *v, const float *X, const float *y, const RowPerm &perm,
-                                 int64_t cnt, float *part, float *grad_out, float lr, int64_t step, hipStream_t s) {
+hipError_t launch_mlp_train_step(float *P, void *packed, float *m, float *v, const float *X, const float *y,
+                                 const RowPerm &perm, int64_t cnt, float *part, float *grad_out, float lr, int64_t step,
+                                 hipStream_t s) {
     if (cnt <= 0) return hipSuccess;
     const int64_t nb = mlp_grad_partials(cnt);
-    hipLaunchKernelGGL(mlp::k_mlp_grad, dim3((unsigned)nb), dim3(64), 0, s, P, X, y, nullptr, perm, cnt,
+    hipLaunchKernelGGL(mlp::k_mlp_grad, dim3((unsigned)nb), dim3(64), 0, s, P, (const __bf16 *)packed, X, y, nullptr, perm, cnt,
                        1.f / (float)cnt, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const float b1 = 0.9f, b2 = 0.999f;
     const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
     hipLaunchKernelGGL(mlp::k_mlp_reduce_adam, dim3((mlp::kParams + 1 + 63) / 64), dim3(64), 0, s, part, nb, grad_out,
-                       P, m, v, lr, b1, b2, 1e-8f, c1, c2);
+                       P, (__bf16 *)packed, m, v, lr, b1, b2, 1e-8f, c1, c2);
     return hipGetLastError();
 }
 
