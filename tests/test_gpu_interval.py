@@ -95,3 +95,69 @@ def test_compact_bounds(vns, T, scale):
     inst.hM[:] = rng.integers(1, 3, 5) if T < 50 else 1
     inst.hR[:] = rng.integers(0, 2, 5)
     check(vns, inst, rng)
+
+
+SEARCHES = [dict(), dict(run_waves=1), dict(run_waves=2, memo=1), dict(run_waves=4, spec=4), dict(run_waves=2, state=0, lds=0)]
+
+
+def options_of(vns, form):
+    keys = dict(memo=vns.OPT_VND_MEMO, spec=vns.OPT_SPEC_ITERS, state=vns.OPT_STATE_LDS, lds=vns.OPT_RUN_LDS,
+                run_waves=vns.OPT_RUN_WAVES)
+    return {keys[k]: v for k, v in form.items()}
+
+
+@pytest.mark.parametrize("form", range(len(SEARCHES)))
+@pytest.mark.parametrize("T", [1, 2, 16, 33, 63, 64, 65, 128])
+def test_search_horizons(vns, T, form):
+    """Records and solutions of the interval search at the edges of its lane forms, against the oracle; its counts against
+    the full-decode search (the one that keeps a move log)."""
+    inst = draw_instance(np.random.default_rng([T, 5]), 6, T)
+    for nb, strict in (((1, 2, 4), False), ((4, 1), True), ((2, 2, 4, 1), False)):
+        inst.strict = strict
+        memo = SEARCHES[form].get("memo", 0)
+        with vns.Context(inst, seed=7, chains=2, nb_list=nb, options=options_of(vns, SEARCHES[form])) as ctx, \
+                vns.Context(inst, seed=7, chains=2, nb_list=nb, options={vns.OPT_LOG: 16, vns.OPT_VND_MEMO: memo}) as full:
+            chains = [oracle.Chain(inst, 7, g, nb) for g in range(2)]
+            for n in (5, 20):   # the second run starts from known local optima
+                ctx.run(n)
+                full.run(n)
+                for g, c in enumerate(chains):
+                    assert (ctx.trajectory(g) == c.run(n)).all(), (nb, g)
+                    zM, zR = ctx.solution(g)
+                    assert (zM == c.zM).all() and (zR == c.zR).all()
+                assert ctx.stats()["last_run_evals"] == full.stats()["last_run_evals"]
+
+
+@pytest.mark.parametrize("T", [12, 52, 104])
+def test_search_after_a_change_of_the_list(vns, T):
+    """Solutions found under one list need not be local optima of another: nothing known of them may be used.  (Both
+    searches go on with the shaken products only, so the full-decode one is the reference, not the oracle.)"""
+    inst = draw_instance(np.random.default_rng([T, 6]), 8, T)
+    with vns.Context(inst, seed=3, chains=3, nb_list=(1,)) as ctx, \
+            vns.Context(inst, seed=3, chains=3, nb_list=(1,), options={vns.OPT_LOG: 16}) as full:
+        for nb in ((1,), (1, 2, 4), (4, 2)):
+            value = 0
+            for i, b in enumerate(nb):
+                value |= b << (4 * i)
+            for c in (ctx, full):
+                c.set_option(vns.OPT_NB_LIST, value)
+                c.run(30)
+            for g in range(3):
+                assert (ctx.trajectory(g) == full.trajectory(g)).all(), (nb, g)
+                assert all((x == y).all() for x, y in zip(ctx.solution(g), full.solution(g)))
+            assert ctx.stats()["last_run_evals"] == full.stats()["last_run_evals"]
+
+
+def test_searches_past_the_compact_bounds(vns):
+    """Products past the 24-bit bounds search by full decodes; the records are the oracle's on both sides."""
+    for scale in (0.999, 1.01):
+        rng = np.random.default_rng(12)
+        inst = draw_instance(rng, 4, 20)
+        for a in (inst.D, inst.R):
+            w = rng.random((4, 20)) + 1e-3
+            a[:] = np.floor(w / w.sum(1, keepdims=True) * 2**23 * scale).astype(np.int32)
+        inst.hM[:], inst.hR[:] = 2, 1
+        with vns.Context(inst, seed=1, chains=2) as ctx:
+            ctx.run(12)
+            for g in range(2):
+                assert (ctx.trajectory(g) == oracle.Chain(inst, 1, g).run(12)).all()
