@@ -625,61 +625,76 @@ __global__ __launch_bounds__(256) void k_eval_prep(EvalPrepArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// k_chain_best: one workgroup per chain; per-product (price, slot) and the chain's lexicographic minimum.  One more
-// workgroup sums the pricing launch's counters and clears them.  Results go where the host reads them (mapped host memory
-// when they are small), so that a call ends with the launch and one wait: six copies and a memset of up to 16 KB
-// each waited for the one before and were 120 of a small call's 131 us.
+// k_chain_best<CHAINS>: per-product (price, slot) and each chain's lexicographic minimum, CHAINS chains to a workgroup.
+// One more workgroup sums the pricing launch's counters and clears them.  Results go where the host reads them (mapped
+// host memory when they are small), so that a call ends with the launch and one wait: six copies and a memset of up to
+// 16 KB each waited for the one before and were 120 of a small call's 131 us.
+//
+// CHAINS = 1: the workgroup's four wavefronts share one chain, the shortest way through few chains.  CHAINS = 16: a
+// wavefront for each chain, and the sixteen results leave in two stores of 128 and 64 bytes; one at a time, 8192 chains'
+// results are 16384 stores across the host link (28 -> 10 us; at 4096 chains of up to
+// 1000 products 18.2 -> 17.8 us, at 64 chains CHAINS = 1 is the faster, 4.0 against 5.0 us).
 // ---------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_chain_best(ChainBestArgs a) {
-    if ((int)blockIdx.x == a.n_chains) {
-        static_assert(kCounterSlots == 256, "one slot per thread");
+template <int CHAINS>
+__global__ __launch_bounds__(CHAINS == 1 ? 256 : 64 * CHAINS) void k_chain_best(ChainBestArgs a) {
+    constexpr int kWavesPer = CHAINS == 1 ? 4 : 1;   // wavefronts to a chain
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (blockIdx.x == gridDim.x - 1) {
+        static_assert(kCounterSlots == 256, "one slot per thread of the first four wavefronts");
         __shared__ unsigned long long s_sum[3][4];
-        unsigned long long *c = a.counters + (size_t)threadIdx.x * kCounterStride;
+        if (threadIdx.x < kCounterSlots) {
+            unsigned long long *c = a.counters + (size_t)threadIdx.x * kCounterStride;
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const int64_t n = wave_sum_i64((int64_t)c[i]);
-            if ((threadIdx.x & 63) == 0) s_sum[i][threadIdx.x >> 6] = (unsigned long long)n;
-            c[i] = 0ull;
+            for (int i = 0; i < 3; ++i) {
+                const int64_t n = wave_sum_i64((int64_t)c[i]);
+                if (lane == 0) s_sum[i][wave] = (unsigned long long)n;
+                c[i] = 0ull;
+            }
         }
         __syncthreads();
         if (threadIdx.x < 3) a.totals[threadIdx.x] = s_sum[threadIdx.x][0] + s_sum[threadIdx.x][1] + s_sum[threadIdx.x][2] + s_sum[threadIdx.x][3];
         return;
     }
-    const int g = a.chain0 + blockIdx.x;
-    const ChainInfo ci = a.chains[g];
-    const int64_t F = a.cstate[g].F;
+    const int b0 = blockIdx.x * CHAINS, b = b0 + (CHAINS == 1 ? 0 : wave);   // b: this wavefront's chain of the launch
     int64_t bp = kInf;
     int64_t bs = -1;
-    for (int p = threadIdx.x; p < ci.K; p += blockDim.x) {
-        const int64_t cp = ci.cp0 + p;
-        const uint64_t key = a.prod_key[cp];
-        int64_t price = kInf;
-        int32_t slot = -1;
-        if (key != kInfKey) {
-            price = F - a.cur_cost[cp] + (int64_t)(key >> kSlotBits);
-            slot = (int32_t)(key & ((1u << kSlotBits) - 1));
+    if (b < a.n_chains) {
+        const int g = a.chain0 + b;
+        const ChainInfo ci = a.chains[g];
+        const int64_t F = a.cstate[g].F;
+#pragma unroll CHAINS == 1 ? 1 : 4
+        for (int p = CHAINS == 1 ? (int)threadIdx.x : lane; p < ci.K; p += 64 * kWavesPer) {
+            const int64_t cp = ci.cp0 + p;
+            const uint64_t key = a.prod_key[cp];
+            int64_t price = kInf;
+            int32_t slot = -1;
+            if (key != kInfKey) {
+                price = F - a.cur_cost[cp] + (int64_t)(key >> kSlotBits);
+                slot = (int32_t)(key & ((1u << kSlotBits) - 1));
+            }
+            if (a.prod_price) a.prod_price[cp] = price;
+            if (a.prod_slot) a.prod_slot[cp] = slot;
+            const int64_t gs = slot < 0 ? -1 : (int64_t)p * 4 * ci.T + slot;
+            if (slot >= 0 && (price < bp || (price == bp && gs < bs))) { bp = price; bs = gs; }
         }
-        if (a.prod_price) a.prod_price[cp] = price;
-        if (a.prod_slot) a.prod_slot[cp] = slot;
-        const int64_t gs = slot < 0 ? -1 : (int64_t)p * 4 * ci.T + slot;
-        if (slot >= 0 && (price < bp || (price == bp && gs < bs))) { bp = price; bs = gs; }
     }
-    // lexicographic (price, slot) minimum over the workgroup
+    // lexicographic (price, slot) minimum over the wavefront
     for (int off = 32; off >= 1; off >>= 1) {
         const int64_t op = __shfl_xor(bp, off, 64);
         const int64_t os = __shfl_xor(bs, off, 64);
         if (os >= 0 && (bs < 0 || op < bp || (op == bp && os < bs))) { bp = op; bs = os; }
     }
-    __shared__ int64_t s_p[4], s_s[4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ int64_t s_p[CHAINS * kWavesPer], s_s[CHAINS * kWavesPer];
     if (lane == 0) { s_p[wave] = bp; s_s[wave] = bs; }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
+    if ((int)threadIdx.x < CHAINS && b0 + (int)threadIdx.x < a.n_chains) {
+        bp = s_p[threadIdx.x];
+        bs = s_s[threadIdx.x];
+        for (int w = 1; w < kWavesPer; ++w) {
             if (s_s[w] >= 0 && (bs < 0 || s_p[w] < bp || (s_p[w] == bp && s_s[w] < bs))) { bp = s_p[w]; bs = s_s[w]; }
         }
-        a.best[blockIdx.x] = bs < 0 ? kInf : bp;
-        a.best_slot[blockIdx.x] = (int32_t)bs;
+        a.best[b0 + threadIdx.x] = bs < 0 ? kInf : bp;
+        a.best_slot[b0 + threadIdx.x] = (int32_t)bs;
     }
 }
 
@@ -2003,7 +2018,12 @@ hipError_t launch_eval_inc(const EvalArgs &a, const EvalWg *wg, int64_t n_wg, si
 }
 
 hipError_t launch_chain_best(const ChainBestArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL(k_chain_best, dim3(a.n_chains + 1), dim3(256), 0, s, a);
+    // more chains than the chip holds workgroups of four wavefronts at once: a wavefront per chain
+    constexpr int kMany = 16;
+    if (a.n_chains > 2048)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_best<kMany>), dim3((a.n_chains + kMany - 1) / kMany + 1), dim3(64 * kMany), 0, s, a);
+    else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_best<1>), dim3(a.n_chains + 1), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
