@@ -960,7 +960,12 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
         if (wave == 0) {
             const bool draw = lane < kshake;
             // lane j: product and flip slot of draw j, drawn ahead during the last iteration's VND if it guessed this one
-            const uint32_t f = sh.draw_it == it ? sh.draw[lane] : shake_flip(a, g, it, stream, lane, nflip_all, T);
+            uint32_t f = sh.draw[lane];
+            if (sh.draw_it != it) {
+                f = shake_flip(a, g, it, stream, lane, nflip_all, T);
+                sh.draw[lane] = f;
+                wave_sync_lds();
+            }
             const int pd = (int)(f >> 8), ld = (int)(f & 255u);
             bool dup = false;                                        // an earlier draw hit the same product
             for (int j = 0; j < kshake; ++j) {
@@ -987,27 +992,39 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                 }
                 nd = __popcll(okm);
             } else {
-                for (int j = 0; j < kshake; ++j) {
-                    const int p = __builtin_amdgcn_readlane(pd, j);
-                    const int l = __builtin_amdgcn_readlane(ld, j);
-                    int e = -1;
-                    for (int q = 0; q < nd; ++q) e = (e < 0 && sh.dp[q] == p) ? q : e;
-                    Bits b;
-                    if (e >= 0) b = sh.db[e];
-                    else b = cur_bits(p);
-                    apply_move(b, l, T);
-                    const ProdParams pp = a.prod[ci.prod0 + p];
-                    const bool ok = rows_in_lds ? shake_feasible<MODEL>(b, s_rows + p * T, T, pp)
-                                                : shake_feasible<MODEL>(b, inst_rows + p * T, T, pp);
-                    if (ok) {
-                        if (e < 0) {
-                            e = nd++;
-                            if (lane == 0) sh.dp[e] = p;
-                        }
-                        if (lane == 0) sh.db[e] = b;
-                    }
-                    wave_sync_lds();
+                // products still are independent of each other: the first lane that drew a product resolves its draws
+                // in order, each kept if it leaves the product feasible.  (One draw after the other, by the whole
+                // wavefront, took 2890 cycles a shake on average in a 10-product instance, where most shakes of three
+                // and more meet a product twice, and 2450 so: its search 2.63 -> 2.52 ms for 500 iterations.)
+                uint64_t own = 0;   // the draws of this lane's product
+                for (int j = 0; j < kshake; ++j) own |= (uint64_t)(__builtin_amdgcn_readlane(pd, j) == pd ? 1u : 0u) << j;
+                int first = -1;     // the first draw that stays
+                Bits b = cur_bits(draw ? pd : 0);
+                if (draw && !dup) {
+                    const ProdParams pp = a.prod[ci.prod0 + pd];
+                    do {
+                        const int j = (int)__builtin_ctzll(own);
+                        own &= own - 1;
+                        Bits bj = b;
+                        apply_move(bj, (int)(sh.draw[j] & 255u), T);
+                        const bool ok = rows_in_lds ? shake_feasible<MODEL>(bj, s_rows + pd * T, T, pp)
+                                                    : shake_feasible<MODEL>(bj, inst_rows + pd * T, T, pp);
+                        if (ok) b = bj;
+                        first = ok && first < 0 ? j : first;
+                    } while (own != 0);
                 }
+                // the dirty list, in the order of the products' first draws that stay
+                uint64_t firsts = 0;
+                for (int j = 0; j < kshake; ++j) {
+                    const int fj = __builtin_amdgcn_readlane(first, j);
+                    firsts |= fj >= 0 ? 1ull << fj : 0ull;
+                }
+                if (first >= 0) {
+                    const int e = __popcll(firsts & ((1ull << first) - 1ull));
+                    sh.dp[e] = pd;
+                    sh.db[e] = b;
+                }
+                nd = __popcll(firsts);
             }
             if (lane == 0) {
                 sh.nd = nd;
