@@ -161,3 +161,37 @@ def test_searches_past_the_compact_bounds(vns):
             ctx.run(12)
             for g in range(2):
                 assert (ctx.trajectory(g) == oracle.Chain(inst, 1, g).run(12)).all()
+
+
+@pytest.mark.parametrize("strict", [False, True])
+@pytest.mark.parametrize("K,T,k_max", [(1, 6, 8), (2, 12, 64), (3, 40, 5), (4, 128, 12)])
+def test_shakes_that_meet_a_product_again(vns, K, T, k_max, strict):
+    """More draws than products, and flips that leave a product infeasible (no demand early: setups may come late)."""
+    inst = edge_instance("big_returns", K, T, seed=2)
+    inst.strict = strict
+    inst.D[:, :T // 3] = 0
+    with vns.Context(inst, seed=5, chains=2, k_max=k_max, nb_list=(1, 2)) as ctx:
+        chains = [oracle.Chain(inst, 5, g, (1, 2), k_max) for g in range(2)]
+        for n in (3, 40):
+            ctx.run(n)
+            for g, c in enumerate(chains):
+                assert (ctx.trajectory(g) == c.run(n)).all(), g
+                zM, zR = ctx.solution(g)
+                assert (zM == c.zM).all() and (zR == c.zR).all()
+
+
+@pytest.mark.parametrize("n", [2048, 2049, 2080])
+def test_best_of_many_chains(vns, n):
+    """The best moves of more chains than a workgroup each takes, against one chain's call: the last sixteen of a launch
+    and what is left over."""
+    rng = np.random.default_rng(n)
+    inst = draw_instance(rng, 3, 5)
+    with vns.Context(inst, seed=1, chains=n) as ctx:
+        for g in range(n):
+            if g < 4 or g > n - 40:
+                ctx.set_solution(g, *solution(inst, rng, 0.4, 0.4))
+        got = ctx.eval_neighbourhood(7)
+        for g in [0, 1, 2, 3, 15, 16, 17, 1000] + list(range(n - 39, n)):
+            one = ctx.eval_neighbourhood(7, chain=g)
+            assert (got["best"][g], got["best_slot"][g]) == (one["best"][0], one["best_slot"][0])
+            assert (got["prod_best"][3 * g:3 * g + 3] == one["prod_best"]).all()
