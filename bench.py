@@ -8,7 +8,7 @@ hM U{2..6}, hR U{1..hM}; instance i drawn from SeedSequence([5, i])), 16 Philox 
 ~2.8e9 move slots per full sweep, all resident in HBM.  It is the largest workload that fits one GPU.
 
 One step = one exact sweep: every move of the neighbourhoods flip zM, flip zR and shift for every chain
-(the pricing kernel k_eval), followed by each chain's lexicographic (price, slot) argmin (k_chain_best),
+(the pricing kernel k_eval_iv), followed by each chain's lexicographic (price, slot) argmin (k_chain_best),
 whose results are copied to the host.  The sweeps run on the states the plain GVNS search reached after the
 workload's 5000 iterations (local optima, as in the VND's last passes).  `value` = move-evaluations of the
 K timed steps / their device time (HIP events on the stream the kernels run on); inputs are resident before
@@ -21,7 +21,7 @@ Beside it, on the same GPU in the same run:
     exactly, the whole neighbourhood when none of them improves) runs on the same instances, seeds and chains
     until every instance reaches its target.  Device times of both, the scorer's and the training's rates.
   * `search`: the plain GVNS search's exact move-evaluations/s over the configured iterations: the 100 x 52
-    instance with 64 chains x 2000 iterations in one launch (with its kernel's roofline), the 4096-instance
+    instance with 64 chains x 2000 iterations in one launch, the 4096-instance
     batch with 8 chains x 1000 iterations in one launch, and the 1024-instance set's 5000 iterations.
   * `sweeps`: the same step on the 4096-instance batch (8 chains, after its 1000 iterations) and on the
     100 x 52 instance (64 chains, after its 2000 iterations).
@@ -46,15 +46,21 @@ from concurrent.futures import ThreadPoolExecutor
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-# int32 VALU peak of MI355X for the decode's own operation mix, from unit counts and clock: 256 CUs x 4 SIMDs x
-# 16 lanes x 2.4 GHz = 39.3e12 lane-slots/s.  Of the 14 operations of a period-step, 10 (bfe x2, bfi x4, min,
+# Interval pricing (csrc/vns_interval.hpp) is bound by VALU issue: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3e12
+# lane-slots/s.  Its operations, one lane-slot each: about 130 per period of a pattern (scans and records), 35 per move
+# (its price and its share of the walks).  Idle lanes (12 of 64 at T = 52, 24 of 128 at T = 104) and the walks' slowest
+# lanes are not counted as work.
+IV_OPS_PER_PERIOD, IV_OPS_PER_MOVE = 130, 35
+
+# int32 VALU peak of MI355X for the full decode's own operation mix, of the same 39.3e12 lane-slots/s.  Of the 14 operations of a period-step, 10 (bfe x2, bfi x4, min,
 # mad x2, and_or) take a lane-slot each and 4 (add, sub x2, the bitop3 of the no-setup mask) take half of one:
 # gfx950 issues that class at twice the rate (the probe in csrc/valu_probe.hip, `bench.py --valu-probe`).
 # 12 lane-slots per period-step make the peak 3.28e12 period-steps/s, 45.9e12 of these operations per second.
 OPS_PER_PERIOD_STEP = 14     # operations of one period-step of the forward decode
 LANE_SLOTS_PER_STEP = 12
 CU, SIMD_PER_CU, LANES_PER_SIMD, CLOCK_HZ = 256, 4, 16, 2.4e9
-VALU_PEAK_OPS = CU * SIMD_PER_CU * LANES_PER_SIMD * CLOCK_HZ * OPS_PER_PERIOD_STEP / LANE_SLOTS_PER_STEP
+LANE_SLOTS = CU * SIMD_PER_CU * LANES_PER_SIMD * CLOCK_HZ
+VALU_PEAK_OPS = LANE_SLOTS * OPS_PER_PERIOD_STEP / LANE_SLOTS_PER_STEP
 TUNE_FILE = os.path.join(ROOT, "paper_1704_05132_amd", "tune_table.json")
 BEST_OF_G = 4                # best-of-G search (Algorithm 2) measured beside the plain one: shakes per iteration
 LEARNED_SPEC_M = 8           # speculative iterations of the learned search (4 wavefronts per workgroup)
@@ -63,8 +69,8 @@ PACKED_P, PACKED_WAVES = 8, 2   # the packed learned search's batch and workgrou
 MLP_FLOP_PER_ROW = 2 * (16 * 64 + 64 * 64 + 64)
 BF16_PEAK_TFLOPS = 2500.0
 METRIC = "exact move-evals/s (int64 cost) + time-to-plain-best-cost, learned vs plain"
-SWEEP_LAUNCH = ("k_eval: every chain, neighbourhoods flip zM + flip zR + shift, tuned launch shape (chains per "
-                "workgroup, or pair ranges spread over the compute units)")
+SWEEP_LAUNCH = ("k_eval_iv: every chain, neighbourhoods flip zM + flip zR + shift, a range of (chain, product) "
+                "pairs per wavefront")
 SEARCH_LAUNCH = "search: every chain, the workload's iterations in one launch, tuned launch shape"
 
 
@@ -182,15 +188,16 @@ def sweep_steps(torch, vns, ctx, stream, steps, warmup):
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     ms = e0.elapsed_time(e1)
-    achieved = psteps * OPS_PER_PERIOD_STEP / (sum(k_ms) / 1e3) / 1e12
-    wide = ctx.get_option(vns.OPT_EVAL_SPREAD) > 4   # the range form with 8-16 wavefronts per workgroup
+    periods = sum(i.K * i.T for i in ctx.instances) * ctx.chains_per_inst
+    achieved = (IV_OPS_PER_PERIOD * periods * steps + IV_OPS_PER_MOVE * evals) / (sum(k_ms) / 1e3) / 1e12
     return {"steps": steps, "move_evals_per_step": evals // max(steps, 1), "device_ms": ms, "wall_s": wall,
-            "value": evals / (ms / 1e3), "unit": "move-evals/s", "kernel": "k_eval_wide" if wide else "k_eval",
+            "value": evals / (ms / 1e3), "unit": "move-evals/s", "kernel": "k_eval_iv",
             "launch_shape": {"spread": ctx.get_option(vns.OPT_EVAL_SPREAD),
                              "group": ctx.get_option(vns.OPT_EVAL_GROUP)},
             "kernel_ms_mean": sum(k_ms) / len(k_ms), "kernel_ms_median": statistics.median(k_ms),
-            "kernel_share": sum(k_ms) / ms, "achieved": achieved, "peak": VALU_PEAK_OPS / 1e12,
-            "frac": achieved / (VALU_PEAK_OPS / 1e12)}
+            "kernel_share": sum(k_ms) / ms, "achieved": achieved, "peak": LANE_SLOTS / 1e12,
+            "frac": achieved / (LANE_SLOTS / 1e12),
+            "full_decode_equivalent_TOPs": psteps * OPS_PER_PERIOD_STEP / (sum(k_ms) / 1e3) / 1e12}
 
 
 def warm_search(vns, make_ctx):
@@ -203,21 +210,22 @@ def warm_search(vns, make_ctx):
 
 
 def search_once(vns, ctx, iters):
-    """One launch of `iters` GVNS iterations of every chain; the search kernel's rate and roofline (the
-    evaluations the search consumed; speculative iterations thrown away are counted apart)."""
+    """One launch of `iters` GVNS iterations of every chain; the search kernel's rate: the evaluations the search
+    consumed (speculative iterations thrown away are counted apart), and what full decodes of them would have to run
+    at.  Neighbourhoods met again on an unchanged pattern count without being priced, so no operation count of its own
+    follows from them."""
     ctx.run(iters)
     st = ctx.stats()
     ms, evals = st["last_run_ms"], st["last_run_evals"]
     spec_m, discarded = st["last_run_spec_iters"], st["last_run_discarded_evals"]
-    achieved = st["last_run_period_steps"] * OPS_PER_PERIOD_STEP / (ms / 1e3) / 1e12
     executed = (evals + discarded) / evals if evals else 1.0
     best = ctx.get_option(vns.OPT_BEST_OF)
-    return {"iters": iters, "kernel": "k_run_coop" if spec_m > 1 or best > 1 else "k_run", "kernel_ms": ms,
+    return {"iters": iters, "kernel": "k_run_coop_iv" if spec_m > 1 or best > 1 else "k_run_iv", "kernel_ms": ms,
             "move_evals": evals, "value": evals / (ms / 1e3), "unit": "move-evals/s",
-            "iterations_per_s": iters / (ms / 1e3), "achieved": achieved, "peak": VALU_PEAK_OPS / 1e12,
-            "unit_achieved": "TOP/s", "frac": achieved / (VALU_PEAK_OPS / 1e12),
+            "iterations_per_s": iters / (ms / 1e3),
+            "full_decode_equivalent_TOPs": st["last_run_period_steps"] * OPS_PER_PERIOD_STEP / (ms / 1e3) / 1e12,
             "speculative_iterations": spec_m, "discarded_move_evals": discarded,
-            "executed_over_consumed": executed, "executed_frac": achieved * executed / (VALU_PEAK_OPS / 1e12)}
+            "executed_over_consumed": executed}
 
 
 def chunked_search(make_ctx, n_inst, chains, max_iters, chunk, targets=None, horizon_ms=None, keep=False):
@@ -377,12 +385,10 @@ def learned_vs_plain(args, vns, stream, table, key, name, insts, w, plain):
     out["per_iteration"] = {"plain": per_it(plain), "learned": per_it(lrn)}
     if packed is not None:
         out["packed"] = packed
-    out["reason"] = ("a learned neighbourhood evaluation scores every move (MFMA) and then needs the exact prices "
-                     "of the best-ranked share, with one move per lane over all T periods (the same decode latency "
-                     "as pricing the whole neighbourhood), and of the whole neighbourhood when none of them "
-                     "improves (fallback_share; both come from one pricing when the neighbourhood fits two "
-                     "wavefront passes); exact pricing runs near the int32 peak, so fewer exact evaluations do not "
-                     "buy back the scoring and the fallbacks")
+    out["reason"] = ("a learned neighbourhood evaluation prices every move exactly (a few dozen operations a move from "
+                     "one decode of the pattern), and scores the moves (MFMA, 10368 flops each) only when one of them "
+                     "improves, as the choice depends on the scores only then; the plain search takes the best move "
+                     "from the same prices without scoring, so scoring is the learned form's extra cost")
     if n_inst == 1:
         out["plain_best_F"] = int(B[0])
         out["learned_best_F"] = int(lrn["best"][0])
@@ -617,7 +623,7 @@ def main():
               "T": Ts[0] if len(Ts) == 1 else Ts, "chains_per_instance": w["chains"],
               "chains": len(insts) * w["chains"], "neighbourhoods": ["flip_zM", "flip_zR", "shift"], "k_max": 5,
               "seed": w["seed"], "search_iters": iters, "tuning": (table.get(key) or {}).get("choice"),
-              "step": "one exact sweep of every move of flip zM, flip zR and shift for every chain (k_eval), then "
+              "step": "one exact sweep of every move of flip zM, flip zR and shift for every chain (k_eval_iv), then "
                       "each chain's (price, slot) argmin (k_chain_best) copied to the host; on the states of "
                       f"the plain search after {iters} iterations"}
     out = {
@@ -626,10 +632,11 @@ def main():
         "scaling": "weak", "vs_baseline": None, "dtype": "int64", "data": "synthetic", "config": config,
         "move_evals_per_step": sweep["move_evals_per_step"], "wall_s": sweep["wall_s"],
         "roofline": {"kernel": sweep["kernel"], "launch": SWEEP_LAUNCH, "bound": "alu", "achieved": sweep["achieved"],
-                     "peak": VALU_PEAK_OPS / 1e12, "unit": "TOP/s", "frac": sweep["frac"],
+                     "peak": LANE_SLOTS / 1e12, "unit": "TOP/s", "frac": sweep["frac"],
                      "traffic": measured_traffic(sweep["kernel"], name, "sweep"),
-                     "kernel_ms_mean": sweep["kernel_ms_mean"], "ops_per_period_step": OPS_PER_PERIOD_STEP,
-                     "accumulators": "int32 under the create-time bounds; costs int64"},
+                     "kernel_ms_mean": sweep["kernel_ms_mean"], "ops_per_period": IV_OPS_PER_PERIOD, "ops_per_move": IV_OPS_PER_MOVE,
+                     "accumulators": "int32 under the create-time bounds; costs int64",
+                     "full_decode_equivalent_TOPs": sweep["full_decode_equivalent_TOPs"]},
         "sweeps": {name: sweep},
         "search": {name: search_main},
     }

@@ -173,7 +173,9 @@ typedef struct vns_record {
 
 typedef struct vns_stats {
     int64_t iterations;      /* GVNS iterations run per chain since creation or the last reset            */
-    int64_t move_evals;      /* exactly priced moves (valid slots) in all chains since creation            */
+    int64_t move_evals;      /* exactly priced moves (valid slots) in all chains since creation; a VND that meets a
+                                neighbourhood again on an unchanged pattern counts it, as Algorithm 1 prices it
+                                (VNS_OPT_VND_MEMO: not), whether or not it is computed again                */
     int64_t last_run_evals;  /* move-evaluations of the last vns_run call                                 */
     double last_run_ms;      /* device time of the last vns_run call (HIP events on the context stream)  */
     int64_t last_eval_evals; /* move-evaluations of the last vns_eval_neighbourhood call                  */

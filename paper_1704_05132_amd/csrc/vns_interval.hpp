@@ -17,9 +17,9 @@
 //
 // What bounds it: VALU issue (97% of the issue slots in the 256 x 16 sweep).  A full decode costs every move 14 T
 // operations (728 at T = 52); here the scans and records are about 130 instructions per pattern, a move takes
-// 20 to 35, and two records of a walk 11 to 15, of which the slowest of 64 lanes needs 3 to 5 pairs (1.3 records on
+// 20 to 35, and four records of a walk 22 to 30, of which the slowest of 64 lanes needs 2 to 3 rounds (1.3 records on
 // average; local optima, T = 52): 500 instructions for a pattern's 156 slots in place of 2000.  Best move of every
-// pattern of 256 instances (K 100..1000, T 52 or 104) x 16 chains: 15.9 -> 3.05 ms; of 1024 instances (K 10..200, T
+// pattern of 256 instances (K 100..1000, T 52 or 104) x 16 chains: 15.9 -> 2.78 ms; of 1024 instances (K 10..200, T
 // 12, 24 or 52) x 8: 1.18 -> 0.43 ms.  Short horizons share a wavefront (16 or 32 lanes per pattern), which halves the
 // instructions per pattern at T = 24 and quarters them at T = 12.
 //

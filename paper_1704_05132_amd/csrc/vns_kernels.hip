@@ -6,11 +6,15 @@
 //                   each product is computed independently of the others).  Moves are compacted (pads and
 //                   swaps of equal bits never take a lane) and the chains of the group share one LDS copy of
 //                   the product's row, so a wavefront is full whatever T is
+//   k_eval_iv       the same prices from one parallel decode of each pattern (vns_interval.hpp), where every product is
+//                   compact and the reading has no disposal
 //   k_chain_best    per chain: lexicographic (price, slot) minimum over its products
 //   k_run           one workgroup per chain running whole GVNS iterations (Algorithm 2): Philox shake,
 //                   VND (Algorithm 1) with one wavefront per product that needs it, acceptance
 //   k_run_spec      the same with the neighbourhoods of a product's VND priced side by side
 //   k_run_learned   the same with the learned scorer choosing which moves are priced exactly
+//   k_run_iv, k_run_coop_iv, k_run_learned_iv   these searches with the VND by interval pricing; the forms above are
+//                   left for the disposal reading, products past the compact bounds and runs that keep a move log
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -440,6 +444,10 @@ __global__ __launch_bounds__(256) void k_eval_inc(EvalArgs a, const EvalWg *__re
 // a time for T > 32, two at a time (32 lanes each) for T > 16, four at a time up to 16, and prices the four slot
 // blocks of each with one period per lane.  No workgroup synchronisation and no move list: a slot is (block,
 // lane).
+//
+// Bound by VALU issue: at 256 instances (K 100..1000, T 52 or 104) x 16 chains 2.78 ms in place of 15.9 (k_eval, 97% of
+// the issue slots in both), at 1024 instances (K 10..200, T 12, 24 or 52) x 8 chains 0.43 in place of 1.18, at one of
+// 100 x 52 with 64 chains 14 us in place of 32.
 // ---------------------------------------------------------------------------------------------------
 namespace {
 
@@ -1779,6 +1787,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 
 // The plain search with interval pricing (contexts of compact products, no move log), one workgroup per chain and
 // with speculative iterations or best-of-G.  IV: 1 when every horizon is at most 64, else 2.
+//
+// Bound by a lone wavefront's instruction issue (about 5 cycles each) and LDS waits along one product's VND: 1.65
+// patterns of 650 cycles, 2.4 neighbourhoods of 680 (T = 12) to 1060 (T = 52) and 1800 of control, then the shake (1700)
+// and the acceptance (1500).  Full decodes -> interval pricing: 500 iterations of 10 x 12 4.66 -> 2.4 ms; 512 instances
+// (K 10..200, T 12, 24 or 52) x 8 chains x 50 5.4 -> 1.17 ms; 64 instances (T 52 or 104) x 16 7.2 -> 0.83 ms; with
+// speculative iterations 100 x 52, 64 chains x 200 1.46 -> 0.65 ms under the profiler; best of 4, 300 x 52 2.2 -> 0.87 ms.
+// Four wavefronts per SIMD for one period a lane, three for two: at four the two-word form spills.
 template <int IV, int MODEL>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(IV == 2 ? 3 : 4))) void k_run_iv(RunArgs a) {
     __shared__ RunShared sh;
@@ -1797,7 +1812,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void k
     run_chain<false, false, true, MODEL, false, false, IV>(a, sh, lists, sp, s_rows);
 }
 
-// The learned search with interval pricing.
+// The learned search with interval pricing: 50 iterations of 100 x 52, 64 chains, 8 side by side, 1.56 -> 0.53 ms.  Scores
+// are computed only where a move improves (0.98 -> 0.53 ms of it); the weights' fragments hold it at two wavefronts per SIMD.
 template <int IV, bool COOP>
 __global__ __launch_bounds__(512) void k_run_learned_iv(RunArgs a) {
     __shared__ RunShared sh;
