@@ -796,9 +796,9 @@ __device__ __forceinline__ void lds_store(T *p, const T &v) {
     for (size_t i = 0; i < sizeof(T) / 8; ++i) w[i] = r[i];
 }
 
-// The flip of draw j (< kmax) of iteration it, as product << 8 | its flip slot (K <= 2^20, 2T <= 256).
+// The flip of draw j of iteration it, as product << 8 | its flip slot (K <= 2^20, 2T <= 256).  Every lane draws: a chain's
+// k may still be above the k_max of this run, when that was lowered after the last one.
 __device__ __forceinline__ uint32_t shake_flip(const RunArgs &a, int g, int64_t it, uint64_t stream, int j, uint64_t n, int T) {
-    if (j >= a.kmax) return 0u;
     const uint32_t f = shake_draw(a.seed, (uint64_t)g, (uint64_t)it, (uint64_t)j, n, stream), p = f / (uint32_t)(2 * T);
     return p << 8 | (f - p * (uint32_t)(2 * T));
 }

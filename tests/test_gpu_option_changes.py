@@ -1,0 +1,37 @@
+"""GPU: options changed between the runs of one context, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1704_05132_amd.instances import draw_instance
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def vns():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_1704_05132_amd import vns as v
+    return v
+
+
+@pytest.mark.parametrize("form", ["plain", "one wavefront", "spec_iters", "full decode", "speculative vnd"])
+@pytest.mark.parametrize("K,T,low", [(10, 12, 3), (3, 40, 1), (6, 70, 5)])
+def test_k_max_lowered_below_a_chains_k(vns, K, T, low, form):
+    """The next shake still takes the chain's k flips, though it is above the new k_max."""
+    opts = {"plain": {}, "one wavefront": {vns.OPT_RUN_WAVES: 1}, "spec_iters": {vns.OPT_SPEC_ITERS: 4, vns.OPT_RUN_WAVES: 4},
+            "full decode": {vns.OPT_LOG: 16}, "speculative vnd": {vns.OPT_SPECULATE: 1}}[form]
+    inst = draw_instance(np.random.default_rng([K, T, 21]), K, T)
+    with vns.Context(inst, seed=1, chains=4, k_max=64, options=opts) as ctx:
+        chains = [oracle.Chain(inst, 1, g, k_max=64) for g in range(4)]
+        for n, k_max in ((45, 64), (20, low)):
+            ctx.set_option(vns.OPT_KMAX, k_max)
+            for c in chains:
+                c.k_max = k_max
+            assert n == 45 or any(c.k > k_max for c in chains)
+            ctx.run(n)
+            for g, c in enumerate(chains):
+                assert (ctx.trajectory(g) == c.run(n)).all(), g
+                zM, zR = ctx.solution(g)
+                assert (zM == c.zM).all() and (zR == c.zR).all(), g
