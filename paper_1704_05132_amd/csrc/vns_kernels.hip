@@ -984,7 +984,11 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                 dup |= draw && j < lane && pj == pd;
             }
             int nd = 0;
-            if (!__any(dup)) {
+            // (k_run under the strict reading takes the second form for every shake: its full decode inlined at both places
+            // costs the fourth wavefront per SIMD, 1.6x the time at eight wavefronts a workgroup.  The other searches keep
+            // their wavefronts with both, and distinct draws are 2 to 4% of a short horizon's iteration faster so.)
+            constexpr bool kOneForm = (MODEL & kModelStrict) != 0 && !(IV || COOP || MULTI);
+            if (!kOneForm && !__any(dup)) {
                 // distinct products: the draws are independent, so each lane resolves its own and the
                 // feasible ones are compacted in draw order
                 bool ok = false;
