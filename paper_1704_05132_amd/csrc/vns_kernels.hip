@@ -714,7 +714,7 @@ __global__ __launch_bounds__(CHAINS == 1 ? 256 : 64 * CHAINS) void k_chain_best(
 // ---------------------------------------------------------------------------------------------------
 namespace {
 
-typedef uint16_t SwapLists[kMaxWaves][2 * kTMax];   // compacted swap moves of each wavefront's product
+typedef uint16_t SwapList[2 * kTMax];   // compacted swap moves of a wavefront's product
 
 struct RunShared {
     Bits db[kShakeMax];                    // shaken products (dirty list): bits after the shake
@@ -806,7 +806,7 @@ __device__ __forceinline__ uint32_t shake_flip(const RunArgs &a, int g, int64_t 
 
 // IV: the plain search's VND by interval pricing, with one (1) or up to two (2) periods per lane; 0: by full decodes.
 template <bool SPEC, bool LEARNED, bool COOP = false, int MODEL = 0, bool PACK = false, bool MULTI = false, int IV = 0>
-__device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapLists &lists, SpecShared &sp, int2 *s_rows) {
+__device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapList *lists, SpecShared &sp, int2 *s_rows) {
     static_assert(!PACK || LEARNED, "the packed form is the learned VND's");
     static_assert(!(SPEC && LEARNED), "the speculative VND prices whole neighbourhoods");
     static_assert(!(COOP && SPEC), "speculative iterations run the sequential VND");
@@ -1775,7 +1775,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
 template <int MODEL>
 __global__ __launch_bounds__(512) void k_run(RunArgs a) {
     __shared__ RunShared sh;
-    __shared__ SwapLists lists;
+    __shared__ SwapList lists[kRunWaves];
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
     run_chain<false, false, false, MODEL>(a, sh, lists, sp, s_rows);
@@ -1786,7 +1786,7 @@ __global__ __launch_bounds__(512) void k_run(RunArgs a) {
 template <int MODEL>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_run_short(RunArgs a) {
     __shared__ RunShared sh;
-    __shared__ SwapLists lists;
+    __shared__ SwapList lists[kRunWaves];
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
     run_chain<false, false, false, MODEL, false, true>(a, sh, lists, sp, s_rows);
@@ -1804,7 +1804,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 template <int IV, int MODEL>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(IV == 2 ? 3 : 4))) void k_run_iv(RunArgs a) {
     __shared__ RunShared sh;
-    __shared__ SwapLists lists;
+    __shared__ SwapList lists[kRunWaves];
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
     run_chain<false, false, false, MODEL, false, false, IV>(a, sh, lists, sp, s_rows);
@@ -1813,7 +1813,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(IV == 2 ? 3
 template <int IV, int MODEL>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void k_run_coop_iv(RunArgs a) {
     __shared__ RunShared sh;
-    __shared__ SwapLists lists;
+    __shared__ SwapList lists[kRunWaves];
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
     run_chain<false, false, true, MODEL, false, false, IV>(a, sh, lists, sp, s_rows);
@@ -1824,7 +1824,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void k
 template <int IV, bool COOP>
 __global__ __launch_bounds__(512) void k_run_learned_iv(RunArgs a) {
     __shared__ RunShared sh;
-    __shared__ SwapLists lists;
+    __shared__ SwapList lists[kRunWaves];
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
     run_chain<false, true, COOP, 0, false, false, IV>(a, sh, lists, sp, s_rows);
@@ -1832,7 +1832,7 @@ __global__ __launch_bounds__(512) void k_run_learned_iv(RunArgs a) {
 
 __global__ __launch_bounds__(1024) void k_run_spec(RunArgs a) {
     __shared__ RunShared sh;
-    __shared__ SwapLists lists;
+    __shared__ SwapList lists[kMaxWaves];
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
     run_chain<true, false>(a, sh, lists, sp, s_rows);
@@ -1843,7 +1843,7 @@ __global__ __launch_bounds__(1024) void k_run_spec(RunArgs a) {
 template <int MODEL>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void k_run_coop(RunArgs a) {
     __shared__ RunShared sh;
-    __shared__ SwapLists lists;
+    __shared__ SwapList lists[kRunWaves];
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
     run_chain<false, false, true, MODEL>(a, sh, lists, sp, s_rows);
@@ -1853,7 +1853,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void k
 // speculative iterations of the learned search
 __global__ __launch_bounds__(512) void k_run_learned_coop(RunArgs a) {
     __shared__ RunShared sh;
-    __shared__ SwapLists lists;
+    __shared__ SwapList lists[kRunWaves];
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
     run_chain<false, true, true>(a, sh, lists, sp, s_rows);
@@ -1861,7 +1861,7 @@ __global__ __launch_bounds__(512) void k_run_learned_coop(RunArgs a) {
 
 __global__ __launch_bounds__(512) void k_run_learned(RunArgs a) {
     __shared__ RunShared sh;
-    __shared__ SwapLists lists;
+    __shared__ SwapList lists[kRunWaves];
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
     run_chain<false, true>(a, sh, lists, sp, s_rows);
@@ -1870,7 +1870,7 @@ __global__ __launch_bounds__(512) void k_run_learned(RunArgs a) {
 // the packed learned VND (batches of products per wavefront), alone and with speculative iterations
 __global__ __launch_bounds__(512) void k_run_learned_packed(RunArgs a) {
     __shared__ RunShared sh;
-    __shared__ SwapLists lists;
+    __shared__ SwapList lists[kRunWaves];
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
     run_chain<false, true, false, 0, true>(a, sh, lists, sp, s_rows);
@@ -1878,7 +1878,7 @@ __global__ __launch_bounds__(512) void k_run_learned_packed(RunArgs a) {
 
 __global__ __launch_bounds__(512) void k_run_learned_coop_packed(RunArgs a) {
     __shared__ RunShared sh;
-    __shared__ SwapLists lists;
+    __shared__ SwapList lists[kRunWaves];
     __shared__ SpecShared sp;
     extern __shared__ __attribute__((aligned(16))) int2 s_rows[];
     run_chain<false, true, true, 0, true>(a, sh, lists, sp, s_rows);

@@ -569,7 +569,7 @@ extern "C" vns_status vns_set_option(vns_ctx *c, int32_t key, int64_t v) {
             c->trace = (int32_t)v;
             return VNS_OK;
         case VNS_OPT_RUN_WAVES:
-            if (v < 1 || v > 8) return fail(c, VNS_EINVAL, "run waves out of range");
+            if (v < 1 || v > kRunWaves) return fail(c, VNS_EINVAL, "run waves out of range");
             c->run_waves = (int32_t)v;
             return VNS_OK;
         case VNS_OPT_EVAL_GROUP:

@@ -18,7 +18,8 @@ namespace vns {
 constexpr int kWords = 4;          // 32-bit words per setup row: T <= 128
 constexpr int kTMax = 32 * kWords;
 constexpr int kShakeMax = 64;
-constexpr int kMaxWaves = 16;     // wavefronts per search workgroup (8 for the sequential VND, 16 speculative)
+constexpr int kMaxWaves = 16;     // wavefronts per search workgroup, speculative VND
+constexpr int kRunWaves = 8;      //   and the other searches
 constexpr int kEvalGroup = 16;
 constexpr int kEvalPairs = 64;    // (chain, product) pairs one pricing workgroup may price
 constexpr int kEvalProds = 8;     //   of at most this many products (short horizons: their rows share LDS)

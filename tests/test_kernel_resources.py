@@ -50,3 +50,11 @@ def test_four_wavefronts_per_simd(kernels, name):
     """A SIMD has 512 VGPRs: at most 128 leave room for four wavefronts, two workgroups of eight to a compute unit."""
     for k, (vgprs, _) in family(kernels, name).items():
         assert vgprs <= 128, (k, vgprs)
+
+
+@pytest.mark.parametrize("name", ["k_run", "k_run_short", "k_run_coop", "k_run_learned", "k_run_learned_coop"])
+def test_static_lds(kernels, name):
+    """Side-by-side and best-of-G searches need their workgroups resident at once: 38 x 52 with disposal, best of 16 on 96
+    chains in workgroups of two wavefronts, is six workgroups to a compute unit's 160 KB, 15808 bytes of each its rows."""
+    for k, (_, lds) in family(kernels, name).items():
+        assert lds + 15808 <= 160 * 1024 // 6, (k, lds)
