@@ -165,7 +165,9 @@ struct vns_ctx {
     uint32_t ws_flags = 0;
 
     // Small results are written by the kernels straight into this pinned, device-mapped buffer (kStageBytes, held for
-    // the context's life) and copied to the caller's arrays after the call's one wait.
+    // the context's life) and copied to the caller's arrays after the call's one wait.  `in_use`: one call at a time uses
+    // it (VNS_STAGE), as threads may read one context side by side.
+    std::mutex in_use;
     unsigned char *h_stage = nullptr, *d_stage = nullptr;
     // scorer calls: device copies of the caller's rows, targets and scores and the gradient's scratch, kept between calls
     // up to kScorerKeep bytes each
@@ -217,6 +219,11 @@ static vns_status hip_fail(vns_ctx *c, hipError_t e, const char *what) {
             return hip_fail((ctx), hipErrorLaunchFailure, "injected failure (vns_test_inject_failure)"); \
         VNS_HIP((ctx), hipSetDevice((ctx)->device));                                          \
     } while (0)
+
+// A call on a live context that uses what calls share: the stage, the scorer buffers.
+#define VNS_STAGE(ctx) \
+    VNS_LIVE(ctx);     \
+    std::lock_guard<std::mutex> hold_((ctx)->in_use)
 
 template <class T>
 static hipError_t dmalloc(T **p, size_t n) {
@@ -855,7 +862,7 @@ static vns_status finish_eval(vns_ctx *c, EvalOut &o, int32_t g0, int32_t ng, in
 extern "C" vns_status vns_eval_neighbourhood(vns_ctx *c, uint32_t nb_mask, int32_t chain, int64_t *slot_price,
                                              int64_t *prod_best, int32_t *prod_best_slot, int64_t *best,
                                              int32_t *best_slot) {
-    VNS_LIVE(c);
+    VNS_STAGE(c);
     if (nb_mask == 0 || (nb_mask & ~7u)) return fail(c, VNS_EINVAL, "bad neighbourhood mask");
     if (c->eval_inc && c->model != 0)
         return fail(c, VNS_EINVAL, "incremental pricing takes only the default decode reading (VNS_OPT_DECODE = 0)");
@@ -1022,7 +1029,7 @@ extern "C" vns_status vns_eval_neighbourhood(vns_ctx *c, uint32_t nb_mask, int32
 extern "C" vns_status vns_eval_neighbourhood_noalloc(vns_ctx *c, uint32_t nb_mask, int32_t chain, int64_t *slot_price,
                                                      int64_t *prod_best, int32_t *prod_best_slot, int64_t *best,
                                                      int32_t *best_slot) {
-    VNS_LIVE(c);
+    VNS_STAGE(c);
     if (nb_mask == 0 || (nb_mask & ~7u)) return fail(c, VNS_EINVAL, "bad neighbourhood mask");
     int32_t g0, ng;
     if (chain == VNS_ALL_CHAINS) {
@@ -1103,7 +1110,7 @@ extern "C" vns_status vns_eval_neighbourhood_noalloc(vns_ctx *c, uint32_t nb_mas
 // search
 // ---------------------------------------------------------------------------------------------------
 extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
-    VNS_LIVE(c);
+    VNS_STAGE(c);
     if (iters < 0) return fail(c, VNS_EINVAL, "iters must be >= 0");
     if (c->iteration + iters > (int64_t)INT32_MAX) return fail(c, VNS_ERANGE, "iteration counter would overflow");
     if (iters == 0) return VNS_OK;
@@ -1352,7 +1359,7 @@ extern "C" vns_status vns_get_cost(vns_ctx *c, int32_t chain, int64_t *F, int64_
 }
 
 extern "C" vns_status vns_get_costs(vns_ctx *c, int64_t *F, int64_t *F_best) {
-    VNS_LIVE(c);
+    VNS_STAGE(c);
     const size_t n = c->chains.size(), bytes = sizeof(int64_t) * n;
     if (2 * bytes <= kStageBytes) {
         int64_t *d = reinterpret_cast<int64_t *>(c->d_stage);
@@ -1373,7 +1380,7 @@ extern "C" vns_status vns_get_costs(vns_ctx *c, int64_t *F, int64_t *F_best) {
 }
 
 extern "C" vns_status vns_get_solution(vns_ctx *c, int32_t chain, int32_t which, uint8_t *zM, uint8_t *zR) {
-    VNS_LIVE(c);
+    VNS_STAGE(c);
     vns_status s = check_chain(c, chain);
     if (s != VNS_OK) return s;
     if (which != VNS_SOLUTION_CURRENT && which != VNS_SOLUTION_BEST) return fail(c, VNS_EINVAL, "which must be 0 or 1");
@@ -1473,7 +1480,7 @@ extern "C" vns_status vns_set_solution(vns_ctx *c, int32_t chain, const uint8_t 
 }
 
 extern "C" vns_status vns_get_trajectory(vns_ctx *c, int32_t chain, vns_record *rec, int64_t cap, int64_t *n) {
-    VNS_LIVE(c);
+    VNS_STAGE(c);
     vns_status s = check_chain(c, chain);
     if (s != VNS_OK) return s;
     const int64_t avail = c->trace_iters;
@@ -1629,7 +1636,7 @@ static vns_status scorer_data(vns_ctx *c, const float *feats, const float *targe
 }
 
 extern "C" vns_status vns_mlp_score(vns_ctx *c, const float *feats, int64_t n, float *scores) {
-    VNS_LIVE(c);
+    VNS_STAGE(c);
     if (n < 0 || (n > 0 && (!feats || !scores))) return fail(c, VNS_EINVAL, "bad arguments");
     if (n == 0) return VNS_OK;
     ScorerCall guard{c};
@@ -1646,7 +1653,7 @@ extern "C" vns_status vns_mlp_score(vns_ctx *c, const float *feats, int64_t n, f
 
 extern "C" vns_status vns_mlp_grad(vns_ctx *c, const float *feats, const float *targets, int64_t n, float *grads,
                                    float *loss) {
-    VNS_LIVE(c);
+    VNS_STAGE(c);
     if (n <= 0 || !feats || !targets) return fail(c, VNS_EINVAL, "bad arguments");
     ScorerCall guard{c};
     vns_status st = scorer_data(c, feats, targets, n, n);
@@ -1665,7 +1672,7 @@ extern "C" vns_status vns_mlp_grad(vns_ctx *c, const float *feats, const float *
 
 extern "C" vns_status vns_mlp_train(vns_ctx *c, const float *feats, const float *targets, int64_t n, int32_t epochs,
                                     int32_t batch, float lr, uint64_t seed, float *last_loss) {
-    VNS_LIVE(c);
+    VNS_STAGE(c);
     if (n <= 0 || !feats || !targets || epochs < 0 || batch < 1 || !(lr > 0.f)) return fail(c, VNS_EINVAL, "bad arguments");
     const int64_t bmax = std::min<int64_t>(batch, n);
     ScorerCall guard{c};
@@ -1726,7 +1733,7 @@ __global__ void k_fill_nan(float *p, int64_t n) {
 
 extern "C" vns_status vns_eval_learned(vns_ctx *c, uint32_t nb, int32_t chain, int32_t top_permille, float *scores,
                                        uint8_t *selected, int64_t *prod_best, int32_t *prod_best_slot, uint8_t *fallback) {
-    VNS_LIVE(c);
+    VNS_STAGE(c);
     if (nb != VNS_NB_FLIP_M && nb != VNS_NB_FLIP_R && nb != VNS_NB_SHIFT) return fail(c, VNS_EINVAL, "nb must be one neighbourhood");
     if (c->model != 0)
         return fail(c, VNS_EINVAL, "the learned choice takes only the default decode reading (VNS_OPT_DECODE = 0)");
