@@ -134,7 +134,9 @@ enum vns_option {
                               vns_stats.last_eval_decoded_steps reports the period-steps decoded.
                               Interval pricing (see VNS_OPT_EVAL_GROUP) always works this way, by setup
                               intervals: with this option it reports the pattern's own T periods per
-                              (chain, product), one step per move and one per later interval priced anew */
+                              (chain, product), one step per move, and the later remanufacturing intervals
+                              (after them the horizon's end) read for a move until it changes nothing
+                              more: four at a time, all four counted                                  */
     VNS_OPT_DECODE = 19,   /* decode reading, a bit set (default 0); the paper leaves both points open
                               (Section 2 names returns and recoverable stock without the rules):
                               bit 1 (strict): a period whose latest setup is remanufacturing only must be
