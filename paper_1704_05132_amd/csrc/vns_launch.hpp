@@ -83,8 +83,8 @@ hipError_t launch_mlp_pack(const float *P, void *packed, hipStream_t s);
 // Gradient (and loss in grad_out[5313]) of the mean squared error over rows idx[0..n) (all rows when idx is
 // null): forward and backward on the matrix cores, one partial per wavefront in part
 // [mlp_grad_partials(n)][5314], then their fixed-order sum.
-hipError_t launch_mlp_grad(const float *P, const void *packed, const float *X, const float *y, const int64_t *idx, int64_t n,
-                           float *part, float *grad_out, hipStream_t s);
+hipError_t launch_mlp_grad(const float *P, const float *X, const float *y, const int64_t *idx, int64_t n, float *part,
+                           float *grad_out, hipStream_t s);
 int64_t mlp_grad_partials(int64_t n);
 // Training rows of a minibatch: row r of it is (mul (start + r) + add) mod n of the training set.
 struct RowPerm {
@@ -93,7 +93,7 @@ struct RowPerm {
 };
 // One training step (Adam step number `step`): the gradient of the minibatch's cnt rows (partials in part,
 // sized for mlp_grad_partials(cnt)), then in one kernel their fixed-order sum into grad_out (loss at
-// [5313]) and the Adam update of P, m, v.
+// [5313]) and the Adam update of P, m, v (and of packed, which may be null: the weights are gathered from P then).
 hipError_t launch_mlp_train_step(float *P, void *packed, float *m, float *v, const float *X, const float *y,
                                  const RowPerm &perm, int64_t cnt, float *part, float *grad_out, float lr, int64_t step,
                                  hipStream_t s);

@@ -87,7 +87,9 @@ constexpr int kGradLd = 64 + 8;   // padded row (bfloat16) of the transposed til
 
 // The gradient kernel's weight fragments, laid out as its lanes hold them (bfloat16, 16 bytes per lane and fragment):
 // w1t[mt], w2t[mt][kt] as in Frags, then w2b[mi][kt], the A fragments of W2 for W2 dz2.  Gathered from the parameters they
-// were 96 strided loads per lane, a few at a time between the registers' other uses, and most of a one-tile launch.
+// were 96 strided loads per lane, a few at a time between the registers' other uses.  Packing is a launch of its own, so a call
+// with one gradient or one training step gathers them itself (64 rows: 48 us a gradient call against 63 packed; two steps 95
+// gathered against 83 packed, 64 steps 1.30 ms against 0.90).
 constexpr int kPkW2t = 4 * 512, kPkW2b = kPkW2t + 8 * 512;
 static_assert(kPkW2b + 8 * 512 == kPackedWeights, "packed weights");
 
@@ -122,6 +124,7 @@ __device__ __forceinline__ int64_t perm_row(const RowPerm &perm, int64_t r) {
     return (int64_t)(((unsigned __int128)perm.mul * i + perm.add) % n);
 }
 
+template <bool PACKED>
 __global__ __launch_bounds__(64) void k_mlp_grad(const float *__restrict__ P, const __bf16 *__restrict__ pk,
                                                  const float *__restrict__ X,
                                                  const float *__restrict__ y, const int64_t *__restrict__ idx,
@@ -134,22 +137,33 @@ __global__ __launch_bounds__(64) void k_mlp_grad(const float *__restrict__ P, co
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     Frags fr;
     bf8 w2b[4][2];   // A fragments of W2 for W2 dz2: rows i = 16 mi + c, inputs j in the order pi(kt, 8g + e)
-    const bf8 *pf = reinterpret_cast<const bf8 *>(pk) + lane;
+    if constexpr (PACKED) {
+        const bf8 *pf = reinterpret_cast<const bf8 *>(pk) + lane;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-        fr.w1t[mt] = pf[mt * 64];
+        for (int mt = 0; mt < 4; ++mt) {
+            fr.w1t[mt] = pf[mt * 64];
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
-            fr.w2t[mt][kt] = pf[(kPkW2t / 8) + (mt * 2 + kt) * 64];
-            w2b[mt][kt] = pf[(kPkW2b / 8) + (mt * 2 + kt) * 64];
+            for (int kt = 0; kt < 2; ++kt) {
+                fr.w2t[mt][kt] = pf[(kPkW2t / 8) + (mt * 2 + kt) * 64];
+                w2b[mt][kt] = pf[(kPkW2b / 8) + (mt * 2 + kt) * 64];
+            }
+            fr.b1[mt] = *reinterpret_cast<const f4 *>(P + oB1 + 16 * mt + 4 * g);
+            fr.b2[mt] = *reinterpret_cast<const f4 *>(P + oB2 + 16 * mt + 4 * g);
+            const f4 w3 = *reinterpret_cast<const f4 *>(P + oW3 + 16 * mt + 4 * g);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) fr.w3[mt][e >> 1][e & 1] = (__bf16)w3[e];
         }
-        fr.b1[mt] = *reinterpret_cast<const f4 *>(P + oB1 + 16 * mt + 4 * g);
-        fr.b2[mt] = *reinterpret_cast<const f4 *>(P + oB2 + 16 * mt + 4 * g);
-        const f4 w3 = *reinterpret_cast<const f4 *>(P + oW3 + 16 * mt + 4 * g);
+        fr.b3 = P[oB3];
+    } else {
+        load_frags(P, fr);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) fr.w3[mt][e >> 1][e & 1] = (__bf16)w3[e];
+        for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    w2b[mi][kt][e] = (__bf16)P[oW2 + (16 * mi + c) * kH + 32 * kt + 16 * (e >> 2) + 4 * g + (e & 3)];
     }
-    fr.b3 = P[oB3];
     const f4 z4 = {0.f, 0.f, 0.f, 0.f};
     const bf8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
     f4 gW2[4][4];                  // [mi][nj]: dW2[16 mi + 4g + e][16 nj + c]
@@ -364,7 +378,7 @@ __global__ __launch_bounds__(64) void k_mlp_reduce_adam(const float *__restrict_
     v[e] = vv;
     const float p = P[e] - lr * (mm / corr1) / (sqrtf(vv / corr2) + eps);
     P[e] = p;
-    put_packed(pk, e, p);
+    if (pk) put_packed(pk, e, p);
 }
 
 }  // namespace mlp
@@ -382,12 +396,21 @@ hipError_t launch_mlp_pack(const float *P, void *packed, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_grad(const float *P, const void *packed, const float *X, const float *y, const int64_t *idx, int64_t n,
-                           float *part, float *grad_out, hipStream_t s) {
+static void launch_grad(int64_t nb, const float *P, const void *packed, const float *X, const float *y, const int64_t *idx,
+                        const RowPerm &perm, int64_t n, float *part, hipStream_t s) {
+    const dim3 grid((unsigned)nb), block(64);
+    const float inv_n = 1.f / (float)n;
+    if (packed)
+        hipLaunchKernelGGL(mlp::k_mlp_grad<true>, grid, block, 0, s, P, (const __bf16 *)packed, X, y, idx, perm, n, inv_n, part);
+    else
+        hipLaunchKernelGGL(mlp::k_mlp_grad<false>, grid, block, 0, s, P, nullptr, X, y, idx, perm, n, inv_n, part);
+}
+
+hipError_t launch_mlp_grad(const float *P, const float *X, const float *y, const int64_t *idx, int64_t n, float *part,
+                           float *grad_out, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const int64_t nb = mlp_grad_partials(n);
-    hipLaunchKernelGGL(mlp::k_mlp_grad, dim3((unsigned)nb), dim3(64), 0, s, P, (const __bf16 *)packed, X, y, idx, RowPerm{0, 0, 0, 0}, n,
-                       1.f / (float)n, part);
+    launch_grad(nb, P, nullptr, X, y, idx, RowPerm{0, 0, 0, 0}, n, part, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(mlp::k_mlp_reduce, dim3((mlp::kParams + 1 + 63) / 64), dim3(64), 0, s, part, nb, grad_out);
@@ -401,8 +424,7 @@ hipError_t launch_mlp_train_step(float *P, void *packed, float *m, float *v, con
                                  hipStream_t s) {
     if (cnt <= 0) return hipSuccess;
     const int64_t nb = mlp_grad_partials(cnt);
-    hipLaunchKernelGGL(mlp::k_mlp_grad, dim3((unsigned)nb), dim3(64), 0, s, P, (const __bf16 *)packed, X, y, nullptr, perm, cnt,
-                       1.f / (float)cnt, part);
+    launch_grad(nb, P, packed, X, y, nullptr, perm, cnt, part, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const float b1 = 0.9f, b2 = 0.999f;

@@ -172,7 +172,7 @@ struct vns_ctx {
     // scorer calls: device copies of the caller's rows, targets and scores and the gradient's scratch, kept between calls
     // up to kScorerKeep bytes each
     float *d_x = nullptr, *d_y = nullptr, *d_s = nullptr, *d_part = nullptr, *d_grad = nullptr;
-    uint16_t *d_packed = nullptr;         // the gradient kernel's copy of the weights, made at each call's start
+    uint16_t *d_packed = nullptr;         // the gradient kernel's copy of the weights, made by each training call of several steps
     size_t cap_x = 0, cap_y = 0, cap_s = 0, cap_part = 0;
 
     hipStream_t own_stream = nullptr, stream = nullptr;
@@ -1631,7 +1631,6 @@ static vns_status scorer_data(vns_ctx *c, const float *feats, const float *targe
     VNS_HIP(c, hipMemcpyAsync(c->d_y, targets, sizeof(float) * (size_t)n, hipMemcpyHostToDevice, c->stream));
     VNS_HIP(c, scorer_buf(c->d_part, c->cap_part, (size_t)(mlp_grad_partials(batch) * (mlp::kParams + 1))));
     if (!c->d_grad) VNS_HIP(c, dmalloc(&c->d_grad, (size_t)(mlp::kParams + 1)));
-    if (!c->d_packed) VNS_HIP(c, dmalloc(&c->d_packed, (size_t)mlp::kPackedWeights));
     return VNS_OK;
 }
 
@@ -1659,8 +1658,7 @@ extern "C" vns_status vns_mlp_grad(vns_ctx *c, const float *feats, const float *
     vns_status st = scorer_data(c, feats, targets, n, n);
     if (st != VNS_OK) return st;
     VNS_HIP(c, hipEventRecord(c->ev0, c->stream));
-    VNS_HIP(c, launch_mlp_pack(c->d_mlp, c->d_packed, c->stream));
-    VNS_HIP(c, launch_mlp_grad(c->d_mlp, c->d_packed, c->d_x, c->d_y, nullptr, n, c->d_part, c->d_grad, c->stream));
+    VNS_HIP(c, launch_mlp_grad(c->d_mlp, c->d_x, c->d_y, nullptr, n, c->d_part, c->d_grad, c->stream));
     VNS_HIP(c, hipEventRecord(c->ev1, c->stream));
     float *g = reinterpret_cast<float *>(c->h_stage);
     VNS_HIP(c, hipMemcpyAsync(g, c->d_grad, sizeof(float) * (mlp::kParams + 1), hipMemcpyDeviceToHost, c->stream));
@@ -1678,6 +1676,10 @@ extern "C" vns_status vns_mlp_train(vns_ctx *c, const float *feats, const float 
     ScorerCall guard{c};
     vns_status st = scorer_data(c, feats, targets, n, bmax);
     if (st != VNS_OK) return st;
+    // a single step gathers the weights itself; for more they are packed once, and every step keeps them so
+    const bool steps = epochs > 1 || (epochs == 1 && bmax < n);
+    if (steps && !c->d_packed) VNS_HIP(c, dmalloc(&c->d_packed, (size_t)mlp::kPackedWeights));
+    void *packed = steps ? c->d_packed : nullptr;
     // rows of each epoch in the order (mul * i + add) mod n, mul coprime to n, add drawn per epoch
     uint64_t mul = 1000003ull;
     auto gcd = [](uint64_t a, uint64_t b) { while (b) { uint64_t t = a % b; a = b; b = t; } return a; };
@@ -1685,14 +1687,14 @@ extern "C" vns_status vns_mlp_train(vns_ctx *c, const float *feats, const float 
     uint64_t state = seed * 0x9E3779B97F4A7C15ull + 1;
     float loss = 0.f;
     VNS_HIP(c, hipEventRecord(c->ev0, c->stream));
-    VNS_HIP(c, launch_mlp_pack(c->d_mlp, c->d_packed, c->stream));
+    if (packed) VNS_HIP(c, launch_mlp_pack(c->d_mlp, packed, c->stream));
     for (int32_t e = 0; e < epochs; ++e) {
         state ^= state >> 33; state *= 0xFF51AFD7ED558CCDull; state ^= state >> 33;
         const uint64_t add = state % (uint64_t)n;
         for (int64_t s0 = 0; s0 < n; s0 += bmax) {
             const int64_t cnt = std::min<int64_t>(bmax, n - s0);
             // the minibatch's rows (mul i + add) mod n, i = s0 .. s0 + cnt - 1, are computed in the gradient kernel
-            VNS_HIP(c, launch_mlp_train_step(c->d_mlp, c->d_packed, c->d_adam_m, c->d_adam_v, c->d_x, c->d_y, RowPerm{mul, add, s0, n}, cnt,
+            VNS_HIP(c, launch_mlp_train_step(c->d_mlp, packed, c->d_adam_m, c->d_adam_v, c->d_x, c->d_y, RowPerm{mul, add, s0, n}, cnt,
                                              c->d_part, c->d_grad, lr, ++c->adam_step, c->stream));
         }
     }
