@@ -153,13 +153,18 @@ enum vns_option {
                               = one product per wavefront at a time.  Moves, prices, records and counted
                               evaluations are the same.  The workgroup then needs 2 KB of LDS per
                               wavefront and 2.1 KB per product                                       */
-    VNS_OPT_EVAL_SPREAD = 21 /* vns_eval_neighbourhood's launch shape: W in {4, 8, 12, 16} = the (chain,
+    VNS_OPT_EVAL_SPREAD = 21, /* vns_eval_neighbourhood's launch shape: W in {4, 8, 12, 16} = the (chain,
                               product) pairs of each instance, product by product, are split into
                               near-equal ranges, 24 / W workgroups of W wavefronts per compute unit
                               (one for W = 16), each pricing every move of its range (a range spans a
                               few products when their rows fit its LDS); 0 (default) = one workgroup
                               per product and group of VNS_OPT_EVAL_GROUP chains.  Same prices and
                               argmins.  Not used with incremental or interval pricing                 */
+    VNS_OPT_INTERVAL = 22  /* read only (setting it is VNS_EINVAL): 1 = interval pricing applies to this context
+                              now (see VNS_OPT_EVAL_GROUP): vns_eval_neighbourhood, its allocation-free form,
+                              and the plain and the learned search without move log, speculative VND or
+                              packing run by it; one product past its bounds puts the whole context on the
+                              full decode                                                             */
 };
 
 /* One GVNS iteration of one chain. */

@@ -5,8 +5,8 @@ chain's products run their VND side by side), whether the neighbourhoods of one 
 side by side by a group of wavefronts (speculative VND, `spec`) and how much LDS it may use to keep an
 instance's rows resident trade occupancy against parallelism, and the best choice depends on K, T and the
 number of chains.  The pricing kernel's tuning knob is how many chains of an instance share one workgroup, or the
-range form with its wavefronts per workgroup (`spread`: the pairs split evenly over the compute units).  Results
-never depend on these choices (the kernels compute the same exact costs and trajectories); only time does.
+range form with its wavefronts per workgroup (`spread`: the pairs split evenly over the compute units); interval
+pricing, where it applies, uses neither.  Results never depend on these choices (the kernels compute the same exact costs and trajectories); only time does.
 
 `tune_search` and `tune_eval` time each candidate on the actual workload with the library's own device
 timers and return the fastest; `TuneTable` persists choices per workload signature in JSON.
@@ -97,8 +97,13 @@ def eval_options(c: dict) -> dict:
 
 
 def tune_eval(ctx, nb_mask: int = 7, reps: int = 5, candidates: Sequence[dict] = tuple(EVAL_CANDIDATES)):
-    """Median device time of a full pricing sweep of every chain of ctx for each pricing launch shape."""
+    """Median device time of a full pricing sweep of every chain of ctx for each pricing launch shape.  Interval pricing
+    has a launch shape of its own, which these options do not change: there ctx keeps its own choice, timed once."""
     from . import vns
+
+    if ctx.get_option(vns.OPT_INTERVAL):
+        spread = ctx.get_option(vns.OPT_EVAL_SPREAD)
+        candidates = [dict(spread=spread) if spread else dict(group=ctx.get_option(vns.OPT_EVAL_GROUP))]
 
     def measure(c):
         for opt, v in eval_options(c).items():

@@ -539,6 +539,9 @@ extern "C" void vns_destroy(vns_ctx *c) {
     delete c;
 }
 
+// Interval pricing applies: every product is compact and the reading has no disposal.
+static bool by_interval(const vns_ctx *c) { return c->compact && !(c->model & kModelDispose); }
+
 // ---------------------------------------------------------------------------------------------------
 // options
 // ---------------------------------------------------------------------------------------------------
@@ -655,6 +658,8 @@ extern "C" vns_status vns_set_option(vns_ctx *c, int32_t key, int64_t v) {
             c->log_cap = v;
             return VNS_OK;
         }
+        case VNS_OPT_INTERVAL:
+            return fail(c, VNS_EINVAL, "whether interval pricing applies can only be read");
         default:
             return fail(c, VNS_EINVAL, "unknown option");
     }
@@ -684,6 +689,7 @@ extern "C" vns_status vns_get_option(const vns_ctx *c, int32_t key, int64_t *v) 
         case VNS_OPT_EVAL_INCREMENTAL: *v = c->eval_inc; return VNS_OK;
         case VNS_OPT_DECODE: *v = c->model; return VNS_OK;
         case VNS_OPT_LOG: *v = c->log_cap; return VNS_OK;
+        case VNS_OPT_INTERVAL: *v = by_interval(c) ? 1 : 0; return VNS_OK;
         default: return fail(const_cast<vns_ctx *>(c), VNS_EINVAL, "unknown option");
     }
 }
@@ -888,7 +894,7 @@ extern "C" vns_status vns_eval_neighbourhood(vns_ctx *c, uint32_t nb_mask, int32
         vns_status s = ws_check(c, &wl);
         if (s != VNS_OK) return s;
     }
-    const bool interval = c->compact && !(c->model & kModelDispose);
+    const bool interval = by_interval(c);
     EvalOut out(slot_price, prod_best, prod_best_slot, best, best_slot, ng, n_cp);
     // (only interval pricing writes every slot once; the full decode clears them first)
     if (slot_price && interval) out.o_sp = out.place(sizeof(int64_t) * (size_t)n_slots);
@@ -1075,7 +1081,7 @@ extern "C" vns_status vns_eval_neighbourhood_noalloc(vns_ctx *c, uint32_t nb_mas
     pa.table = tab;
     pa.counters = ctr;
     // interval pricing has no table, and counts into the context's own counters
-    const bool interval = c->compact && !(c->model & kModelDispose);
+    const bool interval = by_interval(c);
     if (!interval) VNS_HIP(c, launch_eval_prep(pa, c->stream));
     EvalOut out(slot_price, prod_best, prod_best_slot, best, best_slot, ng, n_cp);
     if (slot_price && interval) out.o_sp = out.place(sizeof(int64_t) * (size_t)n_slots);
@@ -1172,8 +1178,7 @@ extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
     for (int32_t i = 0; i < c->n_inst; ++i) min_T = std::min<int32_t>(min_T, c->T[(size_t)i]);
     // interval pricing where it applies (its VND keeps no move log); otherwise full decodes, with the variant for
     // batches with a short horizon in the one-workgroup search
-    const bool interval = (kind == RunKind::kPlain || kind == RunKind::kLearned) && c->compact &&
-                          !(c->model & kModelDispose) && ra.log_x == nullptr;
+    const bool interval = (kind == RunKind::kPlain || kind == RunKind::kLearned) && by_interval(c) && ra.log_x == nullptr;
     const bool long_T = c->max_T > 64;
     const RunKind coop_k = !interval                   ? kind
                            : kind == RunKind::kLearned ? (long_T ? RunKind::kLearnedIntervalLong : RunKind::kLearnedInterval)

@@ -59,3 +59,40 @@ def test_candidates_cover_both_search_kernels():
             assert "iters" not in c   # speculative iterations run the one-wavefront-per-product VND
         assert 1 <= c.get("iters", 1) <= 16
     assert any(c.get("iters", 1) > 1 for c in autotune.SEARCH_CANDIDATES)
+
+
+class PricingContext:
+    """What tune_eval uses of a context."""
+
+    def __init__(self, vns, interval, options={}):
+        self.ms = iter([0.9, 0.5] * 1000)   # whatever is set, the times differ
+        self.options = {vns.OPT_INTERVAL: interval, vns.OPT_EVAL_SPREAD: 0, vns.OPT_EVAL_GROUP: 4, **options}
+
+    def get_option(self, key):
+        return self.options[key]
+
+    def set_option(self, key, value):
+        self.options[key] = value
+
+    def eval_neighbourhood(self, nb_mask, chain, slot_prices):
+        pass
+
+    def stats(self):
+        return {"last_eval_ms": next(self.ms)}
+
+
+def test_tune_eval_keeps_the_choice_of_interval_pricing():
+    from paper_1704_05132_amd import vns
+    for options, choice in (({}, {"group": 4}), ({vns.OPT_EVAL_SPREAD: 8}, {"spread": 8})):
+        ctx = PricingContext(vns, 1, options)
+        best, timings = autotune.tune_eval(ctx, reps=1)
+        assert best == choice and [c for c, _ in timings] == [choice]
+        assert ctx.get_option(vns.OPT_EVAL_SPREAD) == choice.get("spread", 0)
+        assert ctx.get_option(vns.OPT_EVAL_GROUP) == 4
+
+
+def test_tune_eval_times_every_shape_of_the_full_decode():
+    from paper_1704_05132_amd import vns
+    best, timings = autotune.tune_eval(PricingContext(vns, 0), reps=1)
+    assert [c for c, _ in timings] == autotune.EVAL_CANDIDATES
+    assert best == autotune.EVAL_CANDIDATES[1]   # the first of the fastest

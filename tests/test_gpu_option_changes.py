@@ -35,3 +35,21 @@ def test_k_max_lowered_below_a_chains_k(vns, K, T, low, form):
                 assert (ctx.trajectory(g) == c.run(n)).all(), g
                 zM, zR = ctx.solution(g)
                 assert (zM == c.zM).all() and (zR == c.zR).all(), g
+
+
+def test_whether_interval_pricing_applies(vns):
+    inst = draw_instance(np.random.default_rng(3), 4, 20)
+    with vns.Context(inst, seed=1) as ctx:
+        assert ctx.get_option(vns.OPT_INTERVAL) == 1
+        for value in (0, 1):
+            with pytest.raises(vns.VNSError) as e:
+                ctx.set_option(vns.OPT_INTERVAL, value)
+            assert e.value.status == vns.VNS_EINVAL
+        for reading, applies in ((vns.DECODE_DISPOSE, 0), (vns.DECODE_STRICT, 1), (3, 0), (0, 1)):
+            ctx.set_option(vns.OPT_DECODE, reading)
+            assert ctx.get_option(vns.OPT_INTERVAL) == applies
+        ctx.set_unit_costs(np.full(4, 60000), np.zeros(4))   # some 2000 units at 60000: still below 2^31
+        assert ctx.get_option(vns.OPT_INTERVAL) == 1
+    inst.kM[2] = 200_000_000   # twenty setups: 4e9
+    with vns.Context([inst, draw_instance(np.random.default_rng(4), 3, 12)], seed=1) as ctx:
+        assert ctx.get_option(vns.OPT_INTERVAL) == 0
