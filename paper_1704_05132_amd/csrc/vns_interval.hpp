@@ -11,7 +11,7 @@
 //     left over), at most one of them positive, turns d into min(d + c, E), and the difference is made at its
 //     own periods instead, weight w per unit.  |d| never grows and most moves are done after one or two;
 //   * the shortfalls up to the next manufacturing setup M1, when the move changes which period makes them.
-// One lane holds one period (two for T > 63): the pattern's own states come from five wavefront scans, and every
+// One lane holds one period (two for T > 64): the pattern's own states come from five wavefront scans, and every
 // move of the lane's period is then priced from registers, one 8-byte record of the next setup and of M1, and
 // the remanufacturing intervals' records {c, E, w, period} in LDS.
 //

@@ -153,7 +153,7 @@ struct vns_ctx {
     unsigned long long *d_log_n = nullptr;
     hipGraph_t graph = nullptr;           // captured search launch (VNS_OPT_GRAPH)
     hipGraphExec_t graph_exec = nullptr;
-    int64_t graph_key[5] = {-1, -1, -1, -1, -1};  // (iters, chains, waves, LDS bytes, trace buffer)
+    int64_t graph_key[5] = {-1, -1, -1, -1, -1};  // (iters, chains, waves and kernel, LDS bytes, trace buffer)
     EvalWg *d_eval_wg = nullptr;          // k_eval workgroup table of the last chain range priced
     int64_t eval_wg_n = 0;
     int64_t eval_wg_key[4] = {-1, -1, -1, -1};  // (first chain, number of chains, group size, form: 1
@@ -1300,7 +1300,7 @@ extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
         VNS_HIP(c, hipEventRecord(c->ev0, c->stream));
         VNS_HIP(c, launch_run_coop(ra, (int)G, waves, lds_coop, c->stream, coop_k, c->model));
     } else if (c->use_graph) {
-        const int64_t key[5] = {iters, G, waves * 8 + (int64_t)run_k, (int64_t)lds, (int64_t)(intptr_t)ra.trace};
+        const int64_t key[5] = {iters, G, waves * 16 + (int64_t)run_k, (int64_t)lds, (int64_t)(intptr_t)ra.trace};
         bool same = true;
         for (int i = 0; i < 5; ++i) same = same && key[i] == c->graph_key[i];
         if (!same || !c->graph_exec) {
