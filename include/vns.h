@@ -73,13 +73,18 @@ enum vns_option {
                               has its own launch shape                                                 */
     VNS_OPT_RUN_LDS = 7,   /* bytes of LDS the search kernel may use to keep an instance's rows resident,
                               0..131072 (default 65536); a tuning knob, results do not depend on it     */
-    VNS_OPT_GRAPH = 8,     /* 1 = vns_run captures its launch (search kernel + iteration-counter advance)
-                              in a HIP graph once per (iters, layout) and replays it (default 0); needs a
-                              stream other than the legacy default stream                               */
+    VNS_OPT_GRAPH = 8,     /* 1 = vns_run captures its search kernel in a HIP graph once per (iters, layout)
+                              and replays it (default 0); the iteration counter advances, and the counts
+                              are summed, by a launch of its own after each replay.  Needs a stream other
+                              than the legacy default stream                                            */
     VNS_OPT_LEARNED = 9,   /* 0 = plain VND; p in 1..1000 = learned VND: in every neighbourhood evaluation
                               the scorer ranks the moves, the best-ranked ceil(p*n/1000) are priced
                               exactly and the best of them is applied if it improves, otherwise the whole
-                              neighbourhood is priced exactly and its best move applied if it improves   */
+                              neighbourhood is priced exactly and its best move applied if it improves.
+                              Interval pricing (VNS_OPT_INTERVAL) has every move's price before any score
+                              and computes the scores only where a move improves, as the choice depends on
+                              them only there: the same moves, and the evaluations of the rule above are
+                              what is counted                                                           */
     VNS_OPT_LOG = 10,      /* move-log capacity in records (0 = off, default); a plain vns_run appends, for
                               every applied move, its features and cost change and those of one other
                               priced move of the same evaluation                                       */
@@ -152,7 +157,9 @@ enum vns_option {
                               in shared passes and their fallbacks in shared passes; 0 or 1 (default 0)
                               = one product per wavefront at a time.  Moves, prices, records and counted
                               evaluations are the same.  The workgroup then needs 2 KB of LDS per
-                              wavefront and 2.1 KB per product                                       */
+                              wavefront and 2.1 KB per product.  The packed form prices by full decodes
+                              and forgoes interval pricing, which is about three times as fast where it
+                              applies (VNS_OPT_INTERVAL)                                              */
     VNS_OPT_EVAL_SPREAD = 21, /* vns_eval_neighbourhood's launch shape: W in {4, 8, 12, 16} = the (chain,
                               product) pairs of each instance, product by product, are split into
                               near-equal ranges, 24 / W workgroups of W wavefronts per compute unit
@@ -210,7 +217,11 @@ typedef struct vns_stats {
  *   kM, kR, hM, hR: [K] int32, all >= 0.
  *   seed: Philox key word 0 for every chain (word 1 is the chain index).
  * The context starts with 1 chain whose solution is zM = 1, zR = 0 (every period manufactures its own
- * demand), shake size 1, iteration 0.  Returns VNS_ERANGE if a product's cost or the int32 accumulators of
+ * demand), shake size 1, iteration 0.  Besides device memory it holds 256 KB of pinned host memory, through
+ * which small results return, and after a scorer call (vns_mlp_score / _grad / _train) up to 64 MB each of
+ * device memory for rows, targets, scores and gradient partials, kept for the next one; vns_destroy frees all.
+ * Threads may read one context (costs, solutions, records) side by side; calls that change it are the
+ * caller's to order.  Returns VNS_ERANGE if a product's cost or the int32 accumulators of
  * the decode could overflow (per product: sum(D)*T and sum(R)*T must stay below 2^31, the worst-case cost
  * below 2^47).  *out receives the context (NULL on error).
  */
@@ -256,8 +267,9 @@ vns_status vns_bind_stream(vns_ctx *ctx, void *hip_stream);
  *   VNS_WS_RUN          vns_run's speculative-iteration and best-of-G buffers (per chain a 128-byte control
  *                       line, per chain and slot a summary and 40 bytes per product), sized for the current
  *                       VNS_OPT_SPEC_ITERS / VNS_OPT_BEST_OF; nothing when neither is on;
- *   VNS_WS_EVAL         vns_eval_neighbourhood's table of pricing workgroups (40 bytes per (chain, product),
- *                       the most any chain range or VNS_OPT_EVAL_GROUP needs);
+ *   VNS_WS_EVAL         vns_eval_neighbourhood's table of pricing workgroups (48 bytes per (chain, product),
+ *                       the most any chain range or VNS_OPT_EVAL_GROUP needs; interval pricing has none,
+ *                       and the size is the same);
  *   VNS_WS_EVAL_PRICES  as VNS_WS_EVAL, plus the staging of slot prices for every chain (8 bytes per slot).
  * vns_workspace_bytes — bytes a workspace bound with `flags` must have under the current options (0 for no
  * flags).  vns_bind_workspace — bind `dev_ptr` (device memory of the context's device, 256-byte aligned,
@@ -294,14 +306,15 @@ vns_status vns_eval_neighbourhood(vns_ctx *ctx, uint32_t nb_mask, int32_t chain,
  * vns_eval_neighbourhood_noalloc — for callers that cannot allocate memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid allocation): the same pricing as vns_eval_neighbourhood, with
  * the same arguments, outputs (host pointers) and results, but it allocates nothing, on the device or on the
- * host.  Its scratch (evaluation counters, per-product argmin keys, the table of pricing workgroups, built on
- * the device, and the slot-price staging) lives in one static 8 MiB device array per GPU, held until the
- * process ends.  Limits: 56 bytes per (chain, product) priced, plus 8 bytes per slot when slot_price is
+ * host.  Its scratch (per-product argmin keys and the slot-price staging; by full decodes also the evaluation
+ * counters and the table of pricing workgroups, built on the device) lives in one static 8 MiB device array
+ * per GPU, held until the process ends; results of up to 256 KB pass through the context's pinned buffer.  Limits: 56 bytes per (chain, product) priced, plus 8 bytes per slot when slot_price is
  * requested, plus 16 KiB, within the 8 MiB (for example every slot of one chain of 300 x 52, or the argmins
  * of 64 chains of 100 x 52); a larger request returns VNS_EINVAL without running.  Every call on a GPU shares
  * that GPU's array and it keeps the last call's contents (the call clears what must start at zero): calls
- * that overlap on one GPU, from several threads or streams, race.  It always decodes every move in full
- * (VNS_OPT_EVAL_INCREMENTAL is not used); prices and counted evaluations equal vns_eval_neighbourhood's.
+ * that overlap on one GPU, from several threads or streams, race.  It prices as vns_eval_neighbourhood does, by
+ * intervals or full decodes (VNS_OPT_INTERVAL), and the limits are the same for both; VNS_OPT_EVAL_INCREMENTAL
+ * is not used.  Prices and counted evaluations equal vns_eval_neighbourhood's.
  */
 vns_status vns_eval_neighbourhood_noalloc(vns_ctx *ctx, uint32_t nb_mask, int32_t chain, int64_t *slot_price,
                                           int64_t *prod_best, int32_t *prod_best_slot, int64_t *best,
@@ -319,7 +332,7 @@ vns_status vns_run(vns_ctx *ctx, int32_t iters);
 vns_status vns_get_cost(vns_ctx *ctx, int32_t chain, int64_t *F, int64_t *F_best);
 
 /* vns_get_costs — F and the best objective of every chain, [vns_num_chains] int64 each (either may be
- * NULL): one device-to-host copy instead of one call per chain. */
+ * NULL): one call instead of one per chain. */
 vns_status vns_get_costs(vns_ctx *ctx, int64_t *F, int64_t *F_best);
 
 /*

@@ -15,13 +15,14 @@
 // move of the lane's period is then priced from registers, one 8-byte record of the next setup and of M1, and
 // the remanufacturing intervals' records {c, E, w, period} in LDS.
 //
-// What bounds it: VALU issue (97% of the issue slots in the 256 x 16 sweep).  A full decode costs every move 14 T
-// operations (728 at T = 52); here the scans and records are about 130 instructions per pattern, a move takes
-// 20 to 35, and four records of a walk 22 to 30, of which the slowest of 64 lanes needs 2 to 3 rounds (1.3 records on
-// average; local optima, T = 52): 500 instructions for a pattern's 156 slots in place of 2000.  Best move of every
-// pattern of 256 instances (K 100..1000, T 52 or 104) x 16 chains: 15.9 -> 2.78 ms; of 1024 instances (K 10..200, T
-// 12, 24 or 52) x 8: 1.18 -> 0.43 ms.  Short horizons share a wavefront (16 or 32 lanes per pattern), which halves the
-// instructions per pattern at T = 24 and quarters them at T = 12.
+// What bounds it: VALU issue.  The sweep of 1024 instances (K 100..1000, T 52 or 104) x 16 chains issues 6.9e9 VALU
+// instructions in 10.7 ms, 1.05 per SIMD and four cycles (a part of them at the double rate) with 58% of their lanes
+// enabled.  A full decode costs every move 14 T operations (728 at T = 52); here the scans and records are about 130
+// instructions per pattern, a move takes 20 to 35, and four records of a walk 22 to 30, of which the slowest of 64 lanes
+// needs 2 to 3 rounds (1.3 records on average; local optima, T = 52): 600 VALU instructions for a pattern's 156 slots in
+// place of 2000.  Best move of every pattern of 256 instances (K 100..1000, T 52 or 104) x 16 chains: 15.9 -> 2.78 ms; of
+// 1024 instances (K 10..200, T 12, 24 or 52) x 8: 1.18 -> 0.43 ms.  Short horizons share a wavefront (16 or 32 lanes per
+// pattern), which halves the instructions per pattern at T = 24 and quarters them at T = 12.
 //
 // Integers: for a "compact" product (compact_product below: sums of demand and returns, weights and unit terms
 // below 2^23, worst-case cost below 2^31) every product here has two signed 24-bit factors and every sum is

@@ -445,8 +445,7 @@ __global__ __launch_bounds__(256) void k_eval_inc(EvalArgs a, const EvalWg *__re
 // blocks of each with one period per lane.  No workgroup synchronisation and no move list: a slot is (block,
 // lane).
 //
-// Bound by VALU issue: at 256 instances (K 100..1000, T 52 or 104) x 16 chains 2.78 ms in place of 15.9 (k_eval, 97% of
-// the issue slots in both), at 1024 instances (K 10..200, T 12, 24 or 52) x 8 chains 0.43 in place of 1.18, at one of
+// Bound by VALU issue, as k_eval: at 256 instances (K 100..1000, T 52 or 104) x 16 chains 2.78 ms in place of 15.9, at 1024 instances (K 10..200, T 12, 24 or 52) x 8 chains 0.43 in place of 1.18, at one of
 // 100 x 52 with 64 chains 14 us in place of 32.
 // ---------------------------------------------------------------------------------------------------
 namespace {
@@ -1008,9 +1007,9 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
                 nd = __popcll(okm);
             } else {
                 // products still are independent of each other: the first lane that drew a product resolves its draws
-                // in order, each kept if it leaves the product feasible.  (One draw after the other, by the whole
-                // wavefront, took 2890 cycles a shake on average in a 10-product instance, where most shakes of three
-                // and more meet a product twice, and 2450 so: its search 2.63 -> 2.52 ms for 500 iterations.)
+                // in order, each kept if it leaves the product feasible.  (In place of one draw after the other by the
+                // whole wavefront: the search of a 10-product instance, where most shakes of three and more meet a
+                // product twice, 2.63 -> 2.52 ms for 500 iterations.)
                 uint64_t own = 0;   // the draws of this lane's product
                 for (int j = 0; j < kshake; ++j) own |= (uint64_t)(__builtin_amdgcn_readlane(pd, j) == pd ? 1u : 0u) << j;
                 int first = -1;     // the first draw that stays
@@ -1795,9 +1794,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 // The plain search with interval pricing (contexts of compact products, no move log), one workgroup per chain and
 // with speculative iterations or best-of-G.  IV: 1 when every horizon is at most 64, else 2.
 //
-// Bound by a lone wavefront's instruction issue (about 5 cycles each) and LDS waits along one product's VND: 1.65
-// patterns of 650 cycles, 2.4 neighbourhoods of 680 (T = 12) to 1060 (T = 52) and 1800 of control, then the shake (1700)
-// and the acceptance (1500).  Full decodes -> interval pricing: 500 iterations of 10 x 12 4.66 -> 2.4 ms; 512 instances
+// Bound by a lone wavefront's instruction issue and LDS waits along the chain of shake, one product's VND and acceptance
+// (100 x 52, 64 chains side by side: 17% of the chip's VALU issue).  Full decodes -> interval pricing: 500 iterations of 10 x 12 4.66 -> 2.4 ms; 512 instances
 // (K 10..200, T 12, 24 or 52) x 8 chains x 50 5.4 -> 1.17 ms; 64 instances (T 52 or 104) x 16 7.2 -> 0.83 ms; with
 // speculative iterations 100 x 52, 64 chains x 200 1.46 -> 0.65 ms under the profiler; best of 4, 300 x 52 2.2 -> 0.87 ms.
 // Four wavefronts per SIMD for one period a lane, three for two: at four the two-word form spills.

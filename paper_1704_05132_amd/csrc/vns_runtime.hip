@@ -1029,9 +1029,10 @@ extern "C" vns_status vns_eval_neighbourhood(vns_ctx *c, uint32_t nb_mask, int32
     return finish_eval(c, out, g0, ng, cp_begin, n_cp, n_slots, c->d_prod_key, c->d_evals, d_sp);
 }
 
-// The same pricing with its scratch in the per-GPU static array: no device or host allocation.  The table
-// of pricing workgroups is built on the device (one entry per (chain, product), empty for chains that do
-// not lead a group), and every move is decoded in full.
+// The same pricing with its scratch in the per-GPU static array: no device or host allocation.  By full decodes, the
+// table of pricing workgroups is built on the device (one entry per (chain, product), empty for chains that do not lead
+// a group) and counts go to the array too; interval pricing has no table and counts into the context's own counters (the
+// array's limit is the same for both, so that a request's outcome does not depend on the data).
 extern "C" vns_status vns_eval_neighbourhood_noalloc(vns_ctx *c, uint32_t nb_mask, int32_t chain, int64_t *slot_price,
                                                      int64_t *prod_best, int32_t *prod_best_slot, int64_t *best,
                                                      int32_t *best_slot) {
