@@ -1795,10 +1795,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 // with speculative iterations or best-of-G.  IV: 1 when every horizon is at most 64, else 2.
 //
 // Bound by a lone wavefront's instruction issue and LDS waits along the chain of shake, one product's VND and acceptance
-// (100 x 52, 64 chains side by side: 17% of the chip's VALU issue).  Full decodes -> interval pricing: 500 iterations of 10 x 12 4.66 -> 2.4 ms; 512 instances
+// (100 x 52, 64 chains side by side: 16% of the chip's VALU issue).  Full decodes -> interval pricing: 500 iterations of 10 x 12 4.66 -> 2.4 ms; 512 instances
 // (K 10..200, T 12, 24 or 52) x 8 chains x 50 5.4 -> 1.17 ms; 64 instances (T 52 or 104) x 16 7.2 -> 0.83 ms; with
 // speculative iterations 100 x 52, 64 chains x 200 1.46 -> 0.65 ms under the profiler; best of 4, 300 x 52 2.2 -> 0.87 ms.
-// Four wavefronts per SIMD for one period a lane, three for two: at four the two-word form spills.
+// Four wavefronts per SIMD for one period a lane, three for two (2 registers spill, 14 under the strict reading; at four
+// many more).
 template <int IV, int MODEL>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(IV == 2 ? 3 : 4))) void k_run_iv(RunArgs a) {
     __shared__ RunShared sh;
