@@ -795,10 +795,9 @@ __device__ __forceinline__ void lds_store(T *p, const T &v) {
     for (size_t i = 0; i < sizeof(T) / 8; ++i) w[i] = r[i];
 }
 
-// The flip of draw j (< kd) of iteration it, as product << 8 | its flip slot (K <= 2^20, 2T <= 256).
-__device__ __forceinline__ uint32_t shake_flip(const RunArgs &a, int g, int64_t it, uint64_t stream, int j, uint64_t n, int T,
-                                               int kd) {
-    if (j >= kd) return 0u;
+// The flip of draw j (< kdraw) of iteration it, as product << 8 | its flip slot (K <= 2^20, 2T <= 256).
+__device__ __forceinline__ uint32_t shake_flip(const RunArgs &a, int g, int64_t it, uint64_t stream, int j, uint64_t n, int T) {
+    if (j >= a.kdraw) return 0u;
     const uint32_t f = shake_draw(a.seed, (uint64_t)g, (uint64_t)it, (uint64_t)j, n, stream), p = f / (uint32_t)(2 * T);
     return p << 8 | (f - p * (uint32_t)(2 * T));
 }
@@ -904,8 +903,6 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
     mlp::Frags fr;
     if constexpr (LEARNED) mlp::load_frags(a.mlp, fr);
     const uint64_t nflip_all = 2ull * (uint64_t)K * (uint64_t)T;
-    // draws of a shake: a chain's k is above k_max when that was lowered after the last run
-    const int kd = max(a.kmax, cs.k);
     const uint64_t stream = COOP && a.best_of ? (uint64_t)slot : 0u;   // best-of-G: each workgroup its own
     if (threadIdx.x == 0) sh.draw_it = -1;
     __syncthreads();
@@ -972,7 +969,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
             // lane j: product and flip slot of draw j, drawn ahead during the last iteration's VND if it guessed this one
             uint32_t f = sh.draw[lane];
             if (sh.draw_it != it) {
-                f = shake_flip(a, g, it, stream, lane, nflip_all, T, kd);
+                f = shake_flip(a, g, it, stream, lane, nflip_all, T);
                 sh.draw[lane] = f;
                 wave_sync_lds();
             }
@@ -1052,7 +1049,7 @@ __device__ __forceinline__ void run_chain(const RunArgs &a, RunShared &sh, SwapL
         // next one if the round is rejected as a whole; a wrong guess is drawn again
         if (wave == W - 1) {
             const int64_t ahead = it + (COOP && !split && !a.best_of ? a.coop_m : 1);
-            sh.draw[lane] = shake_flip(a, g, ahead, stream, lane, nflip_all, T, kd);
+            sh.draw[lane] = shake_flip(a, g, ahead, stream, lane, nflip_all, T);
             if (lane == 0) sh.draw_it = ahead;
         }
 

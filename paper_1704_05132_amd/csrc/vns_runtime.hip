@@ -82,6 +82,7 @@ struct vns_ctx {
     bool compact = false;                 // every product is compact: interval pricing applies (vns_interval.hpp)
     int32_t max_T = 1;
     bool x_opt = true;                    // every run since the chains were set up searched with nb_list
+    int32_t k_seen = 1;                   // the largest k_max of a run since then: no chain's k is above it
     int64_t n_prod = 0;
     uint64_t seed = 0;
     int device = 0;
@@ -377,6 +378,7 @@ static vns_status setup_chains(vns_ctx *c) {
     VNS_HIP(c, hipStreamSynchronize(c->stream));
     c->iteration = 0;
     c->x_opt = true;
+    c->k_seen = 1;
     c->stats = vns_stats{};
     return VNS_OK;
 }
@@ -1149,6 +1151,7 @@ extern "C" vns_status vns_run(vns_ctx *c, int32_t iters) {
     ra.seed = c->seed;
     ra.iters = iters;
     ra.kmax = c->kmax;
+    ra.kdraw = c->k_seen = std::max(c->k_seen, c->kmax);
     ra.nb_list = c->nb_list;
     ra.n_nb = c->n_nb;
     ra.permille = c->permille;

@@ -122,6 +122,7 @@ struct RunArgs {
                             // at most that many periods in total keeps them all in LDS for the whole launch
     int32_t permille;       // learned scorer: price the best-ranked permille/1000 of each neighbourhood; 0 = off
     int32_t learned_pack;   // learned VND: > 1 = products per workgroup batch (packed form), else one at a time
+    int32_t kdraw;          // draws of a shake: no chain's k is above it (k_max may have been lowered since it was set)
     const float *mlp;       // scorer parameters (5313 float32)
     float *log_x;           // move log: [log_cap][16] features, [log_cap] targets, count (null = off)
     float *log_y;

@@ -37,6 +37,29 @@ def test_k_max_lowered_below_a_chains_k(vns, K, T, low, form):
                 assert (zM == c.zM).all() and (zR == c.zR).all(), g
 
 
+@pytest.mark.parametrize("form", ["intervals", "full decode"])
+def test_k_max_lowered_below_the_kept_k(vns, form):
+    """Best of G as printed keeps k: every later shake takes as many flips, whatever k_max has become."""
+    inst = draw_instance(np.random.default_rng([10, 12, 22]), 10, 12)
+    inst.dispose = form == "full decode"
+    with vns.Context(inst, seed=1, chains=4, k_max=64) as ctx:
+        ref = [oracle.Chain(inst, 1, g, k_max=64) for g in range(4)]
+        ctx.run(45)
+        for c in ref:
+            c.run(45)
+        assert any(c.k > 5 for c in ref)
+        ctx.set_option(vns.OPT_KMAX, 2)
+        ctx.set_option(vns.OPT_BEST_OF, 3)
+        ctx.set_option(vns.OPT_BEST_OF_LITERAL, 1)
+        ctx.run(12)
+        for g, c in enumerate(ref):
+            b = oracle.BestOfChain(inst, 1, g, k_max=2, G=3, literal=True)
+            b.zM, b.zR, b.k, b.it, b.F, b.F_best = c.zM, c.zR, c.k, c.it, c.F, c.F_best
+            assert (ctx.trajectory(g) == b.run(12)).all(), g
+            zM, zR = ctx.solution(g)
+            assert (zM == b.zM).all() and (zR == b.zR).all(), g
+
+
 def test_whether_interval_pricing_applies(vns):
     inst = draw_instance(np.random.default_rng(3), 4, 20)
     with vns.Context(inst, seed=1) as ctx:
